@@ -8,6 +8,7 @@
 namespace nb {
 
 constexpr int kBlock = 256;      // threads of every O(N) kernel and of the pair kernels
+constexpr int kDiagJ = 256;      // sources per pair item of the diagnostics
 constexpr int kScanChunkCells = 1024;   // cells per block of the counting sort's scan
 // Sets of drift outputs (what the encounter check of a step reads): one per
 // step of a captured run, so that the checks of a run, on a second queue, hold
@@ -132,7 +133,7 @@ struct Dev {
                           // per stellar drift into ptot instead of by each of its blocks
     double *fpart;        // 3 x maxs x ntot force partials (FP64 pair arithmetic)
     float *fpart32;       // the same in FP32 (FP32C pair arithmetic; fpart is then null)
-    double *dpart;        // ndw x 4 double-double pair sums (E pair, EK pair)
+    double *dpart;        // ndw x 4 double-double pair sums (m m / r, (K - 1) m m / r)
     double *bpart;        // nrb x 16 body partial sums for diagnostics
     double *diag;         // nsys x 8 results: E, EK, L3, P3
     unsigned long long *keys;  int keys_p2;   // encounter keys (i<<32 | j), pow2 capacity

@@ -47,17 +47,16 @@ __device__ __forceinline__ void dd_add(dd &a, const dd &b)
     a.lo += b.lo;
 }
 
-// 1/sqrt(x) in FP64 to the last bits (diagnostics): the hardware estimate
-// refined through (1-e)^(-1/2) ~ 1 + e/2 + 3e^2/8, e = 1 - x y^2, then one
-// Newton step.
+// 1/sqrt(x) in FP64 to the last bits (diagnostics): the hardware estimate y0
+// (relative error at most 2^-24) corrected through (1-e)^(-1/2) = 1 + e/2 +
+// 3e^2/8 + O(e^3), e = 1 - x y0^2: the dropped 5e^3/16 is below 2^-70, so the
+// result carries the rounding of e and of the last operation only, which a
+// further Newton step would carry again.
 __device__ __forceinline__ double rsqrt64_acc(double x)
 {
-    double y = __builtin_amdgcn_rsq(x);
-    double e = fma(-x * y, y, 1.0);
-    double t = fma(0.375, e, 0.5);
-    y = fma(y * e, t, y);
-    e = fma(-x * y, y, 1.0);
-    return fma(0.5 * y, e, y);
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
 // Deterministic block-wide sum of W doubles per thread (kBlock threads, fixed
@@ -3807,9 +3806,57 @@ __global__ __launch_bounds__(kSortThreads) void k_enc_sort(unsigned long long *k
 // ----------------------------------------------------------------------------
 // Diagnostics (Sec. 2.1.1 energy and momentum routine), FP64 with error-free
 // accumulation: per pair work item the double-double sums of m_i m_j / r and of
-// K m_i m_j / r; per body block kinetic, stellar potential, L and P; then one
-// thread per system combines them in a fixed order.
+// (K - 1) m_i m_j / r over the pairs inside the changeover zone; per body block
+// kinetic, stellar potential, L and P; then one workgroup per system combines
+// them in a fixed order.
+//
+// Bound by FP64 issue: 3 differences, 3 for r^2, 6 for the reciprocal root, one
+// product and 7 for the error-free sum per pair.  K differs from 1 only for the
+// few pairs inside rc_ij, so the second error-free sum takes only those pairs'
+// differences, found by one compare per pair against the tile's largest rc^2
+// and one branch per four sources (a branch per pair left every pair a
+// dependent chain of its own).  Items of kDiagJ sources give a system of 16384
+// bodies 2080 workgroups.  16384 bodies: 362 -> 139 us.
 // ----------------------------------------------------------------------------
+constexpr int kDiagU = 4;    // sources per branch
+
+template <bool DIAG>
+__device__ __forceinline__ void diag_tile(const double4 *sj, const double *srj, int cnt, int jt, int i,
+                                          double xi, double yi, double zi, double rci, double thr,
+                                          double inner, dd &acc, dd &chg)
+{
+    for (int j0 = 0; j0 < cnt; j0 += kDiagU) {
+        double r2[kDiagU], y[kDiagU], u[kDiagU];
+        bool rare = false;
+#pragma unroll
+        for (int k = 0; k < kDiagU; ++k) {
+            const double4 J = sj[j0 + k];
+            const double dx = J.x - xi, dy = J.y - yi, dz = J.z - zi;
+            r2[k] = fma(dz, dz, fma(dy, dy, dx * dx));
+            y[k] = rsqrt64_acc(r2[k]);
+            u[k] = J.w * y[k];
+            // on the diagonal only the pairs j > i
+            const bool on = !DIAG || jt + j0 + k > i;
+            if (DIAG)
+                u[k] = on ? u[k] : 0.0;
+            rare |= on && r2[k] < thr;
+        }
+        if (rare) {
+#pragma unroll
+            for (int k = 0; k < kDiagU; ++k) {
+                const double rcij = fmax(rci, srj[j0 + k]);
+                if (!(r2[k] > 0.0))
+                    u[k] = 0.0;            // coincident bodies
+                else if (r2[k] < rcij * rcij && (!DIAG || jt + j0 + k > i))
+                    dd_add(chg, u[k] * (changeover_K(r2[k] * y[k], rcij, inner) - 1.0));
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kDiagU; ++k)
+            dd_add(acc, u[k]);
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void k_diag_pairs(const PWork *__restrict__ work,
                                                        const double *__restrict__ qx,
                                                        const double *__restrict__ qy,
@@ -3819,47 +3866,40 @@ __global__ __launch_bounds__(kBlock) void k_diag_pairs(const PWork *__restrict__
                                                        double *__restrict__ dpart)
 {
     __shared__ double4 sj[kBlock];
-    __shared__ double sh[4 * kBlock];
+    __shared__ double srj[kBlock];
+    __shared__ double sh[4 * kBlock / 64];
+    static_assert(kDiagJ <= kBlock, "a diagnostics item's sources are one LDS tile");
     const PWork wk = work[blockIdx.x];
     const int t = threadIdx.x;
     const bool has_i = t < wk.ni;
     const int i = wk.i0 + (has_i ? t : 0);
-    const double xi = qx[i], yi = qy[i], zi = qz[i], rci = rc[i];
-    dd acc = {0.0, 0.0}, acck = {0.0, 0.0};
-    const int jend = wk.j0 + wk.nj;
-    __shared__ double srj[kBlock];
-    for (int jt = wk.j0; jt < jend; jt += kBlock) {
-        const int cnt = min(kBlock, jend - jt);
-        __syncthreads();
-        if (t < cnt) {
-            int j = jt + t;
-            sj[t] = make_double4(qx[j], qy[j], qz[j], m[j]);
-            srj[t] = rc[j];
-        }
-        __syncthreads();
-        for (int jj = 0; jj < cnt; ++jj) {
-            const int j = jt + jj;
-            if (!has_i || j <= i)
-                continue;
-            double4 J = sj[jj];
-            double dx = J.x - xi, dy = J.y - yi, dz = J.z - zi;
-            double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-            if (!(r2 > 0.0))
-                continue;
-            double y = rsqrt64_acc(r2);
-            double u = J.w * y;
-            dd_add(acc, u);
-            double rcij = fmax(rci, srj[jj]);
-            if (r2 < rcij * rcij) {
-                double r = r2 * y;
-                u *= changeover_K(r, rcij, inner);
-            }
-            dd_add(acck, u);
-        }
+    const double xi = qx[i], yi = qy[i], zi = qz[i], rci = rc[i], mi = has_i ? m[i] : 0.0;
+    // sources past the end, up to a whole group of kDiagU, are massless and far
+    // away; the largest rc^2 of the tile, never below DBL_MIN (coincident bodies)
+    double tmax = DBL_MIN;
+    {
+        const bool ok = t < wk.nj;
+        const int j = wk.j0 + (ok ? t : 0);
+        const double rcj = ok ? rc[j] : 0.0;
+        sj[t] = ok ? make_double4(qx[j], qy[j], qz[j], m[j]) : make_double4(1e150, 1e150, 1e150, 0.0);
+        srj[t] = rcj;
+        tmax = wave_max(fmax(tmax, rcj * rcj));
+        if ((t & 63) == 0)
+            sh[t >> 6] = tmax;
     }
-    double mi = has_i ? m[i] : 0.0;
+    __syncthreads();
+    double thr = fmax(rci * rci, tmax);
+    for (int w = 0; w < kBlock / 64; ++w)
+        thr = fmax(thr, sh[w]);
+    __syncthreads();
+    dd acc = {0.0, 0.0}, chg = {0.0, 0.0};
+    const int cnt = (wk.nj + kDiagU - 1) / kDiagU * kDiagU;
+    if (wk.j0 < wk.i0 + wk.ni)
+        diag_tile<true>(sj, srj, cnt, wk.j0, i, xi, yi, zi, rci, thr, inner, acc, chg);
+    else
+        diag_tile<false>(sj, srj, cnt, wk.j0, i, xi, yi, zi, rci, thr, inner, acc, chg);
     // m_i times the per-target sums, then a fixed-tree sum of the (hi, lo) parts
-    double v[4] = {mi * acc.hi, mi * acc.lo, mi * acck.hi, mi * acck.lo};
+    double v[4] = {mi * acc.hi, mi * acc.lo, mi * chg.hi, mi * chg.lo};
     block_sum<4>(v, sh);
     if (t == 0)
         for (int w = 0; w < 4; ++w)
@@ -3894,39 +3934,57 @@ __global__ void k_diag_bodies(const RBlk *__restrict__ rblk, const double *__res
             bpart[(size_t)blockIdx.x * 8 + w] = v[w];
 }
 
-__global__ void k_diag_final(int nsys, const int *__restrict__ rb_first,
-                             const int *__restrict__ rb_count, const int *__restrict__ dw_first,
-                             const int *__restrict__ dw_count, const double *__restrict__ bpart,
-                             const double *__restrict__ dpart, const double *__restrict__ m0,
-                             double G, double *__restrict__ out)
+// One workgroup per system: thread t takes every kBlock-th partial from t on,
+// then the threads' double-double sums are added pairwise in a fixed tree.
+// (One thread walking a system's partials in order took 106 us at 16384 bodies:
+// one dependent chain of loads and error-free sums; now 7 us.)
+__global__ __launch_bounds__(kBlock) void k_diag_final(
+    const int *__restrict__ rb_first, const int *__restrict__ rb_count,
+    const int *__restrict__ dw_first, const int *__restrict__ dw_count,
+    const double *__restrict__ bpart, const double *__restrict__ dpart,
+    const double *__restrict__ m0, double G, double *__restrict__ out)
 {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= nsys)
-        return;
-    dd q[8];
-    for (int w = 0; w < 8; ++w)
+    // columns 0-7: the body sums; 8: m m / r; 9: (K - 1) m m / r
+    __shared__ dd sh[10][kBlock];
+    const int s = blockIdx.x, t = threadIdx.x;
+    dd q[10];
+    for (int w = 0; w < 10; ++w)
         q[w] = {0.0, 0.0};
-    for (int b = rb_first[s], e = b + rb_count[s]; b < e; ++b)
+    for (int b = rb_first[s] + t, e = rb_first[s] + rb_count[s]; b < e; b += kBlock)
         for (int w = 0; w < 8; ++w)
             dd_add(q[w], bpart[(size_t)b * 8 + w]);
-    dd pe = {0.0, 0.0}, pk = {0.0, 0.0};
-    for (int k = dw_first[s], e = k + dw_count[s]; k < e; ++k) {
-        dd_add(pe, dd{dpart[(size_t)k * 4 + 0], dpart[(size_t)k * 4 + 1]});
-        dd_add(pk, dd{dpart[(size_t)k * 4 + 2], dpart[(size_t)k * 4 + 3]});
+    for (int k = dw_first[s] + t, e = dw_first[s] + dw_count[s]; k < e; k += kBlock) {
+        dd_add(q[8], dd{dpart[(size_t)k * 4 + 0], dpart[(size_t)k * 4 + 1]});
+        dd_add(q[9], dd{dpart[(size_t)k * 4 + 2], dpart[(size_t)k * 4 + 3]});
     }
-    double P0 = q[5].hi + q[5].lo, P1 = q[6].hi + q[6].lo, P2 = q[7].hi + q[7].lo;
+    for (int w = 0; w < 10; ++w)
+        sh[w][t] = q[w];
+    __syncthreads();
+    for (int o = kBlock / 2; o > 0; o >>= 1) {
+        // the o sums of each column, spread over the workgroup
+        for (int k = t; k < 10 * o; k += kBlock) {
+            const int w = k / o, e = k % o;
+            dd_add(sh[w][e], sh[w][e + o]);
+        }
+        __syncthreads();
+    }
+    if (t != 0)
+        return;
+    for (int w = 0; w < 10; ++w)
+        q[w] = sh[w][0];
+    const double P0 = q[5].hi + q[5].lo, P1 = q[6].hi + q[6].lo, P2 = q[7].hi + q[7].lo;
     dd base = q[0];
     dd_add(base, G * q[1].hi);
     dd_add(base, G * q[1].lo);
     dd_add(base, (P0 * P0 + P1 * P1 + P2 * P2) / (2.0 * m0[s]));
-    dd e1 = base, e2 = base;
-    dd_add(e1, -G * pe.hi);
-    dd_add(e1, -G * pe.lo);
-    dd_add(e2, -G * pk.hi);
-    dd_add(e2, -G * pk.lo);
+    dd_add(base, -G * q[8].hi);
+    dd_add(base, -G * q[8].lo);
+    dd ek = base;
+    dd_add(ek, -G * q[9].hi);
+    dd_add(ek, -G * q[9].lo);
     double *o = out + (size_t)s * 8;
-    o[0] = e1.hi + e1.lo;
-    o[1] = e2.hi + e2.lo;
+    o[0] = base.hi + base.lo;
+    o[1] = ek.hi + ek.lo;
     o[2] = q[2].hi + q[2].lo;
     o[3] = q[3].hi + q[3].lo;
     o[4] = q[4].hi + q[4].lo;
@@ -4906,8 +4964,8 @@ hipError_t launch_diagnostics(const Dev &d, const Params &p, hipStream_t s)
                                                 d.vz, d.bpart);
     const int *dw_first = d.nsplit + d.nsys;      // laid out after nsplit by the runtime
     const int *dw_count = dw_first + d.nsys;
-    k_diag_final<<<cdiv(d.nsys, 64), 64, 0, s>>>(d.nsys, d.rb_first, d.rb_count, dw_first,
-                                                  dw_count, d.bpart, d.dpart, d.m0, p.G, d.diag);
+    k_diag_final<<<d.nsys, kBlock, 0, s>>>(d.rb_first, d.rb_count, dw_first, dw_count, d.bpart,
+                                           d.dpart, d.m0, p.G, d.diag);
     return hipGetLastError();
 }
 

@@ -473,7 +473,7 @@ void build_tables(const Params &p, int nsys, const int32_t *off, const int32_t *
         }
         pair_items(a, n, nb, p.enc_j, t.ework);
         t.dw_first[s] = (int)t.dwork.size();
-        pair_items(a, n, nb, p.enc_j, t.dwork);
+        pair_items(a, n, nb, kDiagJ, t.dwork);
         t.dw_count[s] = (int)t.dwork.size() - t.dw_first[s];
     }
     // few-source force kernels: every system's sources fit one LDS slice (and one
