@@ -92,11 +92,15 @@ typedef struct nb_params {
     double  drag_rho_p;   /* bulk density of the bodies (mass / length^3) */
     int32_t force_jchunk; /* sources per force work item (0: tuned default) */
     int32_t force_r;      /* targets per lane in the force kernel: 1, 2 or 4 (0: default) */
-    int32_t enc_jchunk;   /* sources per encounter work item (0: default) */
-    int32_t enc_algo;     /* encounter check: 0 automatic, 1 every pair through a per-pair
-                             reach filter, 2 spatially sorted tiles with tile-pair culling,
-                             3 every body against the big bodies of its system (at most 256
-                             big bodies per system; automatic when some bodies are small),
+    int32_t enc_jchunk;   /* most sources per work item of the direct encounter check (0: 1024;
+                             halved while the items are too few to fill the GPU) */
+    int32_t enc_algo;     /* encounter check: 0 automatic (1 or 3 for systems of up to about
+                             10000 bodies, 2 for larger ones, whose steps hide it behind the
+                             force; nb_encounters after nb_drift then still runs 1 up to about
+                             40000 bodies: the same list), 1 every pair with a big member
+                             through a matrix-core filter, 2 spatially sorted tiles with
+                             tile-pair culling, 3 as 1 for systems of at most 256 big bodies
+                             (automatic when some bodies are small),
                              4 in nb_step the check of 2 done inside the force pass, which
                              then runs over the sorted order (Sec. 3.1 force and encounter
                              blocks in one tile loop; FP32C, every body big, resolve 0 and

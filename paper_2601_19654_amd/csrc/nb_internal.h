@@ -8,6 +8,7 @@
 namespace nb {
 
 constexpr int kBlock = 256;      // threads of every O(N) kernel and of the pair kernels
+constexpr int kEncTargets = 128; // targets per pair item of the direct encounter check
 constexpr int kDiagJ = 256;      // sources per pair item of the diagnostics
 constexpr int kScanChunkCells = 1024;   // cells per block of the counting sort's scan
 // Sets of drift outputs (what the encounter check of a step reads): one per
@@ -92,6 +93,7 @@ struct Snap {
     double *q0x, *q0y, *q0z, *v0x, *v0y, *v0z;
     double *q1x, *q1y, *q1z, *v1x, *v1y, *v1z, *rc1;
     double4 *mr, *cr;
+    void *eq;
     double *lnr_part;
 };
 
@@ -109,6 +111,9 @@ struct Dev {
     float4 *pk;           // FP32C source records: 2 per body {xhi,yhi,zhi,m},{xlo,ylo,zlo,rc2}
     double4 *mr;          // per body after a drift: chord midpoint (x,y,z) and encounter reach R
     double4 *cr;          // per body after a drift: chord Q1 - Q0 and 3/4 eps (widened)
+    void *eq;             // direct check, per body after a drift: two records of 8 halves (else null)
+    void *eq_alone;       // sorted check in steps, direct check elsewhere: set 0's records (else null)
+    double *scale2;       // nsys: largest |Q|^2 at the upload (the records' unit)
     int *kflag, *ce, *sys_of;
     double *m0;           // nsys
     int *off;             // nsys+1
@@ -142,7 +147,7 @@ struct Dev {
     DevStats *stats;
     // sorted encounter check
     int enc_sorted;
-    int enc_few;          // few big bodies: each body against its system's big bodies
+    int enc_few;          // the direct check chosen for few big bodies (reported as such)
     double *lnr_part;     // nrb x 2: min, max of ln R (cylindrical) of chord midpoints
     int *cell_of, *slot_of;   // ntot
     int *cell_cnt, *cell_off; int ncell;
@@ -203,7 +208,19 @@ struct Dev {
 
     Snap snap() const
     {
-        return Snap{q0x, q0y, q0z, v0x, v0y, v0z, q1x, q1y, q1z, v1x, v1y, v1z, rc1, mr, cr, lnr_part};
+        return Snap{q0x, q0y, q0z, v0x, v0y, v0z, q1x, q1y, q1z, v1x, v1y, v1z, rc1, mr, cr, eq,
+                    lnr_part};
+    }
+    // for a drift and its check with nothing beside them (set 0 of the drift
+    // outputs): the direct check where the context keeps its records
+    Dev alone() const
+    {
+        Dev e = *this;
+        if (eq_alone) {
+            e.eq = eq_alone;
+            e.enc_sorted = 0;
+        }
+        return e;
     }
     // this context with the drift outputs of set `set` (0: the first set)
     Dev with_snap(int set) const
@@ -215,7 +232,7 @@ struct Dev {
             e.v0x = a.v0x; e.v0y = a.v0y; e.v0z = a.v0z;
             e.q1x = a.q1x; e.q1y = a.q1y; e.q1z = a.q1z;
             e.v1x = a.v1x; e.v1y = a.v1y; e.v1z = a.v1z;
-            e.rc1 = a.rc1; e.mr = a.mr; e.cr = a.cr; e.lnr_part = a.lnr_part;
+            e.rc1 = a.rc1; e.mr = a.mr; e.cr = a.cr; e.eq = a.eq; e.lnr_part = a.lnr_part;
         }
         return e;
     }
@@ -226,8 +243,9 @@ struct Params {
     int mode, drag;
     double sigma0, h, cd, rho_p;
     int force_r, force_j, enc_j;
-    int enc_algo;         // 1: all pairs with the reach prefilter, 2: sorted tiles,
-                          // 3: each body against its system's big bodies (at most kBlock)
+    int enc_algo;         // 1: every pair with a big member, 2: sorted tiles, 3: as 1, for
+                          // systems of at most kBlock big bodies
+    int enc_auto;         // 1: the caller left enc_algo to the library
     int step_algo;        // 1: per-phase launches, 2: persistent per-system launch
     int force_algo;       // 0 automatic, 1 ordered pairs, 2 symmetric tile pairs, 4 symmetric
                           // over the radial order (FP32C; FP64: as 2)

@@ -59,6 +59,17 @@ __device__ __forceinline__ double rsqrt64_acc(double x)
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
+// Largest value over the wave, returned in a scalar register (every lane active).
+__device__ __forceinline__ double wave_max(double v)
+{
+    for (int o = 32; o > 0; o >>= 1)
+        v = fmax(v, __shfl_xor(v, o));
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffLL));
+    const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
 // Deterministic block-wide sum of W doubles per thread (kBlock threads, fixed
 // order): each wave's 64 values by an xor-shuffle butterfly (both lanes of a
 // pair add the same two values, so every lane ends with the same bits), then
@@ -157,10 +168,13 @@ __global__ void k_fill_i32(int *p, int n, int value)
 __global__ void k_validate(int ntot, int nsys, const double *__restrict__ m0,
                            const double *__restrict__ m, const double *__restrict__ x,
                            const double *__restrict__ v, const int *__restrict__ sys_of,
-                           const int *__restrict__ off, const int *__restrict__ nbig, int *flag)
+                           const int *__restrict__ off, const int *__restrict__ nbig, int *flag,
+                           double *__restrict__ scale2)
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     int bad = 0;
+    if (i < nsys)
+        scale2[i] = 0.0;
     if (i < ntot) {
         double mi = m[i];
         bad = (!isfinite(mi) || mi < 0.0) ? 1 : 0;
@@ -203,11 +217,15 @@ __global__ void k_to_dh(const RBlk *__restrict__ rblk, const int *__restrict__ r
                         const int *__restrict__ rb_count, const double *__restrict__ m0,
                         const double *__restrict__ part, int ntot, const double *__restrict__ x,
                         const double *__restrict__ v, int helio, double *qx, double *qy,
-                        double *qz, double *vx, double *vy, double *vz)
+                        double *qz, double *vx, double *vy, double *vz,
+                        double *__restrict__ scale2)
 {
+    // scale2: also the largest |Q|^2 of every system (cleared before; non-negative
+    // doubles order like their bits)
     __shared__ double sh[4 * kBlock];
     RBlk b = rblk[blockIdx.x];
     double c[3] = {0.0, 0.0, 0.0};
+    double r2 = 0.0;
     if (helio) {
         double P[4];
         system_sum<4>(part, 4, rb_first[b.sys], rb_count[b.sys], P, sh);
@@ -218,12 +236,25 @@ __global__ void k_to_dh(const RBlk *__restrict__ rblk, const int *__restrict__ r
     }
     int i = b.start + threadIdx.x;
     if (i < b.end) {
-        qx[i] = x[i];
-        qy[i] = x[(size_t)ntot + i];
-        qz[i] = x[(size_t)2 * ntot + i];
+        const double x0 = x[i], x1 = x[(size_t)ntot + i], x2 = x[(size_t)2 * ntot + i];
+        qx[i] = x0;
+        qy[i] = x1;
+        qz[i] = x2;
         vx[i] = v[i] - c[0];
         vy[i] = v[(size_t)ntot + i] - c[1];
         vz[i] = v[(size_t)2 * ntot + i] - c[2];
+        r2 = x0 * x0 + x1 * x1 + x2 * x2;
+    }
+    r2 = wave_max(r2);
+    if ((threadIdx.x & 63) == 0)
+        sh[threadIdx.x >> 6] = r2;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kBlock / 64; ++w)
+            r2 = fmax(r2, sh[w]);
+        // (a block below the largest so far leaves it alone)
+        if (r2 > __hip_atomic_load(&scale2[b.sys], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax((unsigned long long *)&scale2[b.sys], (unsigned long long)__double_as_longlong(r2));
     }
 }
 
@@ -596,6 +627,67 @@ __device__ int kepler_drift(double mu, double dt, double &x, double &y, double &
     return 0;
 }
 
+// The matrix-core filter of the direct encounter check (k_enc_direct): a pair can
+// only be flagged when D^2 <= 2 C^2 + 2 S^2 with D, C the distances of the two
+// chord midpoints M and chords c, and S = 3/4 (eps_i + eps_j) + rc_ij <= s_i + s_j,
+// s = 3/4 eps + rc (k_enc_direct).  Written out, D^2 - 2 C^2 - 2 (s_i + s_j)^2 =
+// al_i + al_j + sum_k g_k u_ik u_jk with u = (M, c, s), g = (-2 -2 -2 4 4 4 -4)
+// and al = |M|^2 - 2|c|^2 - 2 s^2: a product of two matrices.  Each u (in units of
+// the system's scale L, a power of two) is split into two FP16 values, 22 bits,
+// and al, reduced by the body's share of the error bound, likewise; the 32
+// products of a pair are exact in the matrix core's FP32 sum.
+// Bound of the error, with nn = |M|^2 + 2|c|^2 + 2 s^2 (the terms' magnitudes add up
+// to at most 2 (nn_i + nn_j)): splitting 2^-21 (nn_i + nn_j), summing 32 terms
+// (measured: 2^-21 of their magnitudes) 2^-20 (nn_i + nn_j), FP16 values below
+// 2^-14 in steps of 2^-24: 2^-22 (sqrt nn_i + sqrt nn_j) and 2^-31.  The shares
+// below are at least four times that.  A body outside 8 L (or not finite) gets a
+// record that makes a candidate of each of its pairs.
+constexpr double kEncK1 = 0x1p-17, kEncK2 = 0x1p-20, kEncK3 = 0x1p-28;
+constexpr double kEncMax = 8.0;                 // largest component of u / L
+constexpr double kEncAlUnit = 64.0;             // al is stored times this ...
+constexpr double kEncAlOut = -60000.0;          // ... and this for a body outside 8 L
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// 1/L of a system from the largest |Q|^2 of its bodies at the upload: L the power
+// of two at or above |Q| (1 when there is none).
+__device__ __forceinline__ double enc_inv_scale(double r2)
+{
+    if (!(r2 > 0.0) || !isfinite(r2))
+        return 1.0;
+    return ldexp(1.0, -(ilogb(r2) / 2 + 1));
+}
+
+// The record of a body: (u_hi, al_hi), (u_lo, al_lo).
+__device__ __forceinline__ void enc_record(double mx, double my, double mz, double cx, double cy,
+                                           double cz, double sb, double inv_l, v8h *out)
+{
+    const double u[7] = {mx * inv_l, my * inv_l, mz * inv_l, cx * inv_l, cy * inv_l, cz * inv_l, sb * inv_l};
+    const double M2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+    const double C2 = 2.0 * (u[3] * u[3] + u[4] * u[4] + u[5] * u[5] + u[6] * u[6]);
+    const double nn = M2 + C2;
+    const double al = (M2 - C2 - (kEncK1 * nn + kEncK2 * sqrt(nn) + kEncK3)) * kEncAlUnit;
+    v8h hi, lo;
+    bool in = true;
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+        in = in && fabs(u[k]) <= kEncMax;
+        hi[k] = (_Float16)u[k];
+        lo[k] = (_Float16)(u[k] - (double)hi[k]);
+    }
+    hi[7] = (_Float16)al;
+    lo[7] = (_Float16)(al - (double)hi[7]);
+    if (!in) {
+#pragma unroll
+        for (int k = 0; k < 7; ++k)
+            hi[k] = lo[k] = (_Float16)0.0f;
+        hi[7] = (_Float16)(float)kEncAlOut;
+        lo[7] = (_Float16)0.0f;
+    }
+    out[0] = hi;
+    out[1] = lo;
+}
+
 // Snapshot, drift, failure flags and counters, the encounter check's records,
 // and the partial sums of m V after the drift (for the second stellar drift).
 // The check clears its own list and flags, since it may run beside the next drift.
@@ -613,8 +705,11 @@ __global__ void k_drift(const RBlk *__restrict__ rblk, const double *__restrict_
                         double *__restrict__ v1y, double *__restrict__ v1z,
                         double *__restrict__ rc1, const double *__restrict__ part_in,
                         double sun_h, const int *__restrict__ rb_first,
-                        const int *__restrict__ rb_count, const double *__restrict__ ptot)
+                        const int *__restrict__ rb_count, const double *__restrict__ ptot,
+                        v8h *__restrict__ eq, const double *__restrict__ scale2)
 {
+    // the encounter check's records: eq (direct check) or mr, cr and the ln R
+    // range (sorted check)
     __shared__ double sh[3 * kBlock];
     double lnr_lo = INFINITY, lnr_hi = -INFINITY;
     RBlk b = rblk[blockIdx.x];
@@ -656,29 +751,32 @@ __global__ void k_drift(const RBlk *__restrict__ rblk, const double *__restrict_
         v0y[i] = v;
         v0z[i] = w;
         fail = kepler_drift(mu, dt, x, y, z, u, v, w) != 0;
-        // Encounter reach of this body over the step: chord c = Q1 - Q0 with
-        // half-length rho, endpoint velocity deviations e = dt V - c with
-        // largest norm eps; R = 2 rho + 3 eps/4 + rc (widened by 2^-20 for
-        // rounding).  Pairs whose chord midpoints are farther apart than
-        // R_i + R_j cannot be flagged (see k_encounter).
+        // Encounter data of this body over the step: chord c = Q1 - Q0 with
+        // half-length rho, midpoint M, endpoint velocity deviations e = dt V - c
+        // with largest norm eps (see k_enc_direct).
         {
             double cx = x - sx, cy = y - sy, cz = z - sz;
             double rho = 0.5 * sqrt(cx * cx + cy * cy + cz * cz);
             double ax0 = dt * us - cx, ay0 = dt * vs - cy, az0 = dt * ws - cz;
             double ax1 = dt * u - cx, ay1 = dt * v - cy, az1 = dt * w - cz;
             double eps = sqrt(fmax(ax0 * ax0 + ay0 * ay0 + az0 * az0, ax1 * ax1 + ay1 * ay1 + az1 * az1));
-            double R = (2.0 * rho + 0.75 * eps + rci) * (1.0 + 0x1p-20);
             double mx = sx + 0.5 * cx, my = sy + 0.5 * cy, mz = sz + 0.5 * cz;
-            mr[i] = make_double4(mx, my, mz, R);
             // relative pair filter data: the chord and 3/4 eps, widened by 2^-20
             // and by 2^-45 (|M| + |c|) to cover the rounding of midpoint and chord
-            // differences (see k_encounter)
+            // differences
             double e34 = 0.75 * eps * (1.0 + 0x1p-20) +
                          0x1p-45 * (sqrt(mx * mx + my * my + mz * mz) + 2.0 * rho);
-            cr[i] = make_double4(cx, cy, cz, e34);
-            double lnr = log(fmax(sqrt(mx * mx + my * my), 1e-300));
-            lnr_lo = lnr;
-            lnr_hi = lnr;
+            if (eq) {
+                enc_record(mx, my, mz, cx, cy, cz, e34 + rci, enc_inv_scale(scale2[b.sys]),
+                           eq + 2 * (size_t)i);
+            } else {
+                double R = (2.0 * rho + 0.75 * eps + rci) * (1.0 + 0x1p-20);
+                mr[i] = make_double4(mx, my, mz, R);
+                cr[i] = make_double4(cx, cy, cz, e34);
+                double lnr = log(fmax(sqrt(mx * mx + my * my), 1e-300));
+                lnr_lo = lnr;
+                lnr_hi = lnr;
+            }
         }
         qx[i] = x;
         qy[i] = y;
@@ -1229,17 +1327,6 @@ __device__ __forceinline__ double rinv3(double r2)
     const double y2 = y0 * y0;
     const double e = fma(-r2, y2, 1.0);
     return (y0 * y2) * fma(1.5, e, 1.0);
-}
-
-// Largest value over the wave, returned in a scalar register (every lane active).
-__device__ __forceinline__ double wave_max(double v)
-{
-    for (int o = 32; o > 0; o >>= 1)
-        v = fmax(v, __shfl_xor(v, o));
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffLL));
-    const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
 // max of two non-negative finite floats through their bit patterns (one
@@ -2272,252 +2359,183 @@ __device__ double hermite_min(double f0, double f1, double g0, double g1)
     return fmax(best, 0.0);
 }
 
-struct EncRec {
+// The exact test's fields of one record.
+struct HRec {
     double q0[3], v0[3], q1[3], v1[3];
-    double rc, pad;
+    double rc;
+    int body;
 };
 
-// Two-stage pair test, one target per lane, sources broadcast from LDS.
-// Stage 1 (every pair): chord midpoints M and reaches R (from the drift).  The
-// Hermite data split into the straight-chord part |dQ0 + s dc|^2 (which the
-// cubic reproduces exactly and which is >= (D - rho_i - rho_j)^2, D = |dM|)
-// and the endpoint velocity deviations e = dt V - c, weighted by h10(s) and
-// h11(s) with |h10| + |h11| = s(1-s) <= 1/4.  So
-// f(s) >= (D-P)^2 - (1/2)(D+P)E with P = rho_i + rho_j, E = eps_i + eps_j,
-// which exceeds (rc_i + rc_j)^2 >= rc_ij^2 whenever D > R_i + R_j with
-// R = 2 rho + 3 eps/4 + rc.  So only pairs with |dM|^2 <= (R_i + R_j)^2 go on.
-// Stage 1b (relative chords): the same split around the relative chord dc =
-// c_j - c_i gives f(s) >= (D - a)^2 - (1/2)(D + a)E with a = |dc|/2, which
-// exceeds rc_ij^2 whenever D > |dc| + 3E/4 + rc_ij; as (x + y)^2 <= 2x^2 + 2y^2,
-// pairs with D^2 > 2|dc|^2 + 2(3E/4 + rc_ij)^2 are dropped.  Bodies moving
-// together (neighbours on similar orbits) have short relative chords, so this
-// keeps far fewer pairs than stage 1 when steps are long.  The 3/4 eps term
-// stored per body is widened by 2^-20 and by 2^-45 (|M| + |c|) for the rounding
-// of the differences.
-// Stage 2 (candidates): the 4/27 lower bound on the full Hermite data, then
-// the exact minimum.
-__global__ __launch_bounds__(kBlock) void k_encounter(const PWork *__restrict__ work, double dt,
-                                                      const double4 *__restrict__ mr,
-                                                      const double4 *__restrict__ cr,
-                                                      const double *__restrict__ q0x,
-                                                      const double *__restrict__ q0y,
-                                                      const double *__restrict__ q0z,
-                                                      const double *__restrict__ v0x,
-                                                      const double *__restrict__ v0y,
-                                                      const double *__restrict__ v0z,
-                                                      const double *__restrict__ qx,
-                                                      const double *__restrict__ qy,
-                                                      const double *__restrict__ qz,
-                                                      const double *__restrict__ vx,
-                                                      const double *__restrict__ vy,
-                                                      const double *__restrict__ vz,
-                                                      const double *__restrict__ rc,
-                                                      unsigned long long *__restrict__ keys,
-                                                      int cap, int *__restrict__ ce,
-                                                      DevStats *stats)
+// Exact encounter test of a pair (the Hermite bound, then the minimum over the
+// step) and the append of a flagged pair.  J: an HRec or a sorted record.
+template <typename R>
+__device__ __forceinline__ void enc_exact(const HRec &I, const R &J, double dt,
+                                          unsigned long long *keys, int cap, int *ce,
+                                          DevStats *stats)
 {
-    __shared__ double4 smr[kBlock];
-    __shared__ double4 scr[kBlock];
-    __shared__ EncRec sj[kBlock];
-    const PWork wk = work[blockIdx.x];
-    const int t = threadIdx.x;
-    const int lane = t & 63;
-    const double t2 = 2.0 * dt;
-    const double k427 = 4.0 / 27.0;
-    const bool has_i = t < wk.ni;
-    const int i = wk.i0 + (has_i ? t : 0);
-    const double4 Mi = mr[i];
-    const double4 Ci = cr[i];
-    const double a0[3] = {q0x[i], q0y[i], q0z[i]}, b0[3] = {v0x[i], v0y[i], v0z[i]};
-    const double a1[3] = {qx[i], qy[i], qz[i]}, b1[3] = {vx[i], vy[i], vz[i]};
-    const double rci = rc[i];
-    const int jend = wk.j0 + wk.nj;
-    for (int jt = wk.j0; jt < jend; jt += kBlock) {
-        const int cnt = min(kBlock, jend - jt);
-        __syncthreads();
-        if (t < cnt) {
-            int j = jt + t;
-            smr[t] = mr[j];
-            scr[t] = cr[j];
-            EncRec r;
-            r.q0[0] = q0x[j]; r.q0[1] = q0y[j]; r.q0[2] = q0z[j];
-            r.v0[0] = v0x[j]; r.v0[1] = v0y[j]; r.v0[2] = v0z[j];
-            r.q1[0] = qx[j];  r.q1[1] = qy[j];  r.q1[2] = qz[j];
-            r.v1[0] = vx[j];  r.v1[1] = vy[j];  r.v1[2] = vz[j];
-            r.rc = rc[j];
-            r.pad = 0.0;
-            sj[t] = r;
-        }
-        __syncthreads();
-        // only tiles that reach past the target index hold pairs j > i
-        const bool diag = jt < wk.i0 + wk.ni;
-        for (int jj = 0; jj < cnt; ++jj) {
-            const int j = jt + jj;
-            const double4 Mj = smr[jj];
-            double dx = Mj.x - Mi.x, dy = Mj.y - Mi.y, dz = Mj.z - Mi.z;
-            double D2 = fma(dz, dz, fma(dy, dy, dx * dx));
-            double S = Mi.w + Mj.w;
-            bool cand = has_i && D2 <= S * S && (!diag || j > i);
-            if (!__any(cand))
-                continue;
-            {
-                // relative chord filter
-                const double4 Cj = scr[jj];
-                double cx = Cj.x - Ci.x, cy = Cj.y - Ci.y, cz = Cj.z - Ci.z;
-                double C2 = fma(cz, cz, fma(cy, cy, cx * cx));
-                double bb = Ci.w + Cj.w + fmax(rci, sj[jj].rc);
-                cand = cand && D2 <= fma(2.0, C2, 2.0 * bb * bb) * (1.0 + 0x1p-20);
-            }
-            if (!__any(cand))
-                continue;
-            bool hit = false;
-            if (cand) {
-                const EncRec &J = sj[jj];
-                double d0x = J.q0[0] - a0[0], d0y = J.q0[1] - a0[1], d0z = J.q0[2] - a0[2];
-                double d1x = J.q1[0] - a1[0], d1y = J.q1[1] - a1[1], d1z = J.q1[2] - a1[2];
-                double e0x = J.v0[0] - b0[0], e0y = J.v0[1] - b0[1], e0z = J.v0[2] - b0[2];
-                double e1x = J.v1[0] - b1[0], e1y = J.v1[1] - b1[1], e1z = J.v1[2] - b1[2];
-                double f0 = fma(d0z, d0z, fma(d0y, d0y, d0x * d0x));
-                double f1 = fma(d1z, d1z, fma(d1y, d1y, d1x * d1x));
-                double g0 = t2 * fma(d0z, e0z, fma(d0y, e0y, d0x * e0x));
-                double g1 = t2 * fma(d1z, e1z, fma(d1y, e1y, d1x * e1x));
-                double lower = fmin(f0, f1) - k427 * (fmax(0.0, -g0) + fmax(0.0, g1));
-                double rcij = fmax(rci, J.rc);
-                double thr = rcij * rcij;
-                if (lower <= thr * (1.0 + 1e-6) + 1e-15 * (f0 + f1 + fabs(g0) + fabs(g1)))
-                    hit = hermite_min(f0, f1, g0, g1) <= thr;
-            }
-            unsigned long long mask = __ballot(hit);
-            if (mask) {
-                int leader = __ffsll((long long)mask) - 1;
-                int base = 0;
-                if (lane == leader)
-                    base = atomicAdd(&stats->cur_nce, (int)__popcll(mask));
-                base = __shfl(base, leader);
-                if (hit) {
-                    unsigned long long below = mask & ((1ull << lane) - 1ull);
-                    int pos = base + (int)__popcll(below);
-                    if (pos < cap)
-                        keys[pos] = ((unsigned long long)(unsigned)i << 32) | (unsigned)j;
-                    __hip_atomic_store(&ce[i], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(&ce[j], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-            }
-        }
-    }
+    const double t2 = 2.0 * dt, k427 = 4.0 / 27.0;
+    const double d0x = J.q0[0] - I.q0[0], d0y = J.q0[1] - I.q0[1], d0z = J.q0[2] - I.q0[2];
+    const double d1x = J.q1[0] - I.q1[0], d1y = J.q1[1] - I.q1[1], d1z = J.q1[2] - I.q1[2];
+    const double e0x = J.v0[0] - I.v0[0], e0y = J.v0[1] - I.v0[1], e0z = J.v0[2] - I.v0[2];
+    const double e1x = J.v1[0] - I.v1[0], e1y = J.v1[1] - I.v1[1], e1z = J.v1[2] - I.v1[2];
+    const double f0 = fma(d0z, d0z, fma(d0y, d0y, d0x * d0x));
+    const double f1 = fma(d1z, d1z, fma(d1y, d1y, d1x * d1x));
+    const double g0 = t2 * fma(d0z, e0z, fma(d0y, e0y, d0x * e0x));
+    const double g1 = t2 * fma(d1z, e1z, fma(d1y, e1y, d1x * e1x));
+    const double lower = fmin(f0, f1) - k427 * (fmax(0.0, -g0) + fmax(0.0, g1));
+    const double rcij = fmax(I.rc, J.rc);
+    const double thr = rcij * rcij;
+    if (!(lower <= thr * (1.0 + 1e-6) + 1e-15 * (f0 + f1 + fabs(g0) + fabs(g1))))
+        return;
+    if (!(hermite_min(f0, f1, g0, g1) <= thr))
+        return;
+    const int pos = atomicAdd(&stats->cur_nce, 1);
+    const int bi = I.body, bj = J.body;
+    const unsigned lo = (unsigned)min(bi, bj), hi = (unsigned)max(bi, bj);
+    if (pos < cap)
+        keys[pos] = ((unsigned long long)lo << 32) | hi;
+    __hip_atomic_store(&ce[bi], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&ce[bj], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Few big bodies (every system has at most kBlock big bodies; small bodies are
-// massless and never meet each other): one lane per body j of an O(N) block,
-// tested against the big bodies i < j of its system, which the block stages in
-// LDS once.  Same two-stage pair test as k_encounter, so the same pairs are
-// flagged.
-__global__ __launch_bounds__(kBlock) void k_encounter_few(const RBlk *__restrict__ rblk,
-                                                          const int *__restrict__ off,
-                                                          const int *__restrict__ nbig, double dt,
-                                                          const double4 *__restrict__ mr,
-                                                          const double4 *__restrict__ cr,
-                                                          const double *__restrict__ q0x,
-                                                          const double *__restrict__ q0y,
-                                                          const double *__restrict__ q0z,
-                                                          const double *__restrict__ v0x,
-                                                          const double *__restrict__ v0y,
-                                                          const double *__restrict__ v0z,
-                                                          const double *__restrict__ qx,
-                                                          const double *__restrict__ qy,
-                                                          const double *__restrict__ qz,
-                                                          const double *__restrict__ vx,
-                                                          const double *__restrict__ vy,
-                                                          const double *__restrict__ vz,
-                                                          const double *__restrict__ rc,
-                                                          unsigned long long *__restrict__ keys,
-                                                          int cap, int *__restrict__ ce,
-                                                          DevStats *stats)
+// The drift outputs the exact test reads, by body.
+struct EncIn {
+    const double *q0x, *q0y, *q0z, *v0x, *v0y, *v0z, *q1x, *q1y, *q1z, *v1x, *v1y, *v1z, *rc;
+};
+
+__device__ __forceinline__ HRec enc_load(const EncIn &E, int i)
 {
-    __shared__ double4 smr[kBlock];
-    __shared__ double4 scr[kBlock];
-    __shared__ EncRec si[kBlock];
-    const RBlk b = rblk[blockIdx.x];
-    const int t = threadIdx.x;
-    const int lane = t & 63;
-    const int a = off[b.sys], nb = min(nbig[b.sys], kBlock);
-    const double t2 = 2.0 * dt;
-    const double k427 = 4.0 / 27.0;
-    // the system's big bodies
-    if (t < nb) {
-        const int i = a + t;
-        smr[t] = mr[i];
-        scr[t] = cr[i];
-        EncRec r;
-        r.q0[0] = q0x[i]; r.q0[1] = q0y[i]; r.q0[2] = q0z[i];
-        r.v0[0] = v0x[i]; r.v0[1] = v0y[i]; r.v0[2] = v0z[i];
-        r.q1[0] = qx[i];  r.q1[1] = qy[i];  r.q1[2] = qz[i];
-        r.v1[0] = vx[i];  r.v1[1] = vy[i];  r.v1[2] = vz[i];
-        r.rc = rc[i];
-        r.pad = 0.0;
-        si[t] = r;
+    HRec r;
+    r.q0[0] = E.q0x[i]; r.q0[1] = E.q0y[i]; r.q0[2] = E.q0z[i];
+    r.v0[0] = E.v0x[i]; r.v0[1] = E.v0y[i]; r.v0[2] = E.v0z[i];
+    r.q1[0] = E.q1x[i]; r.q1[1] = E.q1y[i]; r.q1[2] = E.q1z[i];
+    r.v1[0] = E.v1x[i]; r.v1[1] = E.v1y[i]; r.v1[2] = E.v1z[i];
+    r.rc = E.rc[i];
+    r.body = i;
+    return r;
+}
+
+// Direct check of every pair i < j with a big member (i big): the filter below as
+// a product of matrices, then the exact test of the pairs it keeps.
+//
+// The Hermite data of a pair split into the straight relative chord, which the
+// cubic reproduces exactly and which stays at least D - |dc|/2 away (D = |dM| the
+// distance of the chord midpoints, dc = c_j - c_i), and the endpoint velocity
+// deviations e = dt V - c, weighted by h10(s) and h11(s) with |h10| + |h11| =
+// s(1-s) <= 1/4.  So f(s) >= (D - a)^2 - (1/2)(D + a)E with a = |dc|/2, E = eps_i +
+// eps_j, which exceeds rc_ij^2 whenever D > |dc| + 3E/4 + rc_ij; as (x + y)^2 <=
+// 2x^2 + 2y^2, pairs with D^2 > 2|dc|^2 + 2(3E/4 + rc_ij)^2 cannot be flagged.
+// Bodies moving together (neighbours on similar orbits) have short relative
+// chords, so this keeps few pairs also when steps are long.
+//
+// A wave owns a work item of up to 128 targets (eight groups of 16, the columns of
+// its matrix products, held in registers) and its sources, 16 at a time (the
+// rows, one 16-byte load per lane): eight 16x16x32 products test 2048 pairs, and
+// the OR of their signs tells whether any is a candidate (enc_record).  The FP32
+// pair test this replaces issued 17 operations per 64 pairs, this one about one
+// and a half; candidates queue in LDS and take the exact test 64 at a time.
+// Bound by the matrix products (128 of about 200 cycles per 2048 pairs), in dense
+// rings with long steps by the exact tests.  Three waves per SIMD: at four the
+// columns spill.  The kernel: 100 bodies 22 -> 5.0 us, 16384 bodies in 0.5-5 AU
+// 14.4 us; the whole check at 1001 bodies 40 -> 8 us (nine launches before).
+__global__ __launch_bounds__(64, 3) void k_enc_direct(const PWork *__restrict__ work,
+                                                   const v8h *__restrict__ eq, EncIn in, double dt,
+                                                   unsigned long long *__restrict__ keys, int cap,
+                                                   int *__restrict__ ce, DevStats *stats)
+{
+    constexpr int NG = kEncTargets / 16;
+    __shared__ int qe[128];
+    const PWork wk = work[blockIdx.x];
+    const int lane = threadIdx.x, q = lane >> 4, r = lane & 15;
+    // columns: K slots 8q .. 8q + 7 are (g u_hi, 1) for even q and (g u_lo, 0) for
+    // odd q, against (u_hi, al_hi) for q < 2 and (u_lo, al_lo) for q >= 2 of the rows
+    v8h col[NG];
+    v4f al[NG];
+    const _Float16 one = (q & 1) ? (_Float16)0.0f : (_Float16)(float)(1.0 / kEncAlUnit);
+    const v8h g = {(_Float16)-2.0f, (_Float16)-2.0f, (_Float16)-2.0f, (_Float16)4.0f,
+                   (_Float16)4.0f,  (_Float16)4.0f,  (_Float16)-4.0f, (_Float16)1.0f};
+#pragma unroll
+    for (int k = 0; k < NG; ++k) {
+        const bool ok = 16 * k + r < wk.ni;
+        const size_t i = 2 * (size_t)(wk.i0 + (ok ? 16 * k + r : 0));
+        const v8h hi = eq[i], lo = eq[i + 1];
+        col[k] = ((q & 1) ? lo : hi) * g;
+        col[k][7] = one;
+        // columns past the targets never go below zero
+        const float a = ok ? ((float)hi[7] + (float)lo[7]) * (float)(1.0 / kEncAlUnit) : 1e30f;
+        al[k] = v4f{a, a, a, a};
     }
-    __syncthreads();
-    const bool has_j = b.start + t < b.end;
-    const int j = b.start + (has_j ? t : 0);
-    const int ni = has_j ? min(nb, j - a) : 0;     // big bodies i < j
-    const double4 Mj = mr[j];
-    const double4 Cj = cr[j];
-    const double a0[3] = {q0x[j], q0y[j], q0z[j]}, b0[3] = {v0x[j], v0y[j], v0z[j]};
-    const double a1[3] = {qx[j], qy[j], qz[j]}, b1[3] = {vx[j], vy[j], vz[j]};
-    const double rcj = rc[j];
-    for (int ii = 0; ii < nb; ++ii) {
-        const double4 Mi = smr[ii];
-        const double dx = Mj.x - Mi.x, dy = Mj.y - Mi.y, dz = Mj.z - Mi.z;
-        const double D2 = fma(dz, dz, fma(dy, dy, dx * dx));
-        const double S = Mi.w + Mj.w;
-        bool cand = ii < ni && D2 <= S * S;
-        if (!__any(cand))
-            continue;
-        {
-            // relative chord filter
-            const double4 Ci = scr[ii];
-            const double cx = Cj.x - Ci.x, cy = Cj.y - Ci.y, cz = Cj.z - Ci.z;
-            const double C2 = fma(cz, cz, fma(cy, cy, cx * cx));
-            const double bb = Ci.w + Cj.w + fmax(si[ii].rc, rcj);
-            cand = cand && D2 <= fma(2.0, C2, 2.0 * bb * bb) * (1.0 + 0x1p-20);
+    int qn = 0;
+    auto drain = [&](int n) {
+        wave_lds_sync();
+        if (lane < n) {
+            const int e = qe[lane];
+            const HRec I = enc_load(in, wk.i0 + (e & 255));
+            enc_exact(I, enc_load(in, wk.j0 + (e >> 8)), dt, keys, cap, ce, stats);
         }
-        if (!__any(cand))
+    };
+    auto rows = [&](int s) {
+        return eq[2 * (size_t)(wk.j0 + min(s + r, wk.nj - 1)) + (q >> 1)];
+    };
+    // rows loaded two groups ahead
+    v8h row = rows(0), next = rows(16);
+    for (int s = 0; s < wk.nj; s += 16) {
+        const v8h after = rows(s + 32);
+        v4f f[NG];
+#pragma unroll
+        for (int k = 0; k < NG; ++k)
+            f[k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(row, col[k], al[k], 0, 0, 0);
+        row = next;
+        next = after;
+        int any = 0;
+#pragma unroll
+        for (int k = 0; k < NG; ++k)
+            any |= __float_as_int(f[k][0]) | __float_as_int(f[k][1]) | __float_as_int(f[k][2]) |
+                   __float_as_int(f[k][3]);
+        if (!__builtin_amdgcn_ballot_w64(any < 0))
             continue;
-        bool hit = false;
-        if (cand) {
-            const EncRec &I = si[ii];
-            const double d0x = a0[0] - I.q0[0], d0y = a0[1] - I.q0[1], d0z = a0[2] - I.q0[2];
-            const double d1x = a1[0] - I.q1[0], d1y = a1[1] - I.q1[1], d1z = a1[2] - I.q1[2];
-            const double e0x = b0[0] - I.v0[0], e0y = b0[1] - I.v0[1], e0z = b0[2] - I.v0[2];
-            const double e1x = b1[0] - I.v1[0], e1y = b1[1] - I.v1[1], e1z = b1[2] - I.v1[2];
-            const double f0 = fma(d0z, d0z, fma(d0y, d0y, d0x * d0x));
-            const double f1 = fma(d1z, d1z, fma(d1y, d1y, d1x * d1x));
-            const double g0 = t2 * fma(d0z, e0z, fma(d0y, e0y, d0x * e0x));
-            const double g1 = t2 * fma(d1z, e1z, fma(d1y, e1y, d1x * e1x));
-            const double lower = fmin(f0, f1) - k427 * (fmax(0.0, -g0) + fmax(0.0, g1));
-            const double rcij = fmax(I.rc, rcj);
-            const double thr = rcij * rcij;
-            if (lower <= thr * (1.0 + 1e-6) + 1e-15 * (f0 + f1 + fabs(g0) + fabs(g1)))
-                hit = hermite_min(f0, f1, g0, g1) <= thr;
-        }
-        const unsigned long long mask = __ballot(hit);
-        if (mask) {
-            const int leader = __ffsll((long long)mask) - 1;
-            int base = 0;
-            if (lane == leader)
-                base = atomicAdd(&stats->cur_nce, (int)__popcll(mask));
-            base = __shfl(base, leader);
-            if (hit) {
-                const int i = a + ii;
-                const int pos = base + (int)__popcll(mask & ((1ull << lane) - 1ull));
-                if (pos < cap)
-                    keys[pos] = ((unsigned long long)(unsigned)i << 32) | (unsigned)j;
-                __hip_atomic_store(&ce[i], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&ce[j], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // the signs as one mask per lane: bit 31 - (4k + v) for row 4q + v of group k
+        unsigned m = 0u;
+#pragma unroll
+        for (int k = 0; k < NG; ++k)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                m = (m << 1) | ((unsigned)__float_as_int(f[k][v]) >> 31);
+        while (__builtin_amdgcn_ballot_w64(m != 0u)) {
+            const int b = m ? __clz(m) : 0;
+            // source j0 + sj, target i0 + ti
+            const int sj = s + 4 * q + (b & 3), ti = 16 * (b >> 2) + r;
+            const bool cand = m != 0u && sj < wk.nj && wk.j0 + sj > wk.i0 + ti;
+            m &= ~(0x80000000u >> b);
+            const unsigned long long mk = __builtin_amdgcn_ballot_w64(cand);
+            if (!mk)
+                continue;
+            if (cand)
+                qe[qn + __popcll(mk & ((1ull << lane) - 1ull))] = ti | (sj << 8);
+            qn += __popcll(mk);
+            if (qn >= 64) {
+                drain(64);
+                const int rest = qn - 64;
+                const int e = lane < rest ? qe[64 + lane] : 0;
+                wave_lds_sync();
+                if (lane < rest)
+                    qe[lane] = e;
+                qn = rest;
             }
         }
     }
+    if (qn > 0)
+        drain(qn);
+}
+
+// Before the direct check: no encounter flag, an empty list.
+__global__ void k_enc_clear(int ntot, int *__restrict__ ce, DevStats *stats)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < ntot)
+        ce[i] = 0;
+    if (i == 0)
+        stats->cur_nce = 0;
 }
 
 // ----------------------------------------------------------------------------
@@ -2996,44 +3014,6 @@ __global__ __launch_bounds__(64 * kTpWaves) void k_tile_pairs(const Tile *__rest
         if (p < tp_cap)
             tpairs[p] = make_int2(A, B);
     }
-}
-
-// The exact test's fields of one sorted record.
-struct HRec {
-    double q0[3], v0[3], q1[3], v1[3];
-    double rc;
-    int body;
-};
-
-// Exact encounter test of a pair (the Hermite bound, then the minimum over the
-// step) and the append of a flagged pair.
-__device__ __forceinline__ void enc_exact(const HRec &I, const SRec &J, double dt,
-                                          unsigned long long *keys, int cap, int *ce,
-                                          DevStats *stats)
-{
-    const double t2 = 2.0 * dt, k427 = 4.0 / 27.0;
-    const double d0x = J.q0[0] - I.q0[0], d0y = J.q0[1] - I.q0[1], d0z = J.q0[2] - I.q0[2];
-    const double d1x = J.q1[0] - I.q1[0], d1y = J.q1[1] - I.q1[1], d1z = J.q1[2] - I.q1[2];
-    const double e0x = J.v0[0] - I.v0[0], e0y = J.v0[1] - I.v0[1], e0z = J.v0[2] - I.v0[2];
-    const double e1x = J.v1[0] - I.v1[0], e1y = J.v1[1] - I.v1[1], e1z = J.v1[2] - I.v1[2];
-    const double f0 = fma(d0z, d0z, fma(d0y, d0y, d0x * d0x));
-    const double f1 = fma(d1z, d1z, fma(d1y, d1y, d1x * d1x));
-    const double g0 = t2 * fma(d0z, e0z, fma(d0y, e0y, d0x * e0x));
-    const double g1 = t2 * fma(d1z, e1z, fma(d1y, e1y, d1x * e1x));
-    const double lower = fmin(f0, f1) - k427 * (fmax(0.0, -g0) + fmax(0.0, g1));
-    const double rcij = fmax(I.rc, J.rc);
-    const double thr = rcij * rcij;
-    if (!(lower <= thr * (1.0 + 1e-6) + 1e-15 * (f0 + f1 + fabs(g0) + fabs(g1))))
-        return;
-    if (!(hermite_min(f0, f1, g0, g1) <= thr))
-        return;
-    const int pos = atomicAdd(&stats->cur_nce, 1);
-    const int bi = I.body, bj = J.body;
-    const unsigned lo = (unsigned)min(bi, bj), hi = (unsigned)max(bi, bj);
-    if (pos < cap)
-        keys[pos] = ((unsigned long long)lo << 32) | hi;
-    __hip_atomic_store(&ce[bi], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&ce[bj], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The same for two sorted positions, every field of both records read at once.
@@ -4126,7 +4106,7 @@ hipError_t launch_validate(const Dev &d, const double *m0, const double *m, cons
 {
     int n = d.ntot > d.nsys ? d.ntot : d.nsys;
     k_validate<<<cdiv(n, kBlock), kBlock, 0, s>>>(d.ntot, d.nsys, m0, m, x, v, d.sys_of, d.off,
-                                                   d.nbig, d.flag);
+                                                   d.nbig, d.flag, d.scale2);
     return hipGetLastError();
 }
 
@@ -4139,7 +4119,7 @@ hipError_t launch_to_dh(const Dev &d, const double *x, const double *v, int fram
         k_partial_mv<<<d.nrb, kBlock, 0, s>>>(d.rblk, d.m, v, v + d.ntot, v + 2 * (size_t)d.ntot,
                                                d.rpart);
     k_to_dh<<<d.nrb, kBlock, 0, s>>>(d.rblk, d.rb_first, d.rb_count, d.m0, d.rpart, d.ntot, x, v,
-                                      helio, d.qx, d.qy, d.qz, d.vx, d.vy, d.vz);
+                                      helio, d.qx, d.qy, d.qz, d.vx, d.vy, d.vz, d.scale2);
     return hipGetLastError();
 }
 
@@ -4224,7 +4204,7 @@ hipError_t launch_drift(const Dev &d, const Params &p, double dt, double sun_h,
                                       d.stats, d.rpart_drift(), d.rc, d.mr, d.cr,
                                       d.enc_sorted ? d.lnr_part : nullptr, d.q1x, d.q1y, d.q1z,
                                       d.v1x, d.v1y, d.v1z, d.rc1, part_in, sun_h, d.rb_first,
-                                      d.rb_count, pre ? d.ptot : nullptr);
+                                      d.rb_count, pre ? d.ptot : nullptr, (v8h *)d.eq, d.scale2);
     return hipGetLastError();
 }
 
@@ -4405,16 +4385,11 @@ hipError_t launch_enc_test(const Dev &d, double dt, hipStream_t s)
             k_enc_pairs<<<grid, kBlock, 0, s>>>(d.tiles, d.tileb, d.tpairs, d.tp_cap, d.srec, d.em, d.eg, dt,
                                                  d.keys, d.enc_cap, d.ce, d.stats);
         }
-    } else if (d.enc_few) {
-        if (d.nrb > 0)
-            k_encounter_few<<<d.nrb, kBlock, 0, s>>>(d.rblk, d.off, d.nbig, dt, d.mr, d.cr, d.q0x,
-                                                      d.q0y, d.q0z, d.v0x, d.v0y, d.v0z, d.q1x,
-                                                      d.q1y, d.q1z, d.v1x, d.v1y, d.v1z, d.rc1,
-                                                      d.keys, d.enc_cap, d.ce, d.stats);
     } else if (d.new_ > 0) {
-        k_encounter<<<d.new_, kBlock, 0, s>>>(d.ework, dt, d.mr, d.cr, d.q0x, d.q0y, d.q0z, d.v0x,
-                                               d.v0y, d.v0z, d.q1x, d.q1y, d.q1z, d.v1x, d.v1y,
-                                               d.v1z, d.rc1, d.keys, d.enc_cap, d.ce, d.stats);
+        const EncIn in{d.q0x, d.q0y, d.q0z, d.v0x, d.v0y, d.v0z, d.q1x, d.q1y, d.q1z, d.v1x, d.v1y, d.v1z,
+                       d.rc1};
+        k_enc_direct<<<d.new_, 64, 0, s>>>(d.ework, (const v8h *)d.eq, in, dt, d.keys, d.enc_cap, d.ce,
+                                           d.stats);
     }
     k_enc_count<<<1, 64, 0, s>>>(d.enc_cap, d.stats);
     return hipGetLastError();
@@ -4467,9 +4442,8 @@ hipError_t launch_encounters(const Dev &d, double dt, hipStream_t s)
     // flags and its scan the count
     hipError_t e = hipSuccess;
     if (!(d.enc_sorted && d.nrb > 0)) {
-        e = launch_fill_i32(&d.stats->cur_nce, 1, 0, s);
-        if (e == hipSuccess)
-            e = launch_fill_i32(d.ce, d.ntot, 0, s);
+        k_enc_clear<<<cdiv(d.ntot, kBlock), kBlock, 0, s>>>(d.ntot, d.ce, d.stats);
+        e = hipGetLastError();
     }
     if (e == hipSuccess)
         e = launch_enc_gather(d, dt, s);

@@ -35,6 +35,8 @@ struct nb_ctx {
     // the drift outputs of set `snap` hold the last drift or per-phase step
     // (the persistent step launch does not write them)
     bool snap_valid = false;
+    // they were written by nb_drift, for the check with nothing beside it (Dev::alone)
+    bool snap_alone = false;
     double last_dt = 0.0;
     // captured runs of steps, one per length (1 .. kMaxGraphSteps) for one dt
     struct Graph {
@@ -114,6 +116,7 @@ Params to_internal(const nb_params &q)
     p.force_j = q.force_jchunk > 0 ? (q.force_jchunk + kBlock - 1) / kBlock * kBlock : kDefaultForceJ;
     p.enc_j = q.enc_jchunk > 0 ? q.enc_jchunk : kDefaultEncJ;
     p.enc_algo = q.enc_algo;
+    p.enc_auto = q.enc_algo == 0;
     p.step_algo = q.step_algo;
     p.force_algo = q.force_algo;
     p.force_g = q.force_g;
@@ -191,7 +194,10 @@ int apply_tuning(const nb_params &u, int nsys, const int32_t *off, const int32_t
         q.force_g = fg;
         q.force_r = fr;
         q.force_j = (fj + kBlock - 1) / kBlock * kBlock;
-        q.enc_algo = ea;
+        // (the table's check was measured beside the steps of a run; the full
+        // method runs nothing beside it and keeps the automatic choice)
+        q.enc_algo = q.resolve && ea == 2 ? 0 : ea;
+        q.enc_auto = q.enc_algo == 0;
         q.enc_j = ej;
         // the persistent launch cannot hand groups to the host resolver
         q.step_algo = q.resolve ? 0 : sa;
@@ -215,9 +221,33 @@ int choose_step_algo(const Params &p, int nsys, const int32_t *off)
     return p.step_algo == 2 && fits ? 2 : 1;
 }
 
-// Encounter algorithm: explicit choice, else sorted tiles when bodies have
-// many candidate partners on average (tested pairs per body >= 512); with few
-// big bodies or small systems every pair through the filters is cheaper.
+// Encounter algorithm: explicit choice, else the direct check up to
+// kEncDirectPairs pairs with a big member in the largest system, and the sorted
+// check above.  Beside the step on the second queue (whole steps, direct against
+// sorted): 1500 bodies 46 / 50 us, 8000 bodies 67 / 72 us, 12000 bodies 112 / 106
+// us, 16384 bodies 165 / 156 us: once the force pass fills the chip, the sorted
+// check's small kernels run in its gaps, while the direct check's matrix products
+// (all pairs) take their time from it.  The line lies at the pairs of 10000
+// bodies.  Where nothing runs beside it (the full method, and nb_drift with
+// nb_encounters, which take the direct check then also in a context whose steps
+// run the sorted one) it pays further: one check alone, direct against sorted,
+// 16384 bodies 17 / 50 us (0.5-5 AU disk) and 43 / 77 us (dense 0.9-1.1 AU ring),
+// 32768 bodies 41 / 72 and 142 / 147 us, 65536 bodies 142 / 125 and 488 / 311 us:
+// up to the pairs of 40960 bodies.
+constexpr long long kEncDirectPairs = 10000ll * 9999 / 2;
+constexpr long long kEncAlonePairs = 40960ll * 40959 / 2;
+
+// Pairs with a big member in the system that has most.
+long long max_pairs(int nsys, const int32_t *off, const int32_t *nbig)
+{
+    long long most = 0;
+    for (int s = 0; s < nsys; ++s) {
+        const long long n = off[s + 1] - off[s], nb = nbig ? nbig[s] : n;
+        most = std::max(most, nb * (n - 1) - nb * (nb - 1) / 2);
+    }
+    return most;
+}
+
 bool has_small(int nsys, const int32_t *off, const int32_t *nbig);
 
 int max_big(int nsys, const int32_t *off, const int32_t *nbig)
@@ -250,12 +280,7 @@ int choose_enc_algo(const Params &p, int nsys, const int32_t *off, const int32_t
     // the big bodies of its system
     if (has_small(nsys, off, nbig) && max_big(nsys, off, nbig) <= kBlock)
         return 3;
-    long long pairs = 0;
-    for (int s = 0; s < nsys; ++s) {
-        const long long n = off[s + 1] - off[s], nb = nbig ? nbig[s] : n;
-        pairs += nb * (n - 1) - nb * (nb - 1) / 2;
-    }
-    return pairs >= 512ll * std::max(off[nsys], 1) ? 2 : 1;
+    return max_pairs(nsys, off, nbig) > (p.resolve ? kEncAlonePairs : kEncDirectPairs) ? 2 : 1;
 }
 
 int check_params(const nb_params *p)
@@ -324,6 +349,7 @@ struct Tables {
     bool enc_sorted = false;
     bool enc_few = false;
     bool enc_fused = false;   // sorted check inside the symmetric force pass
+    bool enc_alone = false;   // sorted, with the direct check where nothing runs beside it
     std::vector<int> tile_first;
     bool force_few = false;
     bool force_sym = false;
@@ -349,6 +375,39 @@ void pair_items(int a, int n, int nb, int J, std::vector<PWork> &out)
                 out.push_back(PWork{a + i0, ni, a + j0, nj});
         }
     }
+}
+
+// Work items of the direct encounter check: targets in strips of kEncTargets big
+// bodies, sources from the strip's first body on in chunks of J (whole groups of
+// 16).  J starts at the parameter and is halved, down to 128, while there are
+// fewer than kEncMinItems items (one wave each; 1024 SIMDs).  The kernel with
+// chunks of 1024 against this rule's: 1001 bodies 21.5 / 5.5 us, 5003 bodies 24.5
+// / 6.8 us, 16384 bodies 17.9 / 14.4 us.
+constexpr long long kEncMinItems = 2048;
+
+int enc_chunk(const Params &p, int nsys, const int32_t *off, const int32_t *nbig)
+{
+    auto items = [&](int J) {
+        long long c = 0;
+        for (int s = 0; s < nsys; ++s) {
+            const int n = off[s + 1] - off[s], nb = nbig ? nbig[s] : n;
+            for (int i0 = 0; i0 < nb && c < kEncMinItems; i0 += kEncTargets)
+                c += (n - i0 + J - 1) / J;
+        }
+        return c;
+    };
+    int J = std::max(16, (std::min(p.enc_j, 1 << 20) + 15) / 16 * 16);
+    while (J > 128 && items(J) < kEncMinItems)
+        J = (J / 2 + 15) / 16 * 16;
+    return J;
+}
+
+void enc_items(int a, int n, int nb, int J, std::vector<PWork> &out)
+{
+    for (int i0 = 0; i0 < nb; i0 += kEncTargets)
+        for (int j0 = i0; j0 < n; j0 += J)
+            if (std::min(n, j0 + J) - 1 > i0)
+                out.push_back(PWork{a + i0, std::min(kEncTargets, nb - i0), a + j0, std::min(J, n - j0)});
 }
 
 // Split partials of the symmetric force: 3 values per body and super-tile of
@@ -413,6 +472,9 @@ void build_tables(const Params &p, int nsys, const int32_t *off, const int32_t *
                    sym_partial_bytes(p, nsys, off, t.sym_g * 64 * p.force_r) <= kSymPartialMax);
     // the fused pass is the symmetric force's: without it, the sorted check alone
     t.enc_fused = t.enc_fused && t.force_sym;
+    t.enc_alone = t.enc_sorted && !t.enc_fused && p.enc_auto &&
+                  max_pairs(nsys, off, nbig) <= kEncAlonePairs;
+    const bool direct = !t.enc_sorted || t.enc_alone;
     // 4: the symmetric FP32C force over the radial order (not with the fused
     // pass, which runs over the encounter check's order)
     t.force_rsort = p.force_algo == 4 && p.mode == NB_FP32C && t.force_sym && !t.enc_fused;
@@ -430,6 +492,7 @@ void build_tables(const Params &p, int nsys, const int32_t *off, const int32_t *
     t.dw_count.assign(nsys, 0);
     t.sys_of.assign(off[nsys], 0);
     const int TI = 64 * p.force_r;
+    const int ej = direct ? enc_chunk(p, nsys, off, nbig) : 0;
     for (int s = 0; s < nsys; ++s) {
         int a = off[s], n = off[s + 1] - off[s];
         for (int i = a; i < a + n; ++i)
@@ -471,7 +534,8 @@ void build_tables(const Params &p, int nsys, const int32_t *off, const int32_t *
                                             t.rb_first[s] + j0 / kBlock, 0});
                 }
         }
-        pair_items(a, n, nb, p.enc_j, t.ework);
+        if (direct)
+            enc_items(a, n, nb, ej, t.ework);
         t.dw_first[s] = (int)t.dwork.size();
         pair_items(a, n, nb, kDiagJ, t.dwork);
         t.dw_count[s] = (int)t.dwork.size() - t.dw_first[s];
@@ -586,6 +650,10 @@ size_t carve(const Params &p, int nsys, int ntot, int enc_cap, const Tables &t, 
     d.pk = (float4 *)take((size_t)ntot * 2 * sizeof(float4));
     d.mr = (double4 *)take((size_t)ntot * sizeof(double4));
     d.cr = (double4 *)take((size_t)ntot * sizeof(double4));
+    const size_t eq_bytes = t.enc_sorted ? 0 : (size_t)ntot * 2 * sizeof(float4);
+    d.eq = eq_bytes ? take(eq_bytes) : nullptr;
+    d.eq_alone = t.enc_alone ? take((size_t)ntot * 2 * sizeof(float4)) : nullptr;
+    d.scale2 = (double *)take((size_t)nsys * sizeof(double));
     // further sets of drift outputs: one per step of a captured run when the
     // check runs on a second queue and the sets stay within kSnapSetBytes, else two
     d.nsnap = snap_sets(p, t, ntot);
@@ -595,8 +663,9 @@ size_t carve(const Params &p, int nsys, int ntot, int enc_cap, const Tables &t, 
                           &a.q1y, &a.q1z, &a.v1x, &a.v1y, &a.v1z, &a.rc1};
         for (double **pl : alt)
             *pl = (double *)take(nd);
-        a.mr = (double4 *)take((size_t)ntot * sizeof(double4));
-        a.cr = (double4 *)take((size_t)ntot * sizeof(double4));
+        a.mr = t.enc_sorted ? (double4 *)take((size_t)ntot * sizeof(double4)) : nullptr;
+        a.cr = t.enc_sorted ? (double4 *)take((size_t)ntot * sizeof(double4)) : nullptr;
+        a.eq = eq_bytes ? take(eq_bytes) : nullptr;
     }
     d.kflag = (int *)take((size_t)ntot * sizeof(int));
     d.ce = (int *)take((size_t)ntot * sizeof(int));
@@ -618,7 +687,11 @@ size_t carve(const Params &p, int nsys, int ntot, int enc_cap, const Tables &t, 
         if (t.rb_count[s] > 0 && t.nsplit[s] != t.maxs)
             d.ns_all = 0;
     d.new_ = (int)t.ework.size();
-    d.ework = (PWork *)take(t.ework.size() * sizeof(PWork));
+    // room for the items of any smaller layout (the chunks shrink with the
+    // systems): a compaction fits the workspace
+    d.ework = (PWork *)take(std::max(t.ework.size(), t.enc_sorted && !t.enc_alone ? (size_t)0
+                                                                                  : (size_t)(4 * kEncMinItems)) *
+                            sizeof(PWork));
     d.ndw = (int)t.dwork.size();
     d.dwork = (PWork *)take(t.dwork.size() * sizeof(PWork));
     d.rpart = (double *)take((size_t)d.nrb * 12 * sizeof(double));
@@ -983,6 +1056,8 @@ int enqueue_steps(nb_ctx *c, double dt, int nsteps)
 {
     int r = NB_OK;
     int done = 0;
+    if (nsteps > 0)
+        c->snap_alone = false;
     if (c->p.step_algo != 2 && merged_kicks(c) && !c->mom_valid && nsteps > 0) {
         // the first S(h) takes P from the momentum before the kicks
         HIP_OK(c, launch_momentum(c->d, c->d.rpart_prev(), c->stream));
@@ -1207,6 +1282,12 @@ int radial_order(nb_ctx *c)
     if ((r = copy(c, c->d.rord, ord.data(), n * sizeof(int))))
         return r;
     return sync(c);
+}
+
+// The layout the check of the last drift reads.
+Dev check_dev(const nb_ctx *c)
+{
+    return (c->snap_alone ? c->d.alone() : c->d).with_snap(c->snap);
 }
 
 int enter(nb_ctx *c)
@@ -1461,8 +1542,9 @@ int nb_drift(nb_ctx *c, double dt, int *nfail)
     if (!std::isfinite(dt))
         return set_err(c, NB_E_INVALID, "nb_drift: dt not finite");
     HIP_OK(c, launch_fill_i32(&c->d.stats->cur_kfail, 1, 0, c->stream));
-    HIP_OK(c, launch_drift(c->d, c->p, dt, 0.0, c->d.rpart, c->stream));
+    HIP_OK(c, launch_drift(c->d.alone(), c->p, dt, 0.0, c->d.rpart, c->stream));
     c->snap = 0;
+    c->snap_alone = true;
     int nf = 0;
     if ((r = read_int(c, &c->d.stats->cur_kfail, &nf)))
         return r;
@@ -1486,9 +1568,8 @@ int nb_encounters(nb_ctx *c, int cap, int *nce, int32_t *ice, int32_t *jce, int3
         return set_err(c, NB_E_NOT_READY, "nb_encounters: no drift since the last upload");
     if (cap < 0 || (where != NB_HOST && where != NB_DEVICE))
         return set_err(c, NB_E_INVALID, "nb_encounters: bad argument");
-    HIP_OK(c, launch_fill_i32(c->d.ce, c->ntot, 0, c->stream));
-    HIP_OK(c, launch_fill_i32(&c->d.stats->cur_nce, 1, 0, c->stream));
-    HIP_OK(c, launch_encounters(c->d.with_snap(c->snap), c->last_dt, c->stream));
+    // (the check starts from an empty list and no flags)
+    HIP_OK(c, launch_encounters(check_dev(c), c->last_dt, c->stream));
     c->have_enc = true;
     return copy_list(c, cap, nce, ice, jce, ce, where);
 }
@@ -1658,13 +1739,12 @@ int nb_time_kernel(nb_ctx *c, int which, int reps, double dt, double *ms)
             HIP_OK(c, launch_force(c->d, c->p, c->stream));
             return NB_OK;
         case NB_K_ENCOUNTER:
-            // each check starts from an empty list, as after a drift
-            HIP_OK(c, launch_fill_i32(&c->d.stats->cur_nce, 1, 0, c->stream));
-            HIP_OK(c, launch_encounters(c->d.with_snap(c->snap), c->last_dt, c->stream));
+            HIP_OK(c, launch_encounters(check_dev(c), c->last_dt, c->stream));
             return NB_OK;
         case NB_K_DRIFT:
-            HIP_OK(c, launch_drift(c->d, c->p, dt, 0.0, c->d.rpart, c->stream));
+            HIP_OK(c, launch_drift(c->d.alone(), c->p, dt, 0.0, c->d.rpart, c->stream));
             c->snap = 0;
+            c->snap_alone = true;
             c->snap_valid = true;
             return NB_OK;
         case NB_K_FORCE_EVAL:
