@@ -106,11 +106,14 @@ typedef struct nb_params {
                              blocks in one tile loop; FP32C, every body big, resolve 0 and
                              the symmetric force, else 2; nb_encounters and nb_force run as
                              with 2) */
-    int32_t step_algo;    /* nb_step: 0 automatic (the tuning table's choice, else 1), 1 one
-                             launch per phase over all systems (HIP graph), 2 one persistent
-                             launch in which a workgroup owns a system for many steps (FP64
-                             pair arithmetic; systems of at most NB_PERSISTENT_MAX_N bodies; not
-                             with resolve; keeps no drift arcs for nb_encounters or nb_events) */
+    int32_t step_algo;    /* nb_step: 0 automatic (the tuning table's choice, else one persistent
+                             launch for systems of up to 256 bodies, which then leaves the
+                             drift arcs and the list of the last step as launches per phase
+                             do, else 1), 1 one launch per phase over all systems (HIP graph),
+                             2 one persistent launch in which a workgroup owns a system for
+                             many steps (FP64 pair arithmetic; systems of at most
+                             NB_PERSISTENT_MAX_N bodies; not with resolve; keeps no drift arcs
+                             for nb_encounters or nb_events) */
     int32_t resolve;      /* 0: flag close encounters only (hot-path mode); 1: the full
                              hybrid method, every flagged group resolved on the host by
                              Bulirsch-Stoer inside each nb_step (Sec. 2.1.1, Sec. 3.2) */

@@ -8,6 +8,7 @@
 namespace nb {
 
 constexpr int kBlock = 256;      // threads of every O(N) kernel and of the pair kernels
+constexpr int kSmallMax = 256;   // most bodies of a system stepped by k_steps_small
 constexpr int kEncTargets = 128; // targets per pair item of the direct encounter check
 constexpr int kDiagJ = 256;      // sources per pair item of the diagnostics
 constexpr int kScanChunkCells = 1024;   // cells per block of the counting sort's scan
@@ -246,7 +247,8 @@ struct Params {
     int enc_algo;         // 1: every pair with a big member, 2: sorted tiles, 3: as 1, for
                           // systems of at most kBlock big bodies
     int enc_auto;         // 1: the caller left enc_algo to the library
-    int step_algo;        // 1: per-phase launches, 2: persistent per-system launch
+    int step_algo;        // 1: per-phase launches, 2: persistent per-system launch, 3: the
+                          // persistent launch of small systems (an automatic choice)
     int force_algo;       // 0 automatic, 1 ordered pairs, 2 symmetric tile pairs, 4 symmetric
                           // over the radial order (FP32C; FP64: as 2)
     int force_g;          // symmetric force: tiles per super-tile (0 automatic, 1, 2, 4)
@@ -292,6 +294,9 @@ hipError_t launch_events(const Dev &d, const Params &p, double tau, double rho, 
 hipError_t launch_compact(const Dev &d, double *out, int *idx, hipStream_t s);
 hipError_t launch_persistent_steps(const Dev &d, const Params &p, double dt, int nsteps,
                                    hipStream_t s);
+// the same for systems of at most kSmallMax bodies with the direct check: state
+// on the chip, drift outputs of the last step in set 0 (mom: rpart_prev())
+hipError_t launch_small_steps(const Dev &d, const Params &p, double dt, int nsteps, hipStream_t s);
 hipError_t launch_step_stats(const Dev &d, int nsteps, hipStream_t s);
 hipError_t launch_enc_sort(const Dev &d, int accumulate, hipStream_t s);
 hipError_t launch_enc_gather(const Dev &d, double dt, hipStream_t s);

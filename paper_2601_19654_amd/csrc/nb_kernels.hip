@@ -2367,11 +2367,9 @@ struct HRec {
 };
 
 // Exact encounter test of a pair (the Hermite bound, then the minimum over the
-// step) and the append of a flagged pair.  J: an HRec or a sorted record.
+// step).  J: an HRec or a sorted record.
 template <typename R>
-__device__ __forceinline__ void enc_exact(const HRec &I, const R &J, double dt,
-                                          unsigned long long *keys, int cap, int *ce,
-                                          DevStats *stats)
+__device__ __forceinline__ bool enc_hit(const HRec &I, const R &J, double dt)
 {
     const double t2 = 2.0 * dt, k427 = 4.0 / 27.0;
     const double d0x = J.q0[0] - I.q0[0], d0y = J.q0[1] - I.q0[1], d0z = J.q0[2] - I.q0[2];
@@ -2386,8 +2384,17 @@ __device__ __forceinline__ void enc_exact(const HRec &I, const R &J, double dt,
     const double rcij = fmax(I.rc, J.rc);
     const double thr = rcij * rcij;
     if (!(lower <= thr * (1.0 + 1e-6) + 1e-15 * (f0 + f1 + fabs(g0) + fabs(g1))))
-        return;
-    if (!(hermite_min(f0, f1, g0, g1) <= thr))
+        return false;
+    return hermite_min(f0, f1, g0, g1) <= thr;
+}
+
+// The test and the append of a flagged pair.
+template <typename R>
+__device__ __forceinline__ void enc_exact(const HRec &I, const R &J, double dt,
+                                          unsigned long long *keys, int cap, int *ce,
+                                          DevStats *stats)
+{
+    if (!enc_hit(I, J, dt))
         return;
     const int pos = atomicAdd(&stats->cur_nce, 1);
     const int bi = I.body, bj = J.body;
@@ -2791,6 +2798,21 @@ __global__ __launch_bounds__(kBlock) void k_cell_order(const int *__restrict__ c
         }
 }
 
+// FP32 record of the pair filter: midpoint M and chord c, and the bound b' of
+// 3/4 eps (e34) widened by 2^-21 (|M|_1 + |c|_1) for the FP32 rounding of M, c and
+// their differences, and by 2^-18 relative for the rounding of the bound itself,
+// negated (sign bit set) for a small body; the chord's fourth word is rc rounded
+// up.  A pair's bound is |b'_i| + |b'_j| + max(rc_i, rc_j).
+__device__ __forceinline__ void enc_record32(double mx, double my, double mz, double cx, double cy,
+                                             double cz, double e34, double rc, bool big, float4 &M,
+                                             float4 &C)
+{
+    const float w = (float)((e34 + 0x1p-21 * (fabs(mx) + fabs(my) + fabs(mz) + fabs(cx) + fabs(cy) +
+                                              fabs(cz))) * (1.0 + 0x1p-18));
+    M = make_float4((float)mx, (float)my, (float)mz, big ? w : -w);
+    C = make_float4((float)cx, (float)cy, (float)cz, (float)(rc * (1.0 + 0x1p-20)));
+}
+
 // The sorted records from the drift outputs, body by body (coalesced reads),
 // each written to the body's sorted position.
 __global__ void k_srec(int ntot, const int *__restrict__ pos_of, const int *__restrict__ sys_of,
@@ -2825,17 +2847,8 @@ __global__ void k_srec(int ntot, const int *__restrict__ pos_of, const int *__re
     r.pad = 0.0;
     srec[pos] = r;
     if (em) {
-        // FP32 records of the pair filter: midpoint M and chord c, and the
-        // bound b' of 3/4 eps widened by 2^-21 (|M|_1 + |c|_1) for the FP32
-        // rounding of M, c and their differences, and by 2^-18 relative for the
-        // rounding of the bound itself, negated (sign bit set) for a small body;
-        // the chord's fourth word is rc rounded up.  A pair's bound is
-        // |b'_i| + |b'_j| + max(rc_i, rc_j).
-        const double w = (C.w + 0x1p-21 * (fabs(M.x) + fabs(M.y) + fabs(M.z) + fabs(C.x) +
-                                           fabs(C.y) + fabs(C.z))) * (1.0 + 0x1p-18);
-        const float rcu = (float)(rc[i] * (1.0 + 0x1p-20));
-        em[2 * (size_t)pos] = make_float4((float)M.x, (float)M.y, (float)M.z, r.big ? (float)w : -(float)w);
-        em[2 * (size_t)pos + 1] = make_float4((float)C.x, (float)C.y, (float)C.z, rcu);
+        enc_record32(M.x, M.y, M.z, C.x, C.y, C.z, C.w, rc[i], r.big != 0, em[2 * (size_t)pos],
+                     em[2 * (size_t)pos + 1]);
         // the endpoint deviations of the step (as the tile bounds take them):
         // their mean eb and half their difference's norm se, rounded up
         double s2 = 0.0, eb[3];
@@ -3648,6 +3661,308 @@ __global__ __launch_bounds__(NT) void k_steps_persistent(
         pkick<NT>(a, n, h, mm, P, drag, dp, m, qx, qy, qz, ax, ay, az, vx, vy, vz);
         __syncthreads();
     }
+}
+
+// Small systems (at most kSmallMax bodies): a workgroup owns a system for many
+// steps with every quantity on the chip: thread t keeps body t's state in
+// registers, the pair phases read LDS.  As launches, a step of 100 bodies is five
+// kernels of 3-7 us and the check's three beside them, each a single workgroup
+// waiting for memory; here a step is three barriers.
+//   body phase   kick, S(h), Kepler drift, the check's records to LDS, sum of m V
+//   barrier      second S(h), critical radii, positions to LDS
+//   barrier      pair phase: the NT threads are up to floor(NT / n) slices of the
+//                sources for every target: FP64 pair sums; each unordered pair
+//                once (j = i + k mod n, k <= n/2) through the FP32 filter of the
+//                check, survivors through the exact test
+//   barrier      each target's slice sums in slice order, closing kick
+// Arithmetic of the per-phase kernels (FP64 pairs also for FP32C contexts); the
+// last step leaves the drift outputs, flags and list the per-phase steps leave.
+// Bound by latency: the Kepler solve's serial chain, then barriers and LDS reads.
+// A step: 64 bodies 31 -> 5.9 us, 100 bodies 32 -> 8.8 us, 200 bodies 34 -> 20.7 us.
+constexpr int kSmallSlices = 8;       // most slices (their sums are added one by one)
+
+struct SmallArgs {
+    const PSys *psys;
+    int nsteps, drag, fp32c, unordered;   // unordered: near pairs counted once per pair
+    double dt, G, n_hill, inner;
+    DragP dp;
+    const double *m0, *m;
+    double *qx, *qy, *qz, *vx, *vy, *vz, *ax, *ay, *az, *rc;
+    double *q0x, *q0y, *q0z, *v0x, *v0y, *v0z, *q1x, *q1y, *q1z, *v1x, *v1y, *v1z, *rc1;
+    v8h *eq;
+    const double *scale2;
+    int *kflag, *ce;
+    unsigned long long *keys;
+    int cap;
+    DevStats *stats;
+    int *step_nce;
+    double *mom;                          // per-block sums of m V: the first S(h)'s, replaced by the last step's
+    const int *rb_first, *rb_count;
+};
+
+template <int NT, int NMAX>
+__global__ __launch_bounds__(NT) void k_steps_small(SmallArgs A)
+{
+    static_assert(NMAX <= NT && NMAX % 64 == 0, "a thread per body");
+    // sources: position and mass; rc and widened rc^2 (the zone test's superset)
+    __shared__ double4 sj[NMAX];
+    __shared__ double sr[NMAX], sw[NMAX];
+    __shared__ double part[3][NT];
+    __shared__ double red[3][NT / 64];
+    __shared__ float4 em[NMAX], ec[NMAX];
+    __shared__ double ex[13][NMAX];       // exact test: q0, v0, q1, v1, rc
+    const PSys S = A.psys[blockIdx.x];
+    const int a = S.start, n = S.n, nb = S.nbig, t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const bool on = t < n;
+    const int i = a + (on ? t : 0);
+    const double mm = A.m0[S.sys], mu = A.G * mm, dt = A.dt, h = 0.5 * dt;
+    // pair phase: target ti, slice sl of nsl
+    const int nsl = min(NT / n, kSmallSlices), sl = t / n, ti = t - sl * n;
+    const bool work = sl < nsl;
+    double x = A.qx[i], y = A.qy[i], z = A.qz[i], u = A.vx[i], v = A.vy[i], w = A.vz[i];
+    double ax = A.ax[i], ay = A.ay[i], az = A.az[i], rc = A.rc[i];
+    const double mi = on ? A.m[i] : 0.0;
+    const double hill = cbrt(mi / (3.0 * mm)), inv_l = enc_inv_scale(A.scale2[S.sys]);
+    const bool big = t < nb;
+    double P[3] = {0.0, 0.0, 0.0};
+    for (int b = 0; b < A.rb_count[S.sys]; ++b)
+        for (int k = 0; k < 3; ++k)
+            P[k] += A.mom[4 * (size_t)(A.rb_first[S.sys] + b) + k];
+    int near = 0, nf = 0;
+    // sum of m V (two barriers; every thread returns it)
+    auto momentum = [&](double (&out)[3]) {
+        double p[3] = {mi * u, mi * v, mi * w};
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            p[k] = wave_sum(p[k]);
+        if (lane == 0)
+            for (int k = 0; k < 3; ++k)
+                red[k][wv] = p[k];
+        __syncthreads();
+        for (int k = 0; k < 3; ++k) {
+            out[k] = red[k][0];
+            for (int q = 1; q < (n + 63) / 64; ++q)
+                out[k] += red[k][q];
+        }
+    };
+    auto kick = [&](const double (&Pk)[3]) {
+        double a0 = ax, a1 = ay, a2 = az;
+        if (A.drag) {
+            double d0, d1, d2;
+            drag_accel(A.dp, mm, mi, x, y, z, u + Pk[0] / mm, v + Pk[1] / mm, w + Pk[2] / mm, d0, d1, d2);
+            a0 += d0;
+            a1 += d1;
+            a2 += d2;
+        }
+        u = fma(h, a0, u);
+        v = fma(h, a1, v);
+        w = fma(h, a2, w);
+    };
+    for (int step = 0; step < A.nsteps; ++step) {
+        const bool last = step == A.nsteps - 1;
+        // with drag the kick needs the current momentum, and so does S(h) after it
+        if (A.drag) {
+            momentum(P);
+            __syncthreads();
+        }
+        if (on)
+            kick(P);
+        if (A.drag) {
+            momentum(P);
+            __syncthreads();
+        }
+        if (on) {
+            x += h * P[0] / mm;
+            y += h * P[1] / mm;
+            z += h * P[2] / mm;
+            const double x0 = x, y0 = y, z0 = z, u0 = u, v0 = v, w0 = w;
+            const bool fail = kepler_drift(mu, dt, x, y, z, u, v, w) != 0;
+            nf += fail;
+            const double cx = x - x0, cy = y - y0, cz = z - z0;
+            const double rho = 0.5 * sqrt(cx * cx + cy * cy + cz * cz);
+            const double ax0 = dt * u0 - cx, ay0 = dt * v0 - cy, az0 = dt * w0 - cz;
+            const double ax1 = dt * u - cx, ay1 = dt * v - cy, az1 = dt * w - cz;
+            const double eps = sqrt(fmax(ax0 * ax0 + ay0 * ay0 + az0 * az0, ax1 * ax1 + ay1 * ay1 + az1 * az1));
+            const double mx = x0 + 0.5 * cx, my = y0 + 0.5 * cy, mz = z0 + 0.5 * cz;
+            const double e34 = 0.75 * eps * (1.0 + 0x1p-20) +
+                               0x1p-45 * (sqrt(mx * mx + my * my + mz * mz) + 2.0 * rho);
+            float4 M, C;
+            enc_record32(mx, my, mz, cx, cy, cz, e34, rc, big, M, C);
+            em[t] = M;
+            ec[t] = C;
+            ex[0][t] = x0; ex[1][t] = y0; ex[2][t] = z0;
+            ex[3][t] = u0; ex[4][t] = v0; ex[5][t] = w0;
+            ex[6][t] = x;  ex[7][t] = y;  ex[8][t] = z;
+            ex[9][t] = u;  ex[10][t] = v; ex[11][t] = w;
+            ex[12][t] = rc;
+            if (last) {
+                A.q0x[i] = x0; A.q0y[i] = y0; A.q0z[i] = z0;
+                A.v0x[i] = u0; A.v0y[i] = v0; A.v0z[i] = w0;
+                A.q1x[i] = x;  A.q1y[i] = y;  A.q1z[i] = z;
+                A.v1x[i] = u;  A.v1y[i] = v;  A.v1z[i] = w;
+                A.rc1[i] = rc;
+                enc_record(mx, my, mz, cx, cy, cz, e34 + rc, inv_l, A.eq + 2 * (size_t)i);
+                A.kflag[i] = fail ? 1 : 0;
+                A.ce[i] = 0;
+            }
+        }
+        momentum(P);
+        if (on) {
+            x += h * P[0] / mm;
+            y += h * P[1] / mm;
+            z += h * P[2] / mm;
+            rc = A.n_hill * sqrt(x * x + y * y + z * z) * hill;
+            sj[t] = make_double4(x, y, z, mi);
+            sr[t] = rc;
+            // FP32C contexts count the pairs inside the radius their kernels widen
+            const double r2 = rc * rc;
+            sw[t] = A.fp32c ? fmax(r2 * (1.0 + 0x1p-9), 0x1p-80) : fmax(r2, DBL_MIN);
+        }
+        __syncthreads();
+        if (work) {
+            // C: pairs (ti, ti + k mod n), the slice's share of k = 1 .. n/2, kU of
+            // them at a time (their LDS reads and chains overlap)
+            constexpr int kU = 4;
+            const int half = n / 2, k1 = 1 + (sl + 1) * half / nsl;
+            const float4 Mi = em[ti], Ci = ec[ti];
+            const float wi = fabsf(Mi.w);
+            for (int k0 = 1 + sl * half / nsl; k0 < k1; k0 += kU) {
+                unsigned cand = 0u;
+#pragma unroll
+                for (int q = 0; q < kU; ++q) {
+                    int j = ti + min(k0 + q, k1 - 1);
+                    j = j >= n ? j - n : j;
+                    const float4 E = em[j], F = ec[j];
+                    const float dx = E.x - Mi.x, dy = E.y - Mi.y, dz = E.z - Mi.z;
+                    const float cx = F.x - Ci.x, cy = F.y - Ci.y, cz = F.z - Ci.z;
+                    const float D2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                    const float C2 = fmaf(cz, cz, fmaf(cy, cy, cx * cx));
+                    const float Sr = (fabsf(E.w) + wi) + max_nonneg(F.w, Ci.w);
+                    cand |= D2 <= fmaf(Sr, Sr, C2) * (2.0f * (1.0f + 0x1p-18f)) ? 1u << q : 0u;
+                }
+                while (cand) {
+                    const int k = k0 + __ffs(cand) - 1;
+                    cand &= cand - 1u;
+                    int j = ti + k;
+                    j = j >= n ? j - n : j;
+                    // not two small bodies; for even n the pairs half apart once
+                    if (k >= k1 || min(ti, j) >= nb || (2 * k == n && ti >= k))
+                        continue;
+                    HRec I, J;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        I.q0[c] = ex[c][ti];
+                        I.v0[c] = ex[3 + c][ti];
+                        I.q1[c] = ex[6 + c][ti];
+                        I.v1[c] = ex[9 + c][ti];
+                        J.q0[c] = ex[c][j];
+                        J.v0[c] = ex[3 + c][j];
+                        J.q1[c] = ex[6 + c][j];
+                        J.v1[c] = ex[9 + c][j];
+                    }
+                    I.rc = ex[12][ti];
+                    J.rc = ex[12][j];
+                    if (!enc_hit(I, J, dt))
+                        continue;
+                    atomicAdd(&A.step_nce[step], 1);
+                    if (last) {
+                        const int pos = atomicAdd(&A.stats->cur_nce, 1);
+                        const unsigned lo = (unsigned)(a + min(ti, j)), hi = (unsigned)(a + max(ti, j));
+                        if (pos < A.cap)
+                            A.keys[pos] = ((unsigned long long)lo << 32) | hi;
+                        __hip_atomic_store(&A.ce[lo], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        __hip_atomic_store(&A.ce[hi], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
+            }
+            // F: the slice's share of the big sources, kU at a time with one branch
+            // for the rare pairs in the changeover zone (the body itself is not one:
+            // a wave meets one of its own bodies in most groups; ordered pairs'
+            // counts include it)
+            if (!A.unordered && sl == 0 && ti < nb)
+                ++near;
+            const double xi = sj[ti].x, yi = sj[ti].y, zi = sj[ti].z, wgt = sw[ti];
+            double f0 = 0.0, f1 = 0.0, f2 = 0.0;
+            const int j1 = (sl + 1) * nb / nsl;
+            for (int j0 = sl * nb / nsl; j0 < j1; j0 += kU) {
+                double dx[kU], dy[kU], dz[kU], r2[kU], g[kU], mj[kU];
+                bool rare = false;
+#pragma unroll
+                for (int q = 0; q < kU; ++q) {
+                    const int j = min(j0 + q, j1 - 1);
+                    const double4 J = sj[j];
+                    dx[q] = J.x - xi;
+                    dy[q] = J.y - yi;
+                    dz[q] = J.z - zi;
+                    // without weight: the body itself, and past the slice's end
+                    mj[q] = j0 + q < j1 && j != ti ? J.w : 0.0;
+                    r2[q] = fma(dz[q], dz[q], fma(dy[q], dy[q], dx[q] * dx[q]));
+                    g[q] = rinv3(r2[q]);
+                    rare |= r2[q] < fmax(wgt, sw[j]) && j != ti;
+                }
+                if (rare) {
+                    for (int q = 0; q < kU && j0 + q < j1; ++q) {
+                        const int j = j0 + q;
+                        double rq = r2[0], gq;
+#pragma unroll
+                        for (int e = 1; e < kU; ++e)
+                            rq = q == e ? r2[e] : rq;
+                        if (!(rq < fmax(wgt, sw[j])) || j == ti)
+                            continue;
+                        gq = changeover_w(rq, fmax(sr[ti], sr[j]), A.inner);
+                        near += !A.unordered || ti < j;
+#pragma unroll
+                        for (int e = 0; e < kU; ++e)
+                            g[e] = q == e ? gq : g[e];
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < kU; ++q) {
+                    const double wq = r2[q] > 0.0 ? g[q] * mj[q] : 0.0;
+                    f0 = fma(wq, dx[q], f0);
+                    f1 = fma(wq, dy[q], f1);
+                    f2 = fma(wq, dz[q], f2);
+                }
+            }
+            part[0][t] = f0;
+            part[1][t] = f1;
+            part[2][t] = f2;
+        }
+        __syncthreads();
+        if (on) {
+            ax = part[0][t];
+            ay = part[1][t];
+            az = part[2][t];
+            for (int q = 1; q < nsl; ++q) {
+                ax += part[0][t + q * n];
+                ay += part[1][t + q * n];
+                az += part[2][t + q * n];
+            }
+            ax *= A.G;
+            ay *= A.G;
+            az *= A.G;
+            kick(P);
+        }
+    }
+    if (on) {
+        A.qx[i] = x; A.qy[i] = y; A.qz[i] = z;
+        A.vx[i] = u; A.vy[i] = v; A.vz[i] = w;
+        A.ax[i] = ax; A.ay[i] = ay; A.az[i] = az;
+        A.rc[i] = rc;
+    }
+    // the momentum the next step's first S(h) takes (drag: it sums its own)
+    if (t == 0)
+        for (int b = 0; b < A.rb_count[S.sys]; ++b)
+            for (int k = 0; k < 3; ++k)
+                A.mom[4 * (size_t)(A.rb_first[S.sys] + b) + k] = b ? 0.0 : P[k];
+    for (int o = 32; o > 0; o >>= 1) {
+        near += __shfl_xor(near, o);
+        nf += __shfl_xor(nf, o);
+    }
+    if (lane == 0 && near)
+        atomicAdd((unsigned long long *)&A.stats->near_pairs, (unsigned long long)near);
+    if (lane == 0 && nf)
+        atomicAdd((unsigned long long *)&A.stats->kepler_fail, (unsigned long long)nf);
 }
 
 // Per-step counts of one persistent launch into the run statistics (one workgroup).
@@ -4475,6 +4790,25 @@ hipError_t launch_persistent_steps(const Dev &d, const Params &p, double dt, int
     else
         k_steps_persistent<512><<<d.npsys, 512, 0, s>>>(NB_PERSIST_ARGS);
 #undef NB_PERSIST_ARGS
+    return hipGetLastError();
+}
+
+hipError_t launch_small_steps(const Dev &d, const Params &p, double dt, int nsteps, hipStream_t s)
+{
+    if (d.npsys == 0 || nsteps <= 0)
+        return hipSuccess;
+    const SmallArgs A{d.psys, nsteps, p.drag, p.mode == 1, d.force_sym, dt, p.G, p.n_hill, p.inner,
+                      drag_params(p), d.m0, d.m, d.qx, d.qy, d.qz, d.vx, d.vy, d.vz, d.ax, d.ay,
+                      d.az, d.rc, d.q0x, d.q0y, d.q0z, d.v0x, d.v0y, d.v0z, d.q1x, d.q1y, d.q1z,
+                      d.v1x, d.v1y, d.v1z, d.rc1, (v8h *)d.eq, d.scale2, d.kflag, d.ce, d.keys,
+                      d.enc_cap, d.stats, d.step_nce, d.rpart_prev(), d.rb_first, d.rb_count};
+    // 512 threads keep the whole state in registers; above 128 bodies the pair phase
+    // is longer than what the 1024 threads' spills cost (100 bodies 8.8 / 11.4 us a
+    // step, 200 bodies 25.8 / 20.7 us)
+    if (d.pmax_n <= 128)
+        k_steps_small<512, 128><<<d.npsys, 512, 0, s>>>(A);
+    else
+        k_steps_small<1024, kSmallMax><<<d.npsys, 1024, 0, s>>>(A);
     return hipGetLastError();
 }
 
