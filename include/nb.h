@@ -91,7 +91,8 @@ typedef struct nb_params {
     double  drag_cd;      /* drag coefficient */
     double  drag_rho_p;   /* bulk density of the bodies (mass / length^3) */
     int32_t force_jchunk; /* sources per force work item (0: tuned default) */
-    int32_t force_r;      /* targets per lane in the force kernel: 1, 2 or 4 (0: default) */
+    int32_t force_r;      /* targets per lane in the force kernel: 1, 2 or 4 (0: the tuning
+                             table's, else by the number of tile pairs) */
     int32_t enc_jchunk;   /* most sources per work item of the direct encounter check (0: 1024;
                              halved while the items are too few to fill the GPU) */
     int32_t enc_algo;     /* encounter check: 0 automatic (1 or 3 for systems of up to about

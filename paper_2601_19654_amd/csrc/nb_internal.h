@@ -21,6 +21,13 @@ constexpr int kSnapSets = 8;
 // needs (one workgroup of g waves per item).
 constexpr long long kSymMinItems(int g) { return g >= 2 ? 8192 : 0; }
 
+// Automatic targets per lane of the symmetric force: two (tiles of 128 bodies)
+// from kSymR1Items tile pairs of 128 on, else one: a pair of tiles of 128 is 23
+// us of one wave, of 64 10 us, and below this line the waves are too few to fill
+// the chip either way.  A step, one against two: 1500 bodies 31 / 46 us, 6000 bodies
+// 53 / 61 us (FP64) and 50 / 54 us (FP32C), 8000 bodies 67 / 63 and 60 / 56 us.
+constexpr long long kSymR1Items = 1536;
+
 // A block of an O(N) kernel: bodies [start, end) of one system (end - start <= kBlock).
 struct RBlk {
     int sys, start, end;
@@ -246,6 +253,7 @@ struct Params {
     int force_r, force_j, enc_j;
     int enc_algo;         // 1: every pair with a big member, 2: sorted tiles, 3: as 1, for
                           // systems of at most kBlock big bodies
+    int r_auto;           // 1: the caller left force_r to the library (resolved at creation)
     int enc_auto;         // 1: the caller left enc_algo to the library
     int step_algo;        // 1: per-phase launches, 2: persistent per-system launch, 3: the
                           // persistent launch of small systems (an automatic choice)

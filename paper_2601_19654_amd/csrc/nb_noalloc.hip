@@ -71,7 +71,9 @@ int nb_force_noalloc(const nb_params *p, int n, double m0, const double *m, cons
     q.n_hill = p->n_hill;
     q.inner = p->chg_inner;
     q.mode = p->mode;
-    q.force_r = p->force_r ? p->force_r : 2;
+    // targets per lane: asked for, or chosen as nb_create chooses them
+    const long long t128 = (n + 127) / 128;
+    q.force_r = p->force_r ? p->force_r : (t128 * (t128 + 1) / 2 < kSymR1Items ? 1 : 2);
     q.force_algo = 2;
     // super-tile width: asked for, or chosen as nb_create chooses it
     const int T = 64 * q.force_r;

@@ -112,6 +112,7 @@ Params to_internal(const nb_params &q)
     p.cd = q.drag_cd;
     p.rho_p = q.drag_rho_p;
     p.force_r = q.force_r > 0 ? q.force_r : kDefaultForceR;
+    p.r_auto = q.force_r == 0;
     // source chunks are whole tiles of kBlock bodies
     p.force_j = q.force_jchunk > 0 ? (q.force_jchunk + kBlock - 1) / kBlock * kBlock : kDefaultForceJ;
     p.enc_j = q.enc_jchunk > 0 ? q.enc_jchunk : kDefaultEncJ;
@@ -193,6 +194,7 @@ int apply_tuning(const nb_params &u, int nsys, const int32_t *off, const int32_t
         q.force_algo = fa;
         q.force_g = fg;
         q.force_r = fr;
+        q.r_auto = 0;
         q.force_j = (fj + kBlock - 1) / kBlock * kBlock;
         // (the table's check was measured beside the steps of a run; the full
         // method runs nothing beside it and keeps the automatic choice)
@@ -270,6 +272,31 @@ int max_big(int nsys, const int32_t *off, const int32_t *nbig)
 }
 
 int choose_enc_algo(const Params &p, int nsys, const int32_t *off, const int32_t *nbig);
+
+long long sym_items(int nsys, const int32_t *off, int TI);
+
+// Target tiles from which the few-source force kernels run.
+constexpr long long kFewTiles = 1024;
+
+// Automatic targets per lane: the symmetric force by its tile pairs (kSymR1Items);
+// the ordered one (some bodies small, or asked for) two from 512 tiles of 128
+// targets on, in FP32C only up to 1024, where the few-source kernels begin: 128 big
+// bodies and 30000 small ones 37 / 44 us a step with one / two targets (FP32C),
+// 100000 small ones 71 / 56 us (FP32C) and 56 / 52 us (FP64), 300000 small ones 119
+// / 127 us (FP32C), their force alone 48 / 41 us (FP64).
+void auto_force_r(Params &p, int nsys, const int32_t *off, const int32_t *nbig)
+{
+    if (!p.r_auto)
+        return;
+    if (p.force_algo != 1 && !has_small(nsys, off, nbig)) {
+        p.force_r = sym_items(nsys, off, 128) < kSymR1Items ? 1 : 2;
+        return;
+    }
+    long long tiles = 0;
+    for (int s = 0; s < nsys; ++s)
+        tiles += (off[s + 1] - off[s] + 127) / 128;
+    p.force_r = tiles < 512 || (p.mode == NB_FP32C && tiles >= kFewTiles) ? 1 : 2;
+}
 
 // The force pass with the encounter test in it holds four targets per lane only
 // by spilling registers: with enc_algo 4 it takes tiles of 128 (two per lane).
@@ -557,7 +584,7 @@ void build_tables(const Params &p, int nsys, const int32_t *off, const int32_t *
         int maxnb = 0;
         for (int s = 0; s < nsys; ++s)
             maxnb = std::max(maxnb, nbig ? nbig[s] : off[s + 1] - off[s]);
-        t.force_few = !t.force_sym && maxnb <= 256 && maxnb <= p.force_j && t.fwork.size() >= 1024;
+        t.force_few = !t.force_sym && maxnb <= 256 && maxnb <= p.force_j && (long long)t.fwork.size() >= kFewTiles;
     }
     // sorted encounter check: about N_s/8 cells per system (a power of two) and
     // tiles of 64 consecutive sorted bodies
@@ -1387,6 +1414,7 @@ int nb_workspace_size(const nb_params *p, int nsys, const int32_t *off, const in
         return NB_E_INVALID;
     if (q.enc_algo == 3 && max_big(nsys, off, nbig) > kBlock)
         q.enc_algo = 0;
+    auto_force_r(q, nsys, off, nbig);
     fused_tiles(q, nsys, off, nbig);
     Tables t;
     build_tables(q, nsys, off, nbig, t);
@@ -1417,6 +1445,7 @@ int nb_create(const nb_params *p, int nsys, const int32_t *off, const int32_t *n
         }
         if (c->p.enc_algo == 3 && max_big(nsys, off, nbig) > kBlock)
             c->p.enc_algo = 0;
+        auto_force_r(c->p, nsys, off, nbig);
         fused_tiles(c->p, nsys, off, nbig);
     }
     c->enc_cap = enc_cap;
