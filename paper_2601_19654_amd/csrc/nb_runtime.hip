@@ -1490,7 +1490,8 @@ int nb_upload(nb_ctx *c, const double *m0, const double *m, const double *x, con
         (where != NB_HOST && where != NB_DEVICE))
         return set_err(c, NB_E_INVALID, "nb_upload: bad argument");
     const size_t nd = (size_t)c->ntot * sizeof(double);
-    drop_graph(c);
+    // (the captured runs stay: they hold addresses in the workspace, which an
+    // upload refills, and constants of the context)
     const double *xs = x, *vs = v;
     if ((r = copy(c, c->d.m, m, nd)) || (r = copy(c, c->d.m0, m0, c->nsys * sizeof(double))))
         return r;
