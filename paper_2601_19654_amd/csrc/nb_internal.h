@@ -28,6 +28,16 @@ constexpr long long kSymMinItems(int g) { return g >= 2 ? 8192 : 0; }
 // 53 / 61 us (FP64) and 50 / 54 us (FP32C), 8000 bodies 67 / 63 and 60 / 56 us.
 constexpr long long kSymR1Items = 1536;
 
+// Most split slots for which the drift launch of a run also sums the force's
+// partials (Dev::fin_drift).
+constexpr int kFinDriftSlots = 64;
+// Threads per body that sum split partials, by the largest slot count: about eight
+// slots each, at most `most` (4 or 16) threads.
+constexpr int fin_slices(int maxs, int most)
+{
+    return maxs <= 8 ? 1 : maxs <= 16 ? 2 : maxs <= 32 || most == 4 ? 4 : maxs <= 64 ? 8 : 16;
+}
+
 // A block of an O(N) kernel: bodies [start, end) of one system (end - start <= kBlock).
 struct RBlk {
     int sys, start, end;
@@ -81,6 +91,10 @@ struct PSys {
     int sys, start, n, nbig;
 };
 
+// Flag of a body in an encounter; within a captured run the direct check of step k
+// writes kEncTag + k instead, and the run's end turns the last step's into flags.
+constexpr int kEncFlag = 2, kEncTag = 16;
+
 // Device statistics block (one per context).
 struct DevStats {
     long long total_nce;
@@ -92,6 +106,7 @@ struct DevStats {
     int cur_kfail;    // failures of the current drift
     int cur_tp;       // tile pairs surviving the cull (sorted encounter check)
     int pad;
+    int set_nce[kSnapSets];   // direct checks of a captured run: the count of each set's check
 };
 
 // What a drift leaves for the encounter check (snapshots, copies, chord
@@ -130,6 +145,7 @@ struct Dev {
     // tables
     RBlk *rblk;  int nrb;
     FWork *fwork; int nfw; int maxs;
+    int fin_drift;        // inside a run the drift launch sums the force's partials and kicks
     int ns_all;           // the split count of every system with bodies, if they all share it; else 0
     PWork *ework; int new_;
     PWork *dwork; int ndw;
@@ -155,6 +171,7 @@ struct Dev {
     DevStats *stats;
     // sorted encounter check
     int enc_sorted;
+    int *nce;             // direct check in a run: where this set's drift clears the count (else null)
     int enc_few;          // the direct check chosen for few big bodies (reported as such)
     double *lnr_part;     // nrb x 2: min, max of ln R (cylindrical) of chord midpoints
     int *cell_of, *slot_of;   // ntot
@@ -280,8 +297,10 @@ hipError_t launch_sun_drift(const Dev &d, double h, int rcrit, const Params &p, 
                             double *copy_to, hipStream_t s);
 // the drift D(dt), preceded by S(sun_h) from the sums after the kick (sun_h = 0: no
 // sun drift); writes the sums after the drift to rpart_drift()
+// fin: first the sum of the force's split partials and two kicks, as
+// launch_force_finalize does them
 hipError_t launch_drift(const Dev &d, const Params &p, double dt, double sun_h,
-                        const double *part_in, hipStream_t s);
+                        const double *part_in, hipStream_t s, bool fin = false);
 hipError_t launch_force(const Dev &d, const Params &p, hipStream_t s);
 // tables of a single system of d.ntot bodies (O(N) blocks, m0, super-tile pairs of
 // ST bodies, nt super-tiles) and a cleared statistics block, written on the device
@@ -306,6 +325,10 @@ hipError_t launch_persistent_steps(const Dev &d, const Params &p, double dt, int
 // on the chip, drift outputs of the last step in set 0 (mom: rpart_prev())
 hipError_t launch_small_steps(const Dev &d, const Params &p, double dt, int nsteps, hipStream_t s);
 hipError_t launch_step_stats(const Dev &d, int nsteps, hipStream_t s);
+// the direct check of a captured run's step (set `set` of the drift outputs), and
+// what the run's checks leave together
+hipError_t launch_enc_in_run(const Dev &d, double dt, int set, hipStream_t s);
+hipError_t launch_enc_run_end(const Dev &d, int nsets, hipStream_t s);
 hipError_t launch_enc_sort(const Dev &d, int accumulate, hipStream_t s);
 hipError_t launch_enc_gather(const Dev &d, double dt, hipStream_t s);
 // fused mode, before the force: an empty list and no flags, the sorted order

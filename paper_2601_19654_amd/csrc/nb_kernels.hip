@@ -73,7 +73,8 @@ __device__ __forceinline__ double wave_max(double v)
 // Deterministic block-wide sum of W doubles per thread (kBlock threads, fixed
 // order): each wave's 64 values by an xor-shuffle butterfly (both lanes of a
 // pair add the same two values, so every lane ends with the same bits), then
-// the wave sums in wave order.  Every thread returns the block's sums.
+// the wave sums in wave order.  Every thread returns the block's sums.  (Threads
+// past kBlock, which help elsewhere in a launch, add nothing.)
 template <int W>
 __device__ __forceinline__ void block_sum(double (&v)[W], double *sh)
 {
@@ -83,7 +84,7 @@ __device__ __forceinline__ void block_sum(double (&v)[W], double *sh)
     for (int w = 0; w < W; ++w)
         for (int o = 32; o > 0; o >>= 1)
             v[w] += __shfl_xor(v[w], o);
-    if (lane == 0) {
+    if (lane == 0 && wv < NW) {
 #pragma unroll
         for (int w = 0; w < W; ++w)
             sh[w * NW + wv] = v[w];
@@ -107,7 +108,7 @@ __device__ __forceinline__ void system_sum(const double *__restrict__ part, int 
 #pragma unroll
     for (int w = 0; w < W; ++w)
         out[w] = 0.0;
-    for (int b = threadIdx.x; b < count; b += kBlock)
+    for (int b = threadIdx.x; b < count && threadIdx.x < kBlock; b += kBlock)
 #pragma unroll
         for (int w = 0; w < W; ++w)
             out[w] += part[(size_t)(first + b) * stride + w];
@@ -688,10 +689,49 @@ __device__ __forceinline__ void enc_record(double mx, double my, double mz, doub
     out[1] = lo;
 }
 
+// One slice of a body's split partials: slots [k0, k1) of position i in order,
+// eight loads of each component in flight.
+template <typename P>
+__device__ __forceinline__ void sum_slots(const P *__restrict__ fpart, int ntot, int maxs, int i,
+                                          int k0, int k1, double &s0, double &s1, double &s2)
+{
+    const P *px = fpart + i, *py = px + (size_t)maxs * ntot, *pz = py + (size_t)maxs * ntot;
+    int k = k0;
+    for (; k + 8 <= k1; k += 8) {
+        P ux[8], uy[8], uz[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            ux[u] = px[(size_t)(k + u) * ntot];
+            uy[u] = py[(size_t)(k + u) * ntot];
+            uz[u] = pz[(size_t)(k + u) * ntot];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            s0 += (double)ux[u];
+            s1 += (double)uy[u];
+            s2 += (double)uz[u];
+        }
+    }
+    for (; k < k1; ++k) {
+        s0 += (double)px[(size_t)k * ntot];
+        s1 += (double)py[(size_t)k * ntot];
+        s2 += (double)pz[(size_t)k * ntot];
+    }
+}
+
 // Snapshot, drift, failure flags and counters, the encounter check's records,
 // and the partial sums of m V after the drift (for the second stellar drift).
 // The check clears its own list and flags, since it may run beside the next drift.
-__global__ void k_drift(const RBlk *__restrict__ rblk, const double *__restrict__ m0, double G,
+// NSL > 0: before the drift the sum of the body's force partials (FP: their type) by
+// NSL threads per body and two kicks V += kick_h a, in the arithmetic and order of
+// k_force_finalize with as many slices; the workgroup has kBlock NSL threads, and
+// those past kBlock only sum.  It saves a launch (and the 96 bytes per body that
+// the finalize and the drift pass through memory) inside a run.
+// A step with the finalize apart / folded in: 300 bodies 29.8 / 27.5 us, 16 systems
+// of 500 bodies 35.7 / 30.7, 3001 bodies (47 slots) 37.1 / 37.5, 5000 bodies (79
+// slots) 47 / 50: hence kFinDriftSlots.
+template <typename FP, int NSL>
+__global__ __launch_bounds__(kBlock * (NSL ? NSL : 1)) void k_drift(const RBlk *__restrict__ rblk, const double *__restrict__ m0, double G,
                         double dt, const double *__restrict__ m, double *qx, double *qy,
                         double *qz, double *vx, double *vy, double *vz, double *__restrict__ q0x,
                         double *__restrict__ q0y, double *__restrict__ q0z,
@@ -706,18 +746,59 @@ __global__ void k_drift(const RBlk *__restrict__ rblk, const double *__restrict_
                         double *__restrict__ rc1, const double *__restrict__ part_in,
                         double sun_h, const int *__restrict__ rb_first,
                         const int *__restrict__ rb_count, const double *__restrict__ ptot,
-                        v8h *__restrict__ eq, const double *__restrict__ scale2)
+                        v8h *__restrict__ eq, const double *__restrict__ scale2,
+                        int *__restrict__ nce, const FP *__restrict__ fpart, int ntot, int maxs,
+                        const int *__restrict__ nsplit, double kick_h)
 {
+    constexpr int NS1 = NSL > 1 ? NSL - 1 : 1;
+    __shared__ double gs[NSL > 1 ? NS1 * 3 * kBlock : 1];
     // the encounter check's records: eq (direct check) or mr, cr and the ln R
-    // range (sorted check)
+    // range (sorted check).  nce: the count of the check that will read this set
+    // of drift outputs, from zero.
+    if (nce && blockIdx.x == 0 && threadIdx.x == 0)
+        *nce = 0;
     __shared__ double sh[3 * kBlock];
     double lnr_lo = INFINITY, lnr_hi = -INFINITY;
     RBlk b = rblk[blockIdx.x];
-    int i = b.start + threadIdx.x;
-    const bool on = i < b.end;
+    const int t = NSL > 1 ? threadIdx.x % kBlock : threadIdx.x;
+    int i = b.start + t;
+    const bool on = i < b.end && threadIdx.x < kBlock;
     // the body's state, loaded while the system's momentum is summed
     const double xs = on ? qx[i] : 0.0, ys = on ? qy[i] : 0.0, zs = on ? qz[i] : 0.0;
-    const double us = on ? vx[i] : 0.0, vs = on ? vy[i] : 0.0, ws = on ? vz[i] : 0.0;
+    double us = on ? vx[i] : 0.0, vs = on ? vy[i] : 0.0, ws = on ? vz[i] : 0.0;
+    if constexpr (NSL > 0) {
+        const int g = threadIdx.x / kBlock;
+        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+        if (i < b.end) {
+            const int ns = nsplit[b.sys];
+            sum_slots(fpart, ntot, maxs, i, g * ns / NSL, (g + 1) * ns / NSL, s0, s1, s2);
+        }
+        if constexpr (NSL > 1) {
+            if (g > 0) {
+                double *o = gs + (size_t)(g - 1) * 3 * kBlock;
+                o[t] = s0;
+                o[kBlock + t] = s1;
+                o[2 * kBlock + t] = s2;
+            }
+            __syncthreads();
+            if (g == 0)
+                for (int q = 0; q < NSL - 1; ++q) {
+                    const double *o = gs + (size_t)q * 3 * kBlock;
+                    s0 += o[t];
+                    s1 += o[kBlock + t];
+                    s2 += o[2 * kBlock + t];
+                }
+        }
+        s0 *= G;
+        s1 *= G;
+        s2 *= G;
+        us = fma(kick_h, s0, us);
+        vs = fma(kick_h, s1, vs);
+        ws = fma(kick_h, s2, ws);
+        us = fma(kick_h, s0, us);
+        vs = fma(kick_h, s1, vs);
+        ws = fma(kick_h, s2, ws);
+    }
     const double rci = on ? rc[i] : 0.0, mi = on ? m[i] : 0.0;
     double mu = G * m0[b.sys];
     bool fail = false;
@@ -807,7 +888,7 @@ __global__ void k_drift(const RBlk *__restrict__ rblk, const double *__restrict_
             lnr_lo = fmin(lnr_lo, __shfl_xor(lnr_lo, o));
             lnr_hi = fmax(lnr_hi, __shfl_xor(lnr_hi, o));
         }
-        if ((threadIdx.x & 63) == 0) {
+        if ((threadIdx.x & 63) == 0 && threadIdx.x < kBlock) {
             sh[threadIdx.x >> 6] = lnr_lo;
             sh[kBlock / 64 + (threadIdx.x >> 6)] = lnr_hi;
         }
@@ -2267,28 +2348,7 @@ __global__ __launch_bounds__(kFinThreads) void k_force_finalize(
         // ns_all != 0: every system has that split count
         const int ns = ns_all ? ns_all : nsplit[sys_of[i]];
         const int k0 = g * ns / nsl, k1 = (g + 1) * ns / nsl;
-        const P *px = fpart + i, *py = px + (size_t)maxs * ntot, *pz = py + (size_t)maxs * ntot;
-        int k = k0;
-        for (; k + 8 <= k1; k += 8) {
-            P ux[8], uy[8], uz[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                ux[u] = px[(size_t)(k + u) * ntot];
-                uy[u] = py[(size_t)(k + u) * ntot];
-                uz[u] = pz[(size_t)(k + u) * ntot];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                s0 += (double)ux[u];
-                s1 += (double)uy[u];
-                s2 += (double)uz[u];
-            }
-        }
-        for (; k < k1; ++k) {
-            s0 += (double)px[(size_t)k * ntot];
-            s1 += (double)py[(size_t)k * ntot];
-            s2 += (double)pz[(size_t)k * ntot];
-        }
+        sum_slots(fpart, ntot, maxs, i, k0, k1, s0, s1, s2);
     }
     if (g > 0) {
         double *o = gs + (size_t)(g - 1) * 3 * B;
@@ -2388,21 +2448,22 @@ __device__ __forceinline__ bool enc_hit(const HRec &I, const R &J, double dt)
     return hermite_min(f0, f1, g0, g1) <= thr;
 }
 
-// The test and the append of a flagged pair.
+// The test and the append of a flagged pair (nce: the list's count; tag: the flag
+// written to both bodies).
 template <typename R>
 __device__ __forceinline__ void enc_exact(const HRec &I, const R &J, double dt,
-                                          unsigned long long *keys, int cap, int *ce,
-                                          DevStats *stats)
+                                          unsigned long long *keys, int cap, int *ce, int *nce,
+                                          int tag = kEncFlag)
 {
     if (!enc_hit(I, J, dt))
         return;
-    const int pos = atomicAdd(&stats->cur_nce, 1);
+    const int pos = atomicAdd(nce, 1);
     const int bi = I.body, bj = J.body;
     const unsigned lo = (unsigned)min(bi, bj), hi = (unsigned)max(bi, bj);
     if (pos < cap)
         keys[pos] = ((unsigned long long)lo << 32) | hi;
-    __hip_atomic_store(&ce[bi], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&ce[bj], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&ce[bi], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&ce[bj], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The drift outputs the exact test reads, by body.
@@ -2448,7 +2509,8 @@ __device__ __forceinline__ HRec enc_load(const EncIn &E, int i)
 __global__ __launch_bounds__(64, 3) void k_enc_direct(const PWork *__restrict__ work,
                                                    const v8h *__restrict__ eq, EncIn in, double dt,
                                                    unsigned long long *__restrict__ keys, int cap,
-                                                   int *__restrict__ ce, DevStats *stats)
+                                                   int *__restrict__ ce, int *__restrict__ nce,
+                                                   int tag)
 {
     constexpr int NG = kEncTargets / 16;
     __shared__ int qe[128];
@@ -2478,7 +2540,7 @@ __global__ __launch_bounds__(64, 3) void k_enc_direct(const PWork *__restrict__ 
         if (lane < n) {
             const int e = qe[lane];
             const HRec I = enc_load(in, wk.i0 + (e & 255));
-            enc_exact(I, enc_load(in, wk.j0 + (e >> 8)), dt, keys, cap, ce, stats);
+            enc_exact(I, enc_load(in, wk.j0 + (e >> 8)), dt, keys, cap, ce, nce, tag);
         }
     };
     auto rows = [&](int s) {
@@ -2533,6 +2595,25 @@ __global__ __launch_bounds__(64, 3) void k_enc_direct(const PWork *__restrict__ 
     }
     if (qn > 0)
         drain(qn);
+}
+
+// After the direct checks of a captured run (nsets steps, the k-th with set k's
+// count and the flags kEncTag + k, each appending to the list from its start): the
+// run's statistics, and the last check's count and flags as one check leaves them.
+__global__ void k_enc_run_end(int ntot, int nsets, int cap, int *__restrict__ ce, DevStats *stats)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < ntot)
+        ce[i] = ce[i] == kEncTag + nsets - 1 ? kEncFlag : 0;
+    if (i == 0) {
+        for (int k = 0; k < nsets; ++k) {
+            const int count = stats->set_nce[k];
+            stats->total_nce += count;
+            stats->max_nce = max(stats->max_nce, count);
+            stats->overflow_steps += count > cap;
+        }
+        stats->cur_nce = stats->set_nce[nsets - 1];
+    }
 }
 
 // Before the direct check: no encounter flag, an empty list.
@@ -3044,7 +3125,7 @@ __device__ __noinline__ void enc_candidate(const SRec *__restrict__ srec, double
     }
     I.rc = R.rc;
     I.body = R.body;
-    enc_exact(I, srec[pj], dt, keys, cap, ce, stats);
+    enc_exact(I, srec[pj], dt, keys, cap, ce, &stats->cur_nce);
 }
 
 // One wave per kept tile pair (A, B), the waves striding over the count: lane
@@ -3135,7 +3216,7 @@ __global__ __launch_bounds__(kBlock) void k_enc_pairs(const Tile *__restrict__ t
             }
             I.rc = ha[wv][12][li];
             I.body = hb[wv][li];
-            enc_exact(I, srec[TB.start + (e >> 8)], dt, keys, cap, ce, stats);
+            enc_exact(I, srec[TB.start + (e >> 8)], dt, keys, cap, ce, &stats->cur_nce);
         };
         auto stage = [&]() {
             if (!staged) {
@@ -4507,19 +4588,38 @@ hipError_t launch_sun_drift(const Dev &d, double h, int rcrit, const Params &p, 
 }
 
 hipError_t launch_drift(const Dev &d, const Params &p, double dt, double sun_h,
-                        const double *part_in, hipStream_t s)
+                        const double *part_in, hipStream_t s, bool fin)
 {
     if (d.nrb == 0)
         return hipSuccess;
     const bool pre = sun_h != 0.0 && d.sys_total;
     if (pre)
         k_sys_total<<<d.nsys, kBlock, 0, s>>>(d.rb_first, d.rb_count, part_in, d.ptot);
-    k_drift<<<d.nrb, kBlock, 0, s>>>(d.rblk, d.m0, p.G, dt, d.m, d.qx, d.qy, d.qz, d.vx, d.vy,
-                                      d.vz, d.q0x, d.q0y, d.q0z, d.v0x, d.v0y, d.v0z, d.kflag,
-                                      d.stats, d.rpart_drift(), d.rc, d.mr, d.cr,
-                                      d.enc_sorted ? d.lnr_part : nullptr, d.q1x, d.q1y, d.q1z,
-                                      d.v1x, d.v1y, d.v1z, d.rc1, part_in, sun_h, d.rb_first,
-                                      d.rb_count, pre ? d.ptot : nullptr, (v8h *)d.eq, d.scale2);
+    const int nsl = fin ? fin_slices(d.maxs, 4) : 0;
+#define NB_DRIFT(FP_, NSL_, PART_)                                                                \
+    k_drift<FP_, NSL_><<<d.nrb, kBlock * (NSL_ ? NSL_ : 1), 0, s>>>(                              \
+        d.rblk, d.m0, p.G, dt, d.m, d.qx, d.qy, d.qz, d.vx, d.vy, d.vz, d.q0x, d.q0y, d.q0z,      \
+        d.v0x, d.v0y, d.v0z, d.kflag, d.stats, d.rpart_drift(), d.rc, d.mr, d.cr,                 \
+        d.enc_sorted ? d.lnr_part : nullptr, d.q1x, d.q1y, d.q1z, d.v1x, d.v1y, d.v1z, d.rc1,     \
+        part_in, sun_h, d.rb_first, d.rb_count, pre ? d.ptot : nullptr, (v8h *)d.eq, d.scale2,    \
+        d.nce, PART_, d.ntot, d.maxs, d.nsplit, 0.5 * dt)
+#define NB_DRIFT_FIN(NSL_)                                                                        \
+    do {                                                                                          \
+        if (d.fpart32)                                                                            \
+            NB_DRIFT(float, NSL_, d.fpart32);                                                     \
+        else                                                                                      \
+            NB_DRIFT(double, NSL_, d.fpart);                                                      \
+    } while (0)
+    if (nsl == 0)
+        NB_DRIFT(double, 0, nullptr);
+    else if (nsl == 1)
+        NB_DRIFT_FIN(1);
+    else if (nsl == 2)
+        NB_DRIFT_FIN(2);
+    else
+        NB_DRIFT_FIN(4);
+#undef NB_DRIFT_FIN
+#undef NB_DRIFT
     return hipGetLastError();
 }
 
@@ -4638,10 +4738,11 @@ hipError_t launch_force_finalize(const Dev &d, const Params &p, double kick_h, i
 {
     if (d.ntot == 0)
         return hipSuccess;
-    // eight slots per slice at the largest split count
-    int nsl = 1;
-    while (nsl < 16 && nsl * 8 < d.maxs)
-        nsl *= 2;
+    // about eight slots per slice at the largest split count; up to kFinDriftSlots at
+    // most four slices, the order that the drift launch sums them in inside a run
+    // (not over the radial order, whose partials only this kernel sums)
+    const bool by4 = d.maxs <= kFinDriftSlots && !d.force_rsort && !ord;
+    const int nsl = fin_slices(d.maxs, by4 ? 4 : 16);
     const int grid = cdiv(d.ntot, kFinThreads / nsl), cc = enc_count ? d.enc_cap : -1;
     // the radial order's partials are by position too
     if (!ord && d.force_rsort)
@@ -4704,7 +4805,7 @@ hipError_t launch_enc_test(const Dev &d, double dt, hipStream_t s)
         const EncIn in{d.q0x, d.q0y, d.q0z, d.v0x, d.v0y, d.v0z, d.q1x, d.q1y, d.q1z, d.v1x, d.v1y, d.v1z,
                        d.rc1};
         k_enc_direct<<<d.new_, 64, 0, s>>>(d.ework, (const v8h *)d.eq, in, dt, d.keys, d.enc_cap, d.ce,
-                                           d.stats);
+                                           &d.stats->cur_nce, kEncFlag);
     }
     k_enc_count<<<1, 64, 0, s>>>(d.enc_cap, d.stats);
     return hipGetLastError();
@@ -4763,6 +4864,22 @@ hipError_t launch_encounters(const Dev &d, double dt, hipStream_t s)
     if (e == hipSuccess)
         e = launch_enc_gather(d, dt, s);
     return e != hipSuccess ? e : launch_enc_test(d, dt, s);
+}
+
+hipError_t launch_enc_in_run(const Dev &d, double dt, int set, hipStream_t s)
+{
+    if (d.new_ == 0)
+        return hipSuccess;
+    const EncIn in{d.q0x, d.q0y, d.q0z, d.v0x, d.v0y, d.v0z, d.q1x, d.q1y, d.q1z, d.v1x, d.v1y, d.v1z, d.rc1};
+    k_enc_direct<<<d.new_, 64, 0, s>>>(d.ework, (const v8h *)d.eq, in, dt, d.keys, d.enc_cap, d.ce,
+                                       &d.stats->set_nce[set], kEncTag + set);
+    return hipGetLastError();
+}
+
+hipError_t launch_enc_run_end(const Dev &d, int nsets, hipStream_t s)
+{
+    k_enc_run_end<<<cdiv(d.ntot, kBlock), kBlock, 0, s>>>(d.ntot, nsets, d.enc_cap, d.ce, d.stats);
+    return hipGetLastError();
 }
 
 hipError_t launch_enc_sort(const Dev &d, int accumulate, hipStream_t s)

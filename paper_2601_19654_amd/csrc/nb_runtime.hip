@@ -720,6 +720,7 @@ size_t carve(const Params &p, int nsys, int ntot, int enc_cap, const Tables &t, 
     d.nfw = (int)t.fwork.size();
     d.fwork = (FWork *)take(t.fwork.size() * sizeof(FWork));
     d.maxs = t.maxs;
+    d.fin_drift = !p.drag && !p.resolve && !t.force_rsort && !t.enc_fused && t.maxs <= kFinDriftSlots;
     d.ns_all = t.maxs;
     for (int s = 0; s < nsys; ++s)
         if (t.rb_count[s] > 0 && t.nsplit[s] != t.maxs)
@@ -885,8 +886,10 @@ int enqueue_step_head(nb_ctx *c, double dt, bool first)
     return NB_OK;
 }
 
-// S(h), critical radii, F, K(h) of a step (and the next step's K(h) unless `last`).
-int enqueue_step_tail(nb_ctx *c, double dt, bool last)
+// S(h), critical radii, F, K(h) of a step (and the next step's K(h) unless `last`);
+// to_drift: the sum of the force's partials and both kicks are left to the next
+// step's drift launch.
+int enqueue_step_tail(nb_ctx *c, double dt, bool last, bool to_drift = false)
 {
     const double h = 0.5 * dt;
     const Dev &d = c->d;
@@ -903,7 +906,7 @@ int enqueue_step_tail(nb_ctx *c, double dt, bool last)
     if (c->p.drag) {
         HIP_OK(c, launch_force_finalize(d, c->p, 0.0, 1, c->stream, ord, fz));
         HIP_OK(c, launch_kick(d, c->p, h, c->stream));
-    } else {
+    } else if (!to_drift) {
         HIP_OK(c, launch_force_finalize(d, c->p, h, last ? 1 : 2, c->stream, ord, fz));
     }
     return NB_OK;
@@ -921,6 +924,11 @@ int enqueue_run(nb_ctx *c, double dt, int steps)
 {
     const bool merge = merged_kicks(c);
     const double h = 0.5 * dt;
+    // direct checks, one launch each, when every step of the run has a set (and a
+    // count) of its own.  A graph with branches costs the host about 3.6 us a node
+    // (a chain 0.5 us): below some 5000 bodies that is the step, and clearing and
+    // counting around each check were two of its eight nodes.
+    const bool in_run = !c->d.enc_sorted && steps <= c->d.nsnap;
     for (int k = 0; k < steps; ++k) {
         const bool first = k == 0 || !merge, last = k == steps - 1 || !merge;
         int r;
@@ -930,17 +938,25 @@ int enqueue_run(nb_ctx *c, double dt, int steps)
             continue;
         }
         const int par = k % c->d.nsnap;
-        const Dev d = c->d.with_snap(par);
+        Dev d = c->d.with_snap(par);
+        if (in_run)
+            d.nce = &d.stats->set_nce[par];
         if (k >= c->d.nsnap)
             HIP_OK(c, hipStreamWaitEvent(c->stream, c->ev_join[par], 0));
         if (first)
             HIP_OK(c, launch_kick(d, c->p, h, c->stream));
-        HIP_OK(c, launch_drift(d, c->p, dt, h, merge ? d.rpart_prev() : d.rpart, c->stream));
+        HIP_OK(c, launch_drift(d, c->p, dt, h, merge ? d.rpart_prev() : d.rpart, c->stream,
+                               d.fin_drift && !first));
         HIP_OK(c, hipEventRecord(c->ev_fork[par], c->stream));
-        if ((r = enqueue_step_tail(c, dt, last)))
+        if ((r = enqueue_step_tail(c, dt, last, d.fin_drift && !last)))
             return r;
         HIP_OK(c, hipStreamWaitEvent(c->side, c->ev_fork[par], 0));
-        HIP_OK(c, launch_encounters(d, dt, c->side));
+        if (in_run)
+            HIP_OK(c, launch_enc_in_run(d, dt, par, c->side));
+        else
+            HIP_OK(c, launch_encounters(d, dt, c->side));
+        if (in_run && k == steps - 1)
+            HIP_OK(c, launch_enc_run_end(d, steps, c->side));
         HIP_OK(c, hipEventRecord(c->ev_join[par], c->side));
         c->snap = par;
     }
@@ -1279,6 +1295,10 @@ int setup_layout(nb_ctx *c, int nsys, const int32_t *off, const int32_t *nbig)
     c->p.step_algo = choose_step_algo(c->p, nsys, off, nbig);
     if (r == NB_OK && launch_fill_i32(c->d.step_nce, c->d.step_chunk, 0, c->stream) != hipSuccess)
         r = set_err(c, NB_E_HIP, "clearing the step counters failed");
+    // (no flag before the first run: a run's end takes what holds its last check's
+    // tag for one)
+    if (r == NB_OK && c->ntot > 0 && launch_fill_i32(c->d.ce, c->ntot, 0, c->stream) != hipSuccess)
+        r = set_err(c, NB_E_HIP, "clearing the encounter flags failed");
     if (r == NB_OK && c->ntot > 0 && launch_fill_i32(c->d.lost, c->ntot, 0, c->stream) != hipSuccess)
         r = set_err(c, NB_E_HIP, "clearing the lost flags failed");
     // the radial order's tiles; until the first upload sets the order, every
