@@ -10,6 +10,7 @@ namespace nb {
 constexpr int kBlock = 256;      // threads of every O(N) kernel and of the pair kernels
 constexpr int kSmallMax = 256;   // most bodies of a system stepped by k_steps_small
 constexpr int kEncTargets = 128; // targets per pair item of the direct encounter check
+constexpr int kEncRecBytes = 48; // direct check: record of a body
 constexpr int kDiagJ = 256;      // sources per pair item of the diagnostics
 constexpr int kScanChunkCells = 1024;   // cells per block of the counting sort's scan
 // Sets of drift outputs (what the encounter check of a step reads): one per
@@ -58,14 +59,12 @@ struct PWork {
     int i0, ni, j0, nj;
 };
 
-// A body's encounter record in spatially sorted order (sorted encounter check;
-// the exact test reads the first 112 bytes, the filters read FP32 records).
+// A body's encounter record in spatially sorted order (sorted encounter check:
+// the exact test; the filters read FP32 records).
 struct SRec {
     double q0[3], v0[3], q1[3], v1[3];
     double rc;
     int body, big;        // global index; 1 for a big body (a gravity source)
-    double M[3], c[3];    // chord midpoint and chord Q1 - Q0
-    double e34, pad;      // 3/4 of the largest endpoint deviation (widened for rounding)
 };
 
 // A tile of up to 64 consecutive sorted bodies of one system; `last` is the
@@ -75,7 +74,7 @@ struct Tile {
 };
 
 // Bounding data of a tile: centre and radius of the chord midpoints, of the
-// chords and of the endpoint velocity deviations (dt V - chord), and the
+// chords and of the endpoint velocity deviations (enc_deviation), and the
 // largest critical radius.
 struct TileB {
     double cm[3], sm;
@@ -115,7 +114,6 @@ struct DevStats {
 struct Snap {
     double *q0x, *q0y, *q0z, *v0x, *v0y, *v0z;
     double *q1x, *q1y, *q1z, *v1x, *v1y, *v1z, *rc1;
-    double4 *mr, *cr;
     void *eq;
     double *lnr_part;
 };
@@ -132,9 +130,8 @@ struct Dev {
     // check, so that it can run beside the next S(h), force and kick
     double *q1x, *q1y, *q1z, *v1x, *v1y, *v1z, *rc1;
     float4 *pk;           // FP32C source records: 2 per body {xhi,yhi,zhi,m},{xlo,ylo,zlo,rc2}
-    double4 *mr;          // per body after a drift: chord midpoint (x,y,z) and encounter reach R
-    double4 *cr;          // per body after a drift: chord Q1 - Q0 and 3/4 eps (widened)
-    void *eq;             // direct check, per body after a drift: two records of 8 halves (else null)
+    double4 *mr;          // persistent steps, per body: chord midpoint (x,y,z) and encounter reach R
+    void *eq;             // direct check, per body after a drift: three records of 8 halves (else null)
     void *eq_alone;       // sorted check in steps, direct check elsewhere: set 0's records (else null)
     double *scale2;       // nsys: largest |Q|^2 at the upload (the records' unit)
     int *kflag, *ce, *sys_of;
@@ -233,7 +230,7 @@ struct Dev {
 
     Snap snap() const
     {
-        return Snap{q0x, q0y, q0z, v0x, v0y, v0z, q1x, q1y, q1z, v1x, v1y, v1z, rc1, mr, cr, eq,
+        return Snap{q0x, q0y, q0z, v0x, v0y, v0z, q1x, q1y, q1z, v1x, v1y, v1z, rc1, eq,
                     lnr_part};
     }
     // for a drift and its check with nothing beside them (set 0 of the drift
@@ -257,7 +254,7 @@ struct Dev {
             e.v0x = a.v0x; e.v0y = a.v0y; e.v0z = a.v0z;
             e.q1x = a.q1x; e.q1y = a.q1y; e.q1z = a.q1z;
             e.v1x = a.v1x; e.v1y = a.v1y; e.v1z = a.v1z;
-            e.rc1 = a.rc1; e.mr = a.mr; e.cr = a.cr; e.eq = a.eq; e.lnr_part = a.lnr_part;
+            e.rc1 = a.rc1; e.eq = a.eq; e.lnr_part = a.lnr_part;
         }
         return e;
     }

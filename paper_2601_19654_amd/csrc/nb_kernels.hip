@@ -555,6 +555,14 @@ __device__ __forceinline__ void gfuncs(double beta, double s, double &G1, double
     G3 = s * s * s * c3;
 }
 
+// A value the compiler cannot relate to the one it had: the expressions before and
+// after are contracted to fused operations apart.  Around the solver it keeps the
+// forms of the drift launch equal to the last bit, whatever else they compute.
+__device__ __forceinline__ void opaque(double &a)
+{
+    __asm__("" : "+v"(a));
+}
+
 // Returns 0 on success; on failure the body is left unchanged.
 __device__ int kepler_drift(double mu, double dt, double &x, double &y, double &z, double &u,
                             double &v, double &w)
@@ -628,21 +636,73 @@ __device__ int kepler_drift(double mu, double dt, double &x, double &y, double &
     return 0;
 }
 
+// The endpoint velocity deviations e0 = dt V0 - c, e1 = dt V1 - c of a step's chord c
+// enter the Hermite interpolant as h10(s) e0 + h11(s) e1 with h10 = s (1-s)^2 >= 0 and
+// h11 = -s^2 (1-s) <= 0, that is as s(1-s) d + s(1-s)(1-2s) p of their half difference
+// d = (e0 - e1)/2 = dt (V0 - V1)/2 and their mean p.  s(1-s) <= 1/4 and s(1-s)|1-2s| <=
+// 1/(6 sqrt 3), so the relative deviation of a pair stays below E/4 with
+//   E = |d_j - d_i| + kEncP (|p_i| + |p_j|).
+// On an orbit d is the fall toward the star, about -dt^2/2 times the acceleration,
+// which neighbours share, and p is of third order in dt: E is small where the largest
+// |e| of either body is not.
+constexpr double kEncP = 0.385;
+
+__device__ __forceinline__ double norm3(double x, double y, double z)
+{
+    return sqrt(x * x + y * y + z * z);
+}
+
+__device__ __forceinline__ double norm1(double x, double y, double z)
+{
+    return fabs(x) + fabs(y) + fabs(z);
+}
+
+// A bound of sqrt(v) from above, within 2^-19 of it (the hardware estimate of
+// 1/sqrt is good to 2^-24).
+__device__ __forceinline__ double sqrt_up(double v)
+{
+    return v > 0.0 ? v * __builtin_amdgcn_rsq(v) * (1.0 + 0x1p-20) : v;
+}
+
+// A value to FP16 (over FP32: the split's low part takes what either rounding left).
+__device__ __forceinline__ _Float16 to_half(double v)
+{
+    return (_Float16)(float)v;
+}
+
+// d and a bound of kEncP |p| of a step.
+__device__ __forceinline__ double enc_deviation(double dt, const double (&v0)[3], const double (&v1)[3],
+                                                const double (&c)[3], double (&d)[3])
+{
+    double p2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        d[k] = 0.5 * dt * (v0[k] - v1[k]);
+        const double p = 0.5 * dt * (v0[k] + v1[k]) - c[k];
+        p2 += p * p;
+    }
+    return kEncP * sqrt_up(p2);
+}
+
 // The matrix-core filter of the direct encounter check (k_enc_direct): a pair can
-// only be flagged when D^2 <= 2 C^2 + 2 S^2 with D, C the distances of the two
-// chord midpoints M and chords c, and S = 3/4 (eps_i + eps_j) + rc_ij <= s_i + s_j,
-// s = 3/4 eps + rc (k_enc_direct).  Written out, D^2 - 2 C^2 - 2 (s_i + s_j)^2 =
-// al_i + al_j + sum_k g_k u_ik u_jk with u = (M, c, s), g = (-2 -2 -2 4 4 4 -4)
-// and al = |M|^2 - 2|c|^2 - 2 s^2: a product of two matrices.  Each u (in units of
-// the system's scale L, a power of two) is split into two FP16 values, 22 bits,
-// and al, reduced by the body's share of the error bound, likewise; the 32
-// products of a pair are exact in the matrix core's FP32 sum.
-// Bound of the error, with nn = |M|^2 + 2|c|^2 + 2 s^2 (the terms' magnitudes add up
-// to at most 2 (nn_i + nn_j)): splitting 2^-21 (nn_i + nn_j), summing 32 terms
-// (measured: 2^-21 of their magnitudes) 2^-20 (nn_i + nn_j), FP16 values below
-// 2^-14 in steps of 2^-24: 2^-22 (sqrt nn_i + sqrt nn_j) and 2^-31.  The shares
-// below are at least four times that.  A body outside 8 L (or not finite) gets a
-// record that makes a candidate of each of its pairs.
+// only be flagged when D <= C + 3/4 |d_j - d_i| + s_i + s_j with D, C the distances of
+// the two chord midpoints M and chords c, and s = 3/4 kEncP |p| + rc.  As (x + y + z)^2
+// <= 2 x^2 + 4 y^2 + 4 z^2, and with d' = sqrt(9/8) d, s' = sqrt 2 s, then
+//   D^2 - 2 C^2 - 2 |d'_j - d'_i|^2 - 2 (s'_i + s'_j)^2 = al_i + al_j + sum_k g_k u_ik u_jk
+// is not positive, with u = (M, c, d', s'), g = (-2 -2 -2 4 4 4 4 4 4 -4) and
+// al = |M|^2 - 2|c|^2 - 2|d'|^2 - 2 s'^2: a product of two matrices.  M and c (in units
+// of the system's scale L, a power of two) are split into two FP16 values, 22 bits,
+// of whose four products the one of the two low values is left out; d' is rounded to
+// one FP16 value, its rounding (2^-11 |d'| and 2^-25 a component, 1/sqrt 2 of it in
+// units of s; with the sum of |d'|'s components) added to s; s' is rounded up to one.  al, from the rounded d' and s' and
+// reduced by the body's share of the error bound, is split into two.  The 27 products
+// of a pair are exact in the matrix core's FP32 sum.
+// Bound of the error, with nn = |M|^2 + 2|c|^2 + 2|d'|^2 + 2 s'^2 (the terms' magnitudes
+// add up to at most 2 (nn_i + nn_j)): splitting 2^-21 (nn_i + nn_j), the products left
+// out 2^-22 (nn_i + nn_j), summing 32 terms (measured: 2^-21 of their magnitudes) 2^-20
+// (nn_i + nn_j), FP16 values below 2^-14 in steps of 2^-24: 2^-22 (sqrt nn_i + sqrt
+// nn_j) and 2^-31.  The shares below are at least four times that.  A body outside 8 L
+// (or not finite) gets a record that makes a candidate of each of its pairs.
 constexpr double kEncK1 = 0x1p-17, kEncK2 = 0x1p-20, kEncK3 = 0x1p-28;
 constexpr double kEncMax = 8.0;                 // largest component of u / L
 constexpr double kEncAlUnit = 64.0;             // al is stored times this ...
@@ -659,34 +719,51 @@ __device__ __forceinline__ double enc_inv_scale(double r2)
     return ldexp(1.0, -(ilogb(r2) / 2 + 1));
 }
 
-// The record of a body: (u_hi, al_hi), (u_lo, al_lo).
+// The record of a body: (M_hi, c_hi, s', al_hi), (M_lo, c_lo, al_lo, 0), (d', 1/unit,
+// 1/unit, al_hi, al_lo, 0).
+constexpr int kEncRec = 3;
 __device__ __forceinline__ void enc_record(double mx, double my, double mz, double cx, double cy,
-                                           double cz, double sb, double inv_l, v8h *out)
+                                           double cz, const double (&d)[3], double s, double inv_l,
+                                           v8h *out)
 {
-    const double u[7] = {mx * inv_l, my * inv_l, mz * inv_l, cx * inv_l, cy * inv_l, cz * inv_l, sb * inv_l};
-    const double M2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-    const double C2 = 2.0 * (u[3] * u[3] + u[4] * u[4] + u[5] * u[5] + u[6] * u[6]);
-    const double nn = M2 + C2;
-    const double al = (M2 - C2 - (kEncK1 * nn + kEncK2 * sqrt(nn) + kEncK3)) * kEncAlUnit;
-    v8h hi, lo;
+    const double u[6] = {mx * inv_l, my * inv_l, mz * inv_l, cx * inv_l, cy * inv_l, cz * inv_l};
+    v8h A, B, D;
     bool in = true;
 #pragma unroll
-    for (int k = 0; k < 7; ++k) {
+    for (int k = 0; k < 6; ++k) {
         in = in && fabs(u[k]) <= kEncMax;
-        hi[k] = (_Float16)u[k];
-        lo[k] = (_Float16)(u[k] - (double)hi[k]);
+        A[k] = to_half(u[k]);
+        B[k] = to_half(u[k] - (double)A[k]);
     }
-    hi[7] = (_Float16)al;
-    lo[7] = (_Float16)(al - (double)hi[7]);
-    if (!in) {
+    double dd = 0.0, d2 = 0.0;
 #pragma unroll
-        for (int k = 0; k < 7; ++k)
-            hi[k] = lo[k] = (_Float16)0.0f;
-        hi[7] = (_Float16)(float)kEncAlOut;
-        lo[7] = (_Float16)0.0f;
+    for (int k = 0; k < 8; ++k) {
+        const double w = k < 3 ? 0x1.0f876ccdf6cd9p+0 * inv_l * d[k < 3 ? k : 0] : 0.0;   // sqrt(9/8)
+        in = in && fabs(w) <= kEncMax;
+        D[k] = to_half(w);
+        dd += fabs(w);
+        d2 += (double)D[k] * (double)D[k];
     }
-    out[0] = hi;
-    out[1] = lo;
+    const double sp = 0x1.6a09e667f3bcdp+0 * (s * inv_l) + 0x1.002p-11 * dd + 0x1p-23;   // sqrt 2
+    in = in && sp <= 0.5 * kEncMax;
+    A[6] = to_half(sp * (1.0 + 0x1p-10));
+    const double M2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+    const double C2 = 2.0 * (u[3] * u[3] + u[4] * u[4] + u[5] * u[5] + d2 + (double)A[6] * (double)A[6]);
+    const double nn = M2 + C2;
+    const double al = (M2 - C2 - (kEncK1 * nn + kEncK2 * sqrt_up(nn) + kEncK3)) * kEncAlUnit;
+    A[7] = to_half(al);
+    B[6] = to_half(al - (double)A[7]);
+    B[7] = (_Float16)0.0f;
+    if (!in) {
+        A = B = D = v8h{};
+        A[7] = (_Float16)(float)kEncAlOut;
+    }
+    D[3] = D[4] = (_Float16)(float)(1.0 / kEncAlUnit);
+    D[5] = A[7];
+    D[6] = B[6];
+    out[0] = A;
+    out[1] = B;
+    out[2] = D;
 }
 
 // One slice of a body's split partials: slots [k0, k1) of position i in order,
@@ -738,8 +815,7 @@ __global__ __launch_bounds__(kBlock * (NSL ? NSL : 1)) void k_drift(const RBlk *
                         double *__restrict__ v0x, double *__restrict__ v0y,
                         double *__restrict__ v0z, int *__restrict__ kflag,
                         DevStats *stats, double *__restrict__ part_out,
-                        const double *__restrict__ rc, double4 *__restrict__ mr,
-                        double4 *__restrict__ cr, double *__restrict__ lnr_part,
+                        const double *__restrict__ rc, double *__restrict__ lnr_part,
                         double *__restrict__ q1x, double *__restrict__ q1y,
                         double *__restrict__ q1z, double *__restrict__ v1x,
                         double *__restrict__ v1y, double *__restrict__ v1z,
@@ -752,8 +828,8 @@ __global__ __launch_bounds__(kBlock * (NSL ? NSL : 1)) void k_drift(const RBlk *
 {
     constexpr int NS1 = NSL > 1 ? NSL - 1 : 1;
     __shared__ double gs[NSL > 1 ? NS1 * 3 * kBlock : 1];
-    // the encounter check's records: eq (direct check) or mr, cr and the ln R
-    // range (sorted check).  nce: the count of the check that will read this set
+    // for the encounter check: eq (records of the direct check) or the ln R range
+    // of the midpoints (sorted check).  nce: the count of the check that will read this set
     // of drift outputs, from zero.
     if (nce && blockIdx.x == 0 && threadIdx.x == 0)
         *nce = 0;
@@ -831,30 +907,25 @@ __global__ __launch_bounds__(kBlock * (NSL ? NSL : 1)) void k_drift(const RBlk *
         v0x[i] = u;
         v0y[i] = v;
         v0z[i] = w;
+        for (double *a : {&x, &y, &z, &u, &v, &w, &mu})
+            opaque(*a);
         fail = kepler_drift(mu, dt, x, y, z, u, v, w) != 0;
-        // Encounter data of this body over the step: chord c = Q1 - Q0 with
-        // half-length rho, midpoint M, endpoint velocity deviations e = dt V - c
-        // with largest norm eps (see k_enc_direct).
+        for (double *a : {&x, &y, &z, &u, &v, &w})
+            opaque(*a);
+        // Encounter data of this body over the step: chord c = Q1 - Q0 and midpoint M
         {
-            double cx = x - sx, cy = y - sy, cz = z - sz;
-            double rho = 0.5 * sqrt(cx * cx + cy * cy + cz * cz);
-            double ax0 = dt * us - cx, ay0 = dt * vs - cy, az0 = dt * ws - cz;
-            double ax1 = dt * u - cx, ay1 = dt * v - cy, az1 = dt * w - cz;
-            double eps = sqrt(fmax(ax0 * ax0 + ay0 * ay0 + az0 * az0, ax1 * ax1 + ay1 * ay1 + az1 * az1));
-            double mx = sx + 0.5 * cx, my = sy + 0.5 * cy, mz = sz + 0.5 * cz;
-            // relative pair filter data: the chord and 3/4 eps, widened by 2^-20
-            // and by 2^-45 (|M| + |c|) to cover the rounding of midpoint and chord
-            // differences
-            double e34 = 0.75 * eps * (1.0 + 0x1p-20) +
-                         0x1p-45 * (sqrt(mx * mx + my * my + mz * mz) + 2.0 * rho);
+            const double c[3] = {x - sx, y - sy, z - sz};
+            const double mx = sx + 0.5 * c[0], my = sy + 0.5 * c[1], mz = sz + 0.5 * c[2];
             if (eq) {
-                enc_record(mx, my, mz, cx, cy, cz, e34 + rci, enc_inv_scale(scale2[b.sys]),
-                           eq + 2 * (size_t)i);
+                const double e0[3] = {us, vs, ws}, e1[3] = {u, v, w};
+                double d[3];
+                const double p = enc_deviation(dt, e0, e1, c, d);
+                // 2^-45 (|M| + |c|): the rounding of midpoint, chord and deviations
+                const double s = 0.75 * p + rci + 0x1p-45 * (norm1(mx, my, mz) + norm1(c[0], c[1], c[2]));
+                enc_record(mx, my, mz, c[0], c[1], c[2], d, s, enc_inv_scale(scale2[b.sys]),
+                           eq + kEncRec * (size_t)i);
             } else {
-                double R = (2.0 * rho + 0.75 * eps + rci) * (1.0 + 0x1p-20);
-                mr[i] = make_double4(mx, my, mz, R);
-                cr[i] = make_double4(cx, cy, cz, e34);
-                double lnr = log(fmax(sqrt(mx * mx + my * my), 1e-300));
+                const double lnr = log(fmax(sqrt(mx * mx + my * my), 1e-300));
                 lnr_lo = lnr;
                 lnr_hi = lnr;
             }
@@ -2448,6 +2519,14 @@ __device__ __forceinline__ bool enc_hit(const HRec &I, const R &J, double dt)
     return hermite_min(f0, f1, g0, g1) <= thr;
 }
 
+// A body's flag.  Stored only where it is not there yet: the stores of many pairs to
+// one body's flag (embryos among many small bodies) take turns, about 10 ns each.
+__device__ __forceinline__ void enc_mark(int *ce, int body, int tag)
+{
+    if (__hip_atomic_load(&ce[body], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != tag)
+        __hip_atomic_store(&ce[body], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The test and the append of a flagged pair (nce: the list's count; tag: the flag
 // written to both bodies).
 template <typename R>
@@ -2462,8 +2541,8 @@ __device__ __forceinline__ void enc_exact(const HRec &I, const R &J, double dt,
     const unsigned lo = (unsigned)min(bi, bj), hi = (unsigned)max(bi, bj);
     if (pos < cap)
         keys[pos] = ((unsigned long long)lo << 32) | hi;
-    __hip_atomic_store(&ce[bi], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&ce[bj], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    enc_mark(ce, bi, tag);
+    enc_mark(ce, bj, tag);
 }
 
 // The drift outputs the exact test reads, by body.
@@ -2483,29 +2562,31 @@ __device__ __forceinline__ HRec enc_load(const EncIn &E, int i)
     return r;
 }
 
-// Direct check of every pair i < j with a big member (i big): the filter below as
+// Direct check of every pair i < j with a big member (i big): the filter of enc_record as
 // a product of matrices, then the exact test of the pairs it keeps.
 //
 // The Hermite data of a pair split into the straight relative chord, which the
 // cubic reproduces exactly and which stays at least D - |dc|/2 away (D = |dM| the
 // distance of the chord midpoints, dc = c_j - c_i), and the endpoint velocity
-// deviations e = dt V - c, weighted by h10(s) and h11(s) with |h10| + |h11| =
-// s(1-s) <= 1/4.  So f(s) >= (D - a)^2 - (1/2)(D + a)E with a = |dc|/2, E = eps_i +
-// eps_j, which exceeds rc_ij^2 whenever D > |dc| + 3E/4 + rc_ij; as (x + y)^2 <=
-// 2x^2 + 2y^2, pairs with D^2 > 2|dc|^2 + 2(3E/4 + rc_ij)^2 cannot be flagged.
-// Bodies moving together (neighbours on similar orbits) have short relative
-// chords, so this keeps few pairs also when steps are long.
+// deviations, at most E/4 (kEncP).  So f(s) >= (D - a)^2 - (1/2)(D + a)E with a =
+// |dc|/2, which exceeds rc_ij^2 whenever D > |dc| + 3E/4 + rc_ij: such pairs cannot be
+// flagged.  Bodies moving together (neighbours on similar orbits) have short relative
+// chords and share their fall toward the star, so this keeps few pairs also when
+// steps are long: 3.7e-5 of the pairs of 20011 bodies at 0.9-1.1 AU and steps of 0.04
+// yr, as many of a 1-3 AU disk and 0.05 yr (with the sum of both bodies' largest
+// deviations for E 1.1e-2 and 4.5e-4: the check alone 57 -> 23 us, and of 256 systems
+// of 200-4000 bodies 104 -> 66 us).
 //
 // A wave owns a work item of up to 128 targets (eight groups of 16, the columns of
 // its matrix products, held in registers) and its sources, 16 at a time (the
 // rows, one 16-byte load per lane): eight 16x16x32 products test 2048 pairs, and
-// the OR of their signs tells whether any is a candidate (enc_record).  The FP32
-// pair test this replaces issued 17 operations per 64 pairs, this one about one
-// and a half; candidates queue in LDS and take the exact test 64 at a time.
-// Bound by the matrix products (128 of about 200 cycles per 2048 pairs), in dense
-// rings with long steps by the exact tests.  Three waves per SIMD: at four the
-// columns spill.  The kernel: 100 bodies 22 -> 5.0 us, 16384 bodies in 0.5-5 AU
-// 14.4 us; the whole check at 1001 bodies 40 -> 8 us (nine launches before).
+// the OR of their signs tells whether any is a candidate.  The FP32 pair test this
+// replaces issued 17 operations per 64 pairs, this one about one and a half;
+// candidates queue in LDS and take the exact test 64 at a time.
+// Bound by the matrix products (128 of about 200 cycles per 2048 pairs); with few
+// items, by the latency of the row loads.  The kernel: 100 bodies 22 -> 5.0 us, 16384
+// bodies in 0.5-5 AU 14.4 us; the whole check at 1001 bodies 40 -> 10 us (nine launches
+// before).
 __global__ __launch_bounds__(64, 3) void k_enc_direct(const PWork *__restrict__ work,
                                                    const v8h *__restrict__ eq, EncIn in, double dt,
                                                    unsigned long long *__restrict__ keys, int cap,
@@ -2516,23 +2597,33 @@ __global__ __launch_bounds__(64, 3) void k_enc_direct(const PWork *__restrict__ 
     __shared__ int qe[128];
     const PWork wk = work[blockIdx.x];
     const int lane = threadIdx.x, q = lane >> 4, r = lane & 15;
-    // columns: K slots 8q .. 8q + 7 are (g u_hi, 1) for even q and (g u_lo, 0) for
-    // odd q, against (u_hi, al_hi) for q < 2 and (u_lo, al_lo) for q >= 2 of the rows
+    // K slots 8q .. 8q + 7, rows against columns (g as in enc_record): q = 0 the high
+    // parts, s' and the row's al_hi; q = 1 the rows' high and the columns' low parts; q = 2
+    // the rows' low parts and al_lo and the columns' high parts; q = 3 d' and the
+    // column's al
+    const _Float16 one = (_Float16)(float)(1.0 / kEncAlUnit), zero = (_Float16)0.0f;
+    const _Float16 g0 = (_Float16)(q == 3 ? 4.0f : -2.0f);
+    const v8h g = {g0, g0, g0, (_Float16)4.0f, (_Float16)4.0f, (_Float16)4.0f, (_Float16)-4.0f, zero};
+    const int cpart = q == 0 || q == 2 ? 0 : (q == 1 ? 1 : 2);
+    const int rpart = q < 2 ? 0 : q - 1;
     v8h col[NG];
-    v4f al[NG];
-    const _Float16 one = (q & 1) ? (_Float16)0.0f : (_Float16)(float)(1.0 / kEncAlUnit);
-    const v8h g = {(_Float16)-2.0f, (_Float16)-2.0f, (_Float16)-2.0f, (_Float16)4.0f,
-                   (_Float16)4.0f,  (_Float16)4.0f,  (_Float16)-4.0f, (_Float16)1.0f};
 #pragma unroll
     for (int k = 0; k < NG; ++k) {
         const bool ok = 16 * k + r < wk.ni;
-        const size_t i = 2 * (size_t)(wk.i0 + (ok ? 16 * k + r : 0));
-        const v8h hi = eq[i], lo = eq[i + 1];
-        col[k] = ((q & 1) ? lo : hi) * g;
-        col[k][7] = one;
-        // columns past the targets never go below zero
-        const float a = ok ? ((float)hi[7] + (float)lo[7]) * (float)(1.0 / kEncAlUnit) : 1e30f;
-        al[k] = v4f{a, a, a, a};
+        const v8h raw = eq[kEncRec * (size_t)(wk.i0 + (ok ? 16 * k + r : 0)) + cpart];
+        v8h c = raw * g;
+        c[6] = q == 0 ? c[6] : (q == 2 ? one : zero);
+        c[7] = q == 0 ? one : zero;
+        c[3] = q == 3 ? raw[5] : c[3];
+        c[4] = q == 3 ? raw[6] : c[4];
+        c[5] = q == 3 ? zero : c[5];
+        // columns past the targets: a large positive al and nothing else, so that
+        // they never go below zero
+        col[k] = c;
+        if (!ok) {
+            col[k] = v8h{};
+            col[k][3] = q == 3 ? (_Float16)60000.0f : zero;
+        }
     }
     int qn = 0;
     auto drain = [&](int n) {
@@ -2544,7 +2635,7 @@ __global__ __launch_bounds__(64, 3) void k_enc_direct(const PWork *__restrict__ 
         }
     };
     auto rows = [&](int s) {
-        return eq[2 * (size_t)(wk.j0 + min(s + r, wk.nj - 1)) + (q >> 1)];
+        return eq[kEncRec * (size_t)(wk.j0 + min(s + r, wk.nj - 1)) + rpart];
     };
     // rows loaded two groups ahead
     v8h row = rows(0), next = rows(16);
@@ -2553,7 +2644,7 @@ __global__ __launch_bounds__(64, 3) void k_enc_direct(const PWork *__restrict__ 
         v4f f[NG];
 #pragma unroll
         for (int k = 0; k < NG; ++k)
-            f[k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(row, col[k], al[k], 0, 0, 0);
+            f[k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(row, col[k], v4f{}, 0, 0, 0);
         row = next;
         next = after;
         int any = 0;
@@ -2569,7 +2660,7 @@ __global__ __launch_bounds__(64, 3) void k_enc_direct(const PWork *__restrict__ 
         for (int k = 0; k < NG; ++k)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                m = (m << 1) | ((unsigned)__float_as_int(f[k][v]) >> 31);
+                m = __builtin_amdgcn_alignbit(m, (unsigned)__float_as_int(f[k][v]), 31);
         while (__builtin_amdgcn_ballot_w64(m != 0u)) {
             const int b = m ? __clz(m) : 0;
             // source j0 + sj, target i0 + ti
@@ -2632,9 +2723,9 @@ __global__ void k_enc_clear(int ntot, int *__restrict__ ce, DevStats *stats)
 // grid of about N_s/8 cells traversed in Morton order, counting-sorted, and
 // cut into tiles of 64 consecutive bodies.  A tile carries the centre and
 // radius of its chord midpoints M, chords c and endpoint velocity deviations
-// e = dt V - c.  For i in tile A and j in tile B the Hermite data split into
-// the chord quadratic |dM + (s - 1/2) dc|^2 and the deviations weighted by
-// |h10| + |h11| = s(1-s) <= 1/4 give f(s) >= Lmin^2 - Qmax Em / 2 with
+// (d, with kEncP |p| added to its radius).  For i in tile A and j in tile B the
+// Hermite data split into the chord quadratic |dM + (s - 1/2) dc|^2 and the
+// relative deviation of at most E/4 (kEncP) give f(s) >= Lmin^2 - Qmax Em / 2 with
 //   Lmin = D - sm_A - sm_B - Cm/2,  Qmax = D + sm_A + sm_B + Cm/2,
 //   D = |cm_B - cm_A|, Cm = |cc_B - cc_A| + sc_A + sc_B, Em = |ce_B - ce_A| + se_A + se_B,
 // so a tile pair whose bound exceeds max rc^2 holds no flagged pair.  Surviving
@@ -2658,7 +2749,9 @@ __device__ __forceinline__ unsigned morton2(unsigned band, int nb, unsigned pb, 
 __global__ void k_cells(const RBlk *__restrict__ rblk, const int *__restrict__ rb_first,
                         const int *__restrict__ rb_count, const double *__restrict__ lnr_part,
                         const int *__restrict__ sys_cell_base, const int *__restrict__ sys_cell_cnt,
-                        const double4 *__restrict__ mr, int *__restrict__ cell_cnt,
+                        const double *__restrict__ q0x, const double *__restrict__ q0y,
+                        const double *__restrict__ q1x, const double *__restrict__ q1y,
+                        int *__restrict__ cell_cnt,
                         int *__restrict__ cell_of, int *__restrict__ slot_of, int *__restrict__ ce)
 {
     __shared__ double sh[2 * kBlock];
@@ -2692,13 +2785,15 @@ __global__ void k_cells(const RBlk *__restrict__ rblk, const int *__restrict__ r
     const int lp = lc - lb;
     const int i = b.start + threadIdx.x;
     if (i < b.end) {
-        double4 M = mr[i];
-        double R = sqrt(M.x * M.x + M.y * M.y);
+        // the chord midpoint, as in k_drift
+        const double x0 = q0x[i], y0 = q0y[i];
+        const double mx = x0 + 0.5 * (q1x[i] - x0), my = y0 + 0.5 * (q1y[i] - y0);
+        double R = sqrt(mx * mx + my * my);
         double lnr = log(fmax(R, 1e-300));
         unsigned band = 0, pb = 0;
         if (span > 0.0)
             band = (unsigned)min((1 << lb) - 1, max(0, (int)((lnr - lo) / span * (double)(1 << lb))));
-        double phi = atan2(M.y, M.x);
+        double phi = atan2(my, mx);
         pb = (unsigned)min((1 << lp) - 1, max(0, (int)((phi + 3.141592653589793) *
                                                       (0.15915494309189535 * (double)(1 << lp)))));
         int cell = sys_cell_base[b.sys] + (int)morton2(band, lb, pb, lp);
@@ -2894,6 +2989,18 @@ __device__ __forceinline__ void enc_record32(double mx, double my, double mz, do
     C = make_float4((float)cx, (float)cy, (float)cz, (float)(rc * (1.0 + 0x1p-20)));
 }
 
+// Chord midpoint M, chord c, deviation d and the bound p of the mean deviation
+// (enc_deviation) of one record.
+__device__ __forceinline__ void rec_geometry(const SRec &r, double dt, double (&M)[3],
+                                             double (&c)[3], double (&d)[3], double &p)
+{
+    for (int k = 0; k < 3; ++k) {
+        c[k] = r.q1[k] - r.q0[k];
+        M[k] = r.q0[k] + 0.5 * c[k];
+    }
+    p = enc_deviation(dt, r.v0, r.v1, c, d);
+}
+
 // The sorted records from the drift outputs, body by body (coalesced reads),
 // each written to the body's sorted position.
 __global__ void k_srec(int ntot, const int *__restrict__ pos_of, const int *__restrict__ sys_of,
@@ -2903,10 +3010,9 @@ __global__ void k_srec(int ntot, const int *__restrict__ pos_of, const int *__re
                        const double *__restrict__ qx, const double *__restrict__ qy,
                        const double *__restrict__ qz, const double *__restrict__ vx,
                        const double *__restrict__ vy, const double *__restrict__ vz,
-                       const double *__restrict__ rc, const double4 *__restrict__ mr,
-                       const double4 *__restrict__ cr, const int *__restrict__ off,
+                       const double *__restrict__ rc, const int *__restrict__ off,
                        const int *__restrict__ nbig, SRec *__restrict__ srec,
-                       float4 *__restrict__ em, float4 *__restrict__ eg, double dt)
+                       float4 *__restrict__ em, float4 *__restrict__ eg, double dt, int fused)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= ntot)
@@ -2921,41 +3027,18 @@ __global__ void k_srec(int ntot, const int *__restrict__ pos_of, const int *__re
     r.rc = rc[i];
     r.body = i;
     r.big = (i - off[sy]) < nbig[sy] ? 1 : 0;
-    const double4 M = mr[i], C = cr[i];
-    r.M[0] = M.x; r.M[1] = M.y; r.M[2] = M.z;
-    r.c[0] = C.x; r.c[1] = C.y; r.c[2] = C.z;
-    r.e34 = C.w;
-    r.pad = 0.0;
     srec[pos] = r;
-    if (em) {
-        enc_record32(M.x, M.y, M.z, C.x, C.y, C.z, C.w, rc[i], r.big != 0, em[2 * (size_t)pos],
-                     em[2 * (size_t)pos + 1]);
-        // the endpoint deviations of the step (as the tile bounds take them):
-        // their mean eb and half their difference's norm se, rounded up
-        double s2 = 0.0, eb[3];
-        for (int k = 0; k < 3; ++k) {
-            const double e0 = dt * r.v0[k] - (r.q1[k] - r.q0[k]), e1 = dt * r.v1[k] - (r.q1[k] - r.q0[k]);
-            eb[k] = 0.5 * (e0 + e1);
-            s2 += (e0 - e1) * (e0 - e1);
-        }
-        eg[pos] = make_float4((float)eb[0], (float)eb[1], (float)eb[2],
-                              (float)(0.5 * sqrt(s2) * (1.0 + 0x1p-20)));
-    }
-}
-
-// Chord midpoint M, chord c, mean deviation eb and deviation radius se of one record.
-__device__ __forceinline__ void rec_geometry(const SRec &r, double dt, double M[3], double c[3],
-                                             double eb[3], double &se)
-{
-    double s2 = 0.0;
-    for (int k = 0; k < 3; ++k) {
-        c[k] = r.q1[k] - r.q0[k];
-        M[k] = r.q0[k] + 0.5 * c[k];
-        double e0 = dt * r.v0[k] - c[k], e1 = dt * r.v1[k] - c[k];
-        eb[k] = 0.5 * (e0 + e1);
-        s2 += (e0 - e1) * (e0 - e1);
-    }
-    se = 0.5 * sqrt(s2);
+    double M[3], c[3], d[3], p;
+    rec_geometry(r, dt, M, c, d, p);
+    // the bound: 3/4 E's share of the body, with the deviation d apart (k_enc_pairs) or
+    // its norm in it (the force pass with the encounter test in it, which has no d),
+    // and 2^-45 (|M| + |c|) for the rounding of midpoint, chord and deviations
+    const double e34 = 0.75 * (p + (fused ? norm3(d[0], d[1], d[2]) : 0.0)) * (1.0 + 0x1p-20) +
+                       0x1p-21 * norm1(d[0], d[1], d[2]) +
+                       0x1p-45 * (norm1(M[0], M[1], M[2]) + norm1(c[0], c[1], c[2]));
+    enc_record32(M[0], M[1], M[2], c[0], c[1], c[2], e34, rc[i], r.big != 0, em[2 * (size_t)pos],
+                 em[2 * (size_t)pos + 1]);
+    eg[pos] = make_float4((float)d[0], (float)d[1], (float)d[2], (float)(p * (1.0 + 0x1p-20)));
 }
 
 __device__ __forceinline__ double wave_sum(double v)
@@ -2972,11 +3055,6 @@ __device__ __forceinline__ double wave_maxd(double v)
     return v;
 }
 
-__device__ __forceinline__ double norm3(double x, double y, double z)
-{
-    return sqrt(x * x + y * y + z * z);
-}
-
 // One wave per tile: centres (means) and radii (maxima) of its bodies' geometry.
 __global__ __launch_bounds__(kBlock) void k_tile_bounds(const Tile *__restrict__ tiles, int ntile,
                                                         const SRec *__restrict__ srec, double dt,
@@ -2988,11 +3066,11 @@ __global__ __launch_bounds__(kBlock) void k_tile_bounds(const Tile *__restrict__
         return;
     const Tile T = tiles[tw];
     const bool on = lane < T.count;
-    double M[3] = {0, 0, 0}, c[3] = {0, 0, 0}, eb[3] = {0, 0, 0}, se = 0.0, rc = 0.0;
+    double M[3] = {0, 0, 0}, c[3] = {0, 0, 0}, d[3] = {0, 0, 0}, p = 0.0, rc = 0.0;
     bool big = false;
     if (on) {
         const SRec r = srec[T.start + lane];
-        rec_geometry(r, dt, M, c, eb, se);
+        rec_geometry(r, dt, M, c, d, p);
         rc = r.rc;
         big = r.big != 0;
     }
@@ -3002,13 +3080,13 @@ __global__ __launch_bounds__(kBlock) void k_tile_bounds(const Tile *__restrict__
     for (int k = 0; k < 3; ++k) {
         cm[k] = wave_sum(M[k]) * inv;
         cc[k] = wave_sum(c[k]) * inv;
-        ce[k] = wave_sum(eb[k]) * inv;
+        ce[k] = wave_sum(d[k]) * inv;
     }
     double dm = 0.0, dc = 0.0, de = 0.0;
     if (on) {
         dm = norm3(M[0] - cm[0], M[1] - cm[1], M[2] - cm[2]);
         dc = norm3(c[0] - cc[0], c[1] - cc[1], c[2] - cc[2]);
-        de = norm3(eb[0] - ce[0], eb[1] - ce[1], eb[2] - ce[2]) + se;
+        de = norm3(d[0] - ce[0], d[1] - ce[1], d[2] - ce[2]) + p;
     }
     // radii widened by 2^-20 to cover the rounding of the centres and norms
     const double wf = 1.0 + 0x1p-20;
@@ -3110,12 +3188,9 @@ __global__ __launch_bounds__(64 * kTpWaves) void k_tile_pairs(const Tile *__rest
     }
 }
 
-// The same for two sorted positions, every field of both records read at once.
-__device__ __noinline__ void enc_candidate(const SRec *__restrict__ srec, double dt,
-                                           unsigned long long *keys, int cap, int *ce,
-                                           DevStats *stats, int pi, int pj)
+// The record of a sorted position, every field read at once.
+__device__ __forceinline__ HRec enc_load(const SRec &R)
 {
-    const SRec &R = srec[pi];
     HRec I;
     for (int k = 0; k < 3; ++k) {
         I.q0[k] = R.q0[k];
@@ -3125,23 +3200,32 @@ __device__ __noinline__ void enc_candidate(const SRec *__restrict__ srec, double
     }
     I.rc = R.rc;
     I.body = R.body;
-    enc_exact(I, srec[pj], dt, keys, cap, ce, &stats->cur_nce);
+    return I;
+}
+
+// The exact test of two sorted positions, and the append of a flagged pair.
+__device__ __noinline__ void enc_candidate(const SRec *__restrict__ srec, double dt,
+                                           unsigned long long *keys, int cap, int *ce,
+                                           DevStats *stats, int pi, int pj)
+{
+    enc_exact(enc_load(srec[pi]), srec[pj], dt, keys, cap, ce, &stats->cur_nce);
 }
 
 // One wave per kept tile pair (A, B), the waves striding over the count: lane
 // L holds the FP32 filter records of body L of tile A (midpoint with widened
 // bound, chord with big flag: 32 B), tile B's sit in the wave's LDS slice, and
 // every lane meets the 64 sources in turn with the relative-chord filter in
-// FP32, a superset of the pairs that can be flagged (the widening covers the
-// rounding).  A lane first meets tile B's bounds with the tile-pair test, as a
+// FP32 and the relative deviation in it (kEncP), a superset of the pairs that can be
+// flagged (the widening covers the rounding).  A lane first meets tile B's bounds with the tile-pair test, as a
 // tile of one body whose FP32 records stand for small balls around its FP64
 // values (third record: the mean endpoint deviation and its radius).  The
 // pairs the filter keeps are queued in the wave's LDS and take the exact test
-// from the sorted FP64 records in memory 64 at a time, one per lane (with long
-// steps most pairs of a dense ring pass the filter, and a test per pass would
-// run on a few lanes); a tile pair reads 5 KB of filter records instead of the
-// 176-byte records of both tiles.
-__global__ __launch_bounds__(kBlock) void k_enc_pairs(const Tile *__restrict__ tiles,
+// from the sorted FP64 records in memory 64 at a time, one per lane (with steps of a
+// radian most pairs of a dense ring pass the filter, and a test per pass would run on
+// a few lanes); a tile pair reads 6 KB of filter records instead of the 112-byte
+// records of both tiles.  One wave per workgroup: its 10 KB of LDS fit beside the force
+// kernel's workgroups, which hold most of a compute unit's.
+__global__ __launch_bounds__(64) void k_enc_pairs(const Tile *__restrict__ tiles,
                                                       const TileB *__restrict__ tileb,
                                                       const int2 *__restrict__ tpairs, int tp_cap,
                                                       const SRec *__restrict__ srec,
@@ -3151,18 +3235,18 @@ __global__ __launch_bounds__(kBlock) void k_enc_pairs(const Tile *__restrict__ t
                                                       int cap, int *__restrict__ ce,
                                                       DevStats *stats)
 {
-    __shared__ float4 sm_[kBlock / 64][64], sc_[kBlock / 64][64];
-    // per wave: queued pairs (lane | source << 8), fewer than 64 between drains
-    __shared__ int qe[kBlock / 64][128];
-    // per wave: tile A's exact-test fields (q0, v0, q1, v1, rc by plane; body
+    __shared__ float4 sm_[64], sc_[64], sd_[64];
+    // queued pairs (lane | source << 8), fewer than 64 between drains
+    __shared__ int qe[128];
+    // tile A's exact-test fields (q0, v0, q1, v1, rc by plane; body
     // index), staged at the tile pair's first full drain: a drain's 64 pairs
     // hold many targets and few sources
-    __shared__ double ha[kBlock / 64][13][64];
-    __shared__ int hb[kBlock / 64][64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    __shared__ double ha[13][64];
+    __shared__ int hb[64];
+    const int lane = threadIdx.x;
     const int npair = min(stats->cur_tp, tp_cap);
     const float qnan = __int_as_float(0x7fc00000);
-    for (int p = blockIdx.x * (kBlock / 64) + wv; p < npair; p += gridDim.x * (kBlock / 64)) {
+    for (int p = blockIdx.x; p < npair; p += gridDim.x) {
         const int2 AB = tpairs[p];
         Tile TA = tiles[AB.x], TB = tiles[AB.y];
         // uniform over the wave (one tile pair a wave): kept in scalar registers
@@ -3173,11 +3257,12 @@ __global__ __launch_bounds__(kBlock) void k_enc_pairs(const Tile *__restrict__ t
         // tile B's FP32 filter records in the wave's LDS slice (padding: NaN
         // midpoints, which no test passes)
         if (lane < TB.count) {
-            sm_[wv][lane] = em[2 * (size_t)(TB.start + lane)];
-            sc_[wv][lane] = em[2 * (size_t)(TB.start + lane) + 1];
+            sm_[lane] = em[2 * (size_t)(TB.start + lane)];
+            sc_[lane] = em[2 * (size_t)(TB.start + lane) + 1];
+            sd_[lane] = eg[TB.start + lane];
         } else {
-            sm_[wv][lane] = make_float4(qnan, qnan, qnan, 0.0f);
-            sc_[wv][lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            sm_[lane] = make_float4(qnan, qnan, qnan, 0.0f);
+            sc_[lane] = sd_[lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
         wave_lds_sync();
         const bool on = lane < TA.count;
@@ -3187,8 +3272,8 @@ __global__ __launch_bounds__(kBlock) void k_enc_pairs(const Tile *__restrict__ t
         // tile of one body whose FP32 records stand for balls around them: 2^-23
         // of each vector's norm covers its rounding, se and rc are rounded up
         bool lane_ok = false;
+        const float4 Gi = on ? eg[TA.start + lane] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         if (on) {
-            const float4 Gi = eg[TA.start + lane];
             const double Mv[3] = {Mi.x, Mi.y, Mi.z}, cv[3] = {Ci.x, Ci.y, Ci.z},
                          ev[3] = {Gi.x, Gi.y, Gi.z};
             const double sM = 0x1p-23 * norm3(Mv[0], Mv[1], Mv[2]);
@@ -3209,27 +3294,27 @@ __global__ __launch_bounds__(kBlock) void k_enc_pairs(const Tile *__restrict__ t
             const int li = e & 255;
             HRec I;
             for (int k = 0; k < 3; ++k) {
-                I.q0[k] = ha[wv][k][li];
-                I.v0[k] = ha[wv][3 + k][li];
-                I.q1[k] = ha[wv][6 + k][li];
-                I.v1[k] = ha[wv][9 + k][li];
+                I.q0[k] = ha[k][li];
+                I.v0[k] = ha[3 + k][li];
+                I.q1[k] = ha[6 + k][li];
+                I.v1[k] = ha[9 + k][li];
             }
-            I.rc = ha[wv][12][li];
-            I.body = hb[wv][li];
+            I.rc = ha[12][li];
+            I.body = hb[li];
             enc_exact(I, srec[TB.start + (e >> 8)], dt, keys, cap, ce, &stats->cur_nce);
         };
         auto stage = [&]() {
             if (!staged) {
                 if (on) {
-                    const SRec &R = srec[TA.start + lane];
+                    const HRec R = enc_load(srec[TA.start + lane]);
                     for (int k = 0; k < 3; ++k) {
-                        ha[wv][k][lane] = R.q0[k];
-                        ha[wv][3 + k][lane] = R.v0[k];
-                        ha[wv][6 + k][lane] = R.q1[k];
-                        ha[wv][9 + k][lane] = R.v1[k];
+                        ha[k][lane] = R.q0[k];
+                        ha[3 + k][lane] = R.v0[k];
+                        ha[6 + k][lane] = R.q1[k];
+                        ha[9 + k][lane] = R.v1[k];
                     }
-                    ha[wv][12][lane] = R.rc;
-                    hb[wv][lane] = R.body;
+                    ha[12][lane] = R.rc;
+                    hb[lane] = R.body;
                 }
                 staged = true;
             }
@@ -3240,15 +3325,19 @@ __global__ __launch_bounds__(kBlock) void k_enc_pairs(const Tile *__restrict__ t
         constexpr bool DG = decltype(diag_c)::value, SM = decltype(small_c)::value;
         for (int jj = 0; jj < nj; ++jj) {
             // source jj's FP32 filter records (one broadcast read each)
-            const float4 E = sm_[wv][jj], F = sc_[wv][jj];
+            const float4 E = sm_[jj], F = sc_[jj], H = sd_[jj];
             // relative chord filter in FP32 (the bound's widening covers the
             // rounding), every lane without a branch
             const float ex = E.x - Mi.x, ey = E.y - Mi.y, ez = E.z - Mi.z;
             const float cx = F.x - Ci.x, cy = F.y - Ci.y, cz = F.z - Ci.z;
             const float D2 = fmaf(ez, ez, fmaf(ey, ey, ex * ex));
             const float C2 = fmaf(cz, cz, fmaf(cy, cy, cx * cx));
+            const float hx = H.x - Gi.x, hy = H.y - Gi.y, hz = H.z - Gi.z;
+            const float H2 = fmaf(hz, hz, fmaf(hy, hy, hx * hx));
             const float Sr = (fabsf(E.w) + wi) + max_nonneg(F.w, Ci.w);
-            bool cand = lane_ok & (D2 <= fmaf(Sr, Sr, C2) * (2.0f * (1.0f + 0x1p-18f)));
+            // D <= C + 3/4 |dd| + S, squared as in enc_record
+            bool cand = lane_ok & (D2 <= fmaf(2.0f * Sr, Sr, fmaf(1.125f, H2, C2)) *
+                                             (2.0f * (1.0f + 0x1p-18f)));
             if (DG)
                 cand &= jj > lane;
             if (SM)
@@ -3258,17 +3347,17 @@ __global__ __launch_bounds__(kBlock) void k_enc_pairs(const Tile *__restrict__ t
             const unsigned long long mk = __builtin_amdgcn_ballot_w64(cand);
             if (mk) {
                 if ((mk >> lane) & 1ull)
-                    qe[wv][qn + __popcll(mk & ((1ull << lane) - 1ull))] = lane | (jj << 8);
+                    qe[qn + __popcll(mk & ((1ull << lane) - 1ull))] = lane | (jj << 8);
                 qn += __popcll(mk);
                 if (qn >= 64) {
                     stage();
                     wave_lds_sync();
-                    test_entry(qe[wv][lane]);
+                    test_entry(qe[lane]);
                     const int rest = qn - 64;
-                    const int v = lane < rest ? qe[wv][64 + lane] : 0;
+                    const int v = lane < rest ? qe[64 + lane] : 0;
                     wave_lds_sync();
                     if (lane < rest)
-                        qe[wv][lane] = v;
+                        qe[lane] = v;
                     wave_lds_sync();
                     qn = rest;
                 }
@@ -3294,7 +3383,7 @@ __global__ __launch_bounds__(kBlock) void k_enc_pairs(const Tile *__restrict__ t
             // both records from memory (a tile pair with few pairs to test)
             wave_lds_sync();
             if (lane < qn) {
-                const int e = qe[wv][lane];
+                const int e = qe[lane];
                 if (staged)
                     test_entry(e);
                 else
@@ -3882,7 +3971,12 @@ __global__ __launch_bounds__(NT) void k_steps_small(SmallArgs A)
                 A.q1x[i] = x;  A.q1y[i] = y;  A.q1z[i] = z;
                 A.v1x[i] = u;  A.v1y[i] = v;  A.v1z[i] = w;
                 A.rc1[i] = rc;
-                enc_record(mx, my, mz, cx, cy, cz, e34 + rc, inv_l, A.eq + 2 * (size_t)i);
+                const double c3[3] = {cx, cy, cz}, e0[3] = {u0, v0, w0}, e1[3] = {u, v, w};
+                double d[3];
+                const double p = enc_deviation(dt, e0, e1, c3, d);
+                enc_record(mx, my, mz, cx, cy, cz, d,
+                           0.75 * p + rc + 0x1p-45 * (norm1(mx, my, mz) + norm1(cx, cy, cz)), inv_l,
+                           A.eq + kEncRec * (size_t)i);
                 A.kflag[i] = fail ? 1 : 0;
                 A.ce[i] = 0;
             }
@@ -4599,7 +4693,7 @@ hipError_t launch_drift(const Dev &d, const Params &p, double dt, double sun_h,
 #define NB_DRIFT(FP_, NSL_, PART_)                                                                \
     k_drift<FP_, NSL_><<<d.nrb, kBlock * (NSL_ ? NSL_ : 1), 0, s>>>(                              \
         d.rblk, d.m0, p.G, dt, d.m, d.qx, d.qy, d.qz, d.vx, d.vy, d.vz, d.q0x, d.q0y, d.q0z,      \
-        d.v0x, d.v0y, d.v0z, d.kflag, d.stats, d.rpart_drift(), d.rc, d.mr, d.cr,                 \
+        d.v0x, d.v0y, d.v0z, d.kflag, d.stats, d.rpart_drift(), d.rc,                             \
         d.enc_sorted ? d.lnr_part : nullptr, d.q1x, d.q1y, d.q1z, d.v1x, d.v1y, d.v1z, d.rc1,     \
         part_in, sun_h, d.rb_first, d.rb_count, pre ? d.ptot : nullptr, (v8h *)d.eq, d.scale2,    \
         d.nce, PART_, d.ntot, d.maxs, d.nsplit, 0.5 * dt)
@@ -4767,7 +4861,7 @@ hipError_t launch_enc_gather(const Dev &d, double dt, hipStream_t s)
 {
     if (d.enc_sorted && d.nrb > 0) {
         k_cells<<<d.nrb, kBlock, 0, s>>>(d.rblk, d.rb_first, d.rb_count, d.lnr_part,
-                                          d.sys_cell_base, d.sys_cell_cnt, d.mr, d.cell_cnt,
+                                          d.sys_cell_base, d.sys_cell_cnt, d.q0x, d.q0y, d.q1x, d.q1y, d.cell_cnt,
                                           d.cell_of, d.slot_of, d.ce);
         const int nchunk = cdiv(d.ncell, kScanChunk);
         if (nchunk <= kScanSerialChunks) {
@@ -4782,8 +4876,8 @@ hipError_t launch_enc_gather(const Dev &d, double dt, hipStream_t s)
                                                                     d.slot_of);
         k_srec<<<cdiv(d.ntot, kBlock), kBlock, 0, s>>>(d.ntot, d.slot_of, d.sys_of, d.q0x, d.q0y, d.q0z,
                                                        d.v0x, d.v0y, d.v0z, d.q1x, d.q1y, d.q1z,
-                                                       d.v1x, d.v1y, d.v1z, d.rc1, d.mr, d.cr, d.off,
-                                                       d.nbig, d.srec, d.em, d.eg, dt);
+                                                       d.v1x, d.v1y, d.v1z, d.rc1, d.off,
+                                                       d.nbig, d.srec, d.em, d.eg, dt, d.enc_fused);
     }
     return hipGetLastError();
 }
@@ -4796,9 +4890,11 @@ hipError_t launch_enc_test(const Dev &d, double dt, hipStream_t s)
                                                                          d.tileb);
             k_tile_pairs<<<cdiv(d.nunit, kTpWaves), 64 * kTpWaves, 0, s>>>(
                 d.tiles, d.units, d.nunit, d.tileb, d.tpairs, d.tp_cap, d.stats);
-            // one wave per kept tile pair
-            int grid = std::min(std::max(1, cdiv(d.tp_cap, kBlock / 64)), 8192);
-            k_enc_pairs<<<grid, kBlock, 0, s>>>(d.tiles, d.tileb, d.tpairs, d.tp_cap, d.srec, d.em, d.eg, dt,
+            // one wave per kept tile pair, at most eight times as many as fit at once: they
+            // take turns where pairs differ (steps of a radian, 20011 bodies of a ring: 986
+            // us with 4096 waves, 743 with 16384, 707 with 32768)
+            const int grid = std::min(std::max(1, d.tp_cap), 32768);
+            k_enc_pairs<<<grid, 64, 0, s>>>(d.tiles, d.tileb, d.tpairs, d.tp_cap, d.srec, d.em, d.eg, dt,
                                                  d.keys, d.enc_cap, d.ce, d.stats);
         }
     } else if (d.new_ > 0) {

@@ -663,7 +663,7 @@ constexpr long long kSnapSetBytes = 1ll << 30;
 // and the further sets fit in kSnapSetBytes; else two.
 int snap_sets(const Params &p, const Tables &t, int ntot)
 {
-    const long long per = (long long)ntot * (13 * sizeof(double) + 2 * sizeof(double4));
+    const long long per = (long long)ntot * (13 * sizeof(double) + (t.enc_sorted ? 0 : kEncRecBytes));
     if (p.resolve || p.step_algo == 2 || t.enc_fused || per * (kSnapSets - 1) > kSnapSetBytes)
         return 2;
     return kSnapSets;
@@ -687,10 +687,9 @@ size_t carve(const Params &p, int nsys, int ntot, int enc_cap, const Tables &t, 
         *pl = (double *)take(nd);
     d.pk = (float4 *)take((size_t)ntot * 2 * sizeof(float4));
     d.mr = (double4 *)take((size_t)ntot * sizeof(double4));
-    d.cr = (double4 *)take((size_t)ntot * sizeof(double4));
-    const size_t eq_bytes = t.enc_sorted ? 0 : (size_t)ntot * 2 * sizeof(float4);
+    const size_t eq_all = (size_t)ntot * kEncRecBytes, eq_bytes = t.enc_sorted ? 0 : eq_all;
     d.eq = eq_bytes ? take(eq_bytes) : nullptr;
-    d.eq_alone = t.enc_alone ? take((size_t)ntot * 2 * sizeof(float4)) : nullptr;
+    d.eq_alone = t.enc_alone ? take(eq_all) : nullptr;
     d.scale2 = (double *)take((size_t)nsys * sizeof(double));
     // further sets of drift outputs: one per step of a captured run when the
     // check runs on a second queue and the sets stay within kSnapSetBytes, else two
@@ -701,8 +700,6 @@ size_t carve(const Params &p, int nsys, int ntot, int enc_cap, const Tables &t, 
                           &a.q1y, &a.q1z, &a.v1x, &a.v1y, &a.v1z, &a.rc1};
         for (double **pl : alt)
             *pl = (double *)take(nd);
-        a.mr = t.enc_sorted ? (double4 *)take((size_t)ntot * sizeof(double4)) : nullptr;
-        a.cr = t.enc_sorted ? (double4 *)take((size_t)ntot * sizeof(double4)) : nullptr;
         a.eq = eq_bytes ? take(eq_bytes) : nullptr;
     }
     d.kflag = (int *)take((size_t)ntot * sizeof(int));
