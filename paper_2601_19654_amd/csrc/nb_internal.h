@@ -23,11 +23,12 @@ constexpr int kSnapSets = 8;
 constexpr long long kSymMinItems(int g) { return g >= 2 ? 8192 : 0; }
 
 // Automatic targets per lane of the symmetric force: two (tiles of 128 bodies)
-// from kSymR1Items tile pairs of 128 on, else one: a pair of tiles of 128 is 23
-// us of one wave, of 64 10 us, and below this line the waves are too few to fill
-// the chip either way.  A step, one against two: 1500 bodies 31 / 46 us, 6000 bodies
-// 53 / 61 us (FP64) and 50 / 54 us (FP32C), 8000 bodies 67 / 63 and 60 / 56 us.
-constexpr long long kSymR1Items = 1536;
+// from kSymR1Items tile pairs of 128 on, else one: two targets per lane share each
+// source's fetch and moves, one gives four times the tile pairs to spread over the
+// chip.  The force kernel, one against two targets: 2500 bodies 7.7 / 10.0 us, 4000
+// 13.5 / 15.2 us (FP64) and 10.2 / 12.0 us (FP32C), 4500 bodies 17.4 / 15.6 and 13.6
+// / 12.4 us, 8 systems of up to 3000 bodies 23.7 / 22.8 us.
+constexpr long long kSymR1Items = 600;
 
 // Most split slots for which the drift launch of a run also sums the force's
 // partials (Dev::fin_drift).

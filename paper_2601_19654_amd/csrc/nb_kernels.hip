@@ -1656,21 +1656,40 @@ __device__ __forceinline__ double wave_rotl1(double v)
 // j), so that lane L reads source (L + k) mod 64 at entry L + k: a fixed
 // offset from the lane's own entry, no wrap.  Only the FP64 totals of the
 // sources' sums live here.
-template <int R>
+template <int R, int C = 1>
 struct alignas(512) SymTile64R {
     struct Sub {
         double x[128], y[128], z[128], m[128];
     } s[R];
     double r2[64 * R];                 // max(rc^2, DBL_MIN)
     double rc[64 * R];
-    double ax[64 * R], ay[64 * R], az[64 * R];   // tile J's FP64 totals
+    double tot[C][3][64 * R];          // tile J's FP64 totals (C copies: sym_part)
 };
 
-template <int R>
-__device__ __forceinline__ void put_src64(SymTile64R<R> &S, int e, double x, double y, double z,
+// The waves of a workgroup that share one tile pair (H of them, one tile pair per
+// workgroup) split its 64 R steps evenly: wave h takes the sub-tiles from t0 on,
+// t1 not included, and of each the kSteps steps from k0 on.  Where the waves
+// outnumber the sub-tiles, the kCopies waves of one sub-tile meet the same sources
+// and each adds to totals of its own (copy c).
+template <int R, int H>
+struct SymPart {
+    static constexpr int kCopies = H > R ? H / R : 1;
+    static constexpr int kSteps = 64 / kCopies;
+    int t0, t1, k0, c;
+    __device__ __forceinline__ explicit SymPart(int h)
+    {
+        c = h % kCopies;
+        t0 = h * R / H;
+        t1 = H > R ? t0 + 1 : (h + 1) * R / H;
+        k0 = c * kSteps;
+    }
+};
+
+template <int R, int C>
+__device__ __forceinline__ void put_src64(SymTile64R<R, C> &S, int e, double x, double y, double z,
                                           double m, double rcj)
 {
-    typename SymTile64R<R>::Sub &U = S.s[e / 64];
+    typename SymTile64R<R, C>::Sub &U = S.s[e / 64];
     const int j = e % 64;
     U.x[j] = U.x[j + 64] = x;
     U.y[j] = U.y[j + 64] = y;
@@ -1678,7 +1697,9 @@ __device__ __forceinline__ void put_src64(SymTile64R<R> &S, int e, double x, dou
     U.m[j] = U.m[j + 64] = m;
     S.rc[e] = rcj;
     S.r2[e] = fmax(rcj * rcj, DBL_MIN);
-    S.ax[e] = S.ay[e] = S.az[e] = 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+        S.tot[c][0][e] = S.tot[c][1][e] = S.tot[c][2][e] = 0.0;
 }
 
 template <int T>
@@ -1702,8 +1723,8 @@ __device__ __forceinline__ void put_src64(SymTile64<T> &S, int e, double x, doub
 // then carries only the source records (32 B per lane and step instead of 80
 // with the sums' read-modify-write), which keeps the FP64 loop off the LDS
 // bandwidth limit; the moves cost 6 VALU per step.
-template <int R, bool DIAG>
-__device__ __forceinline__ void sym_tile64_rot(SymTile64R<R> &L, int lane, int i0, int ni,
+template <int R, bool DIAG, int H, int C>
+__device__ __forceinline__ void sym_tile64_rot(SymTile64R<R, C> &L, const SymPart<R, H> &part, int lane, int i0, int ni, int nj,
                                                double inner, const double *__restrict__ rc,
                                                const double (&xi)[R], const double (&yi)[R],
                                                const double (&zi)[R], const double (&mi)[R],
@@ -1711,15 +1732,16 @@ __device__ __forceinline__ void sym_tile64_rot(SymTile64R<R> &L, int lane, int i
                                                double (&az)[R], int &near)
 {
 #pragma unroll 1
-    for (int t = 0; t < R; ++t) {
+    for (int t = part.t0; t < part.t1 && 64 * t < nj; ++t) {
         const double thr = fmax(tmi, wave_max(L.r2[64 * t + lane]));
-        // LDS address of x[lane] of sub-tile t; y, z, m at fixed offsets
+        // LDS address of x[lane + k0] of sub-tile t; y, z, m at fixed offsets
         constexpr uint32_t kY = 8 * 128, kZ = 16 * 128, kM = 24 * 128;
-        uint32_t ac = lds_addr(&L.s[t].x[lane]);
+        uint32_t ac = lds_addr(&L.s[t].x[lane + part.k0]);
         double jxs = lds_ld8(ac), jys = lds_ld8(ac + kY), jzs = lds_ld8(ac + kZ), jms = lds_ld8(ac + kM);
         double jx = 0.0, jy = 0.0, jz = 0.0;
 #pragma unroll 2
-        for (int k = 0; k < 64; ++k) {
+        for (int kk = 0; kk < SymPart<R, H>::kSteps; ++kk) {
+            const int k = part.k0 + kk;
             const uint32_t an = ac + 8;
             const double xn = lds_ld8(an), yn = lds_ld8(an + kY), zn = lds_ld8(an + kZ),
                          mn = lds_ld8(an + kM);
@@ -1772,24 +1794,29 @@ __device__ __forceinline__ void sym_tile64_rot(SymTile64R<R> &L, int lane, int i
             jzs = zn;
             jms = mn;
         }
-        L.ax[64 * t + lane] += jx;
-        L.ay[64 * t + lane] += jy;
-        L.az[64 * t + lane] += jz;
+        // the sums in this lane are now those of the source it would meet next
+        double (&tot)[3][64 * R] = L.tot[part.c];
+        const int js = 64 * t + ((lane + part.k0 + SymPart<R, H>::kSteps) & 63);
+        tot[0][js] += jx;
+        tot[1][js] += jy;
+        tot[2][js] += jz;
     }
 }
 
-template <int R, bool DIAG, int T>
-__device__ __forceinline__ void sym_round64(SymTile64R<R> &L, int lane, int i0, int ni, double inner,
+template <int R, bool DIAG, int T, int H, int C>
+__device__ __forceinline__ void sym_round64(SymTile64R<R, C> &L, const SymPart<R, H> &part, int lane,
+                                            int i0, int ni, int nj, double inner,
                                             const double *__restrict__ rc, const double (&xi)[R],
                                             const double (&yi)[R], const double (&zi)[R],
                                             const double (&mi)[R], double tmi, double (&ax)[R],
                                             double (&ay)[R], double (&az)[R], int &near)
 {
-    sym_tile64_rot<R, DIAG>(L, lane, i0, ni, inner, rc, xi, yi, zi, mi, tmi, ax, ay, az, near);
+    sym_tile64_rot<R, DIAG>(L, part, lane, i0, ni, nj, inner, rc, xi, yi, zi, mi, tmi, ax, ay, az, near);
 }
 
-template <int R, bool DIAG, int T>
-__device__ __forceinline__ void sym_round64(SymTile64<T> &L, int lane, int i0, int ni, double inner,
+template <int R, bool DIAG, int T, int H>
+__device__ __forceinline__ void sym_round64(SymTile64<T> &L, const SymPart<R, H> &, int lane, int i0,
+                                            int ni, int, double inner,
                                             const double *__restrict__ rc, const double (&xi)[R],
                                             const double (&yi)[R], const double (&zi)[R],
                                             const double (&mi)[R], double tmi, double (&ax)[R],
@@ -1798,8 +1825,25 @@ __device__ __forceinline__ void sym_round64(SymTile64<T> &L, int lane, int i0, i
     sym_tile64<R, DIAG, T>(L, lane, i0, ni, inner, rc, xi, yi, zi, mi, tmi, ax, ay, az, near);
 }
 
-template <int R, int G>
-__global__ __launch_bounds__(64 * G, R == 4 ? 2 : 3) void k_force64_sym(const FWork *__restrict__ work, int nitems,
+// Total c of source e of the tile, its copies in order.
+template <int R, int C>
+__device__ __forceinline__ double src_total(const SymTile64R<R, C> &S, int c, int e)
+{
+    double v = S.tot[0][c][e];
+#pragma unroll
+    for (int k = 1; k < C; ++k)
+        v += S.tot[k][c][e];
+    return v;
+}
+
+template <int T>
+__device__ __forceinline__ double src_total(const SymTile64<T> &S, int c, int e)
+{
+    return c == 0 ? S.ax[e] : (c == 1 ? S.ay[e] : S.az[e]);
+}
+
+template <int R, int G, int H = 1>
+__global__ __launch_bounds__(64 * G * H, R == 4 ? 2 : 3) void k_force64_sym(const FWork *__restrict__ work, int nitems,
                                                         const double *__restrict__ qx,
                                                         const double *__restrict__ qy,
                                                         const double *__restrict__ qz,
@@ -1808,19 +1852,25 @@ __global__ __launch_bounds__(64 * G, R == 4 ? 2 : 3) void k_force64_sym(const FW
                                                         double *__restrict__ fpart, int ntot, int maxs,
                                                         double inner, DevStats *stats)
 {
+    static_assert(H == 1 || (G == 1 && R <= 2), "only single tile pairs are shared");
     constexpr int T = 64 * R;
     // R <= 2: the sources' sums in registers, moved between lanes (LDS holds
     // the records only); R = 4 amortises the sums' LDS traffic over four
     // targets per lane and keeps them in LDS, within its LDS budget
-    using Tile = typename std::conditional<(R <= 2), SymTile64R<R>, SymTile64<T>>::type;
+    using Tile = typename std::conditional<(R <= 2), SymTile64R<R, SymPart<R, H>::kCopies>,
+                                           SymTile64<T>>::type;
     __shared__ Tile tl[G];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    // H > 1: the waves' sums of the targets
+    __shared__ double tgt[H > 1 ? H : 1][3][H > 1 ? T : 1];
+    const int lane = threadIdx.x & 63, wv = H > 1 ? 0 : threadIdx.x >> 6;
+    const int wh = threadIdx.x >> 6;
+    const SymPart<R, H> part(H > 1 ? wh : 0);
     int near = 0;
     for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
         const FWork wk = work[it];
         const bool diag = wk.i0 == wk.j0;
         // the G source tiles of super-tile J (nj real records from j0)
-        for (int k = threadIdx.x; k < G * T; k += 64 * G) {
+        for (int k = threadIdx.x; k < G * T; k += 64 * G * H) {
             // sources past the end: massless and far away (r^2 ~ 1e300, so
             // their weight underflows to 0 instead of meeting a target at r = 0)
             const bool ok = k < wk.nj;
@@ -1855,10 +1905,10 @@ __global__ __launch_bounds__(64 * G, R == 4 ? 2 : 3) void k_force64_sym(const FW
             const bool go = tni > 0 && s * T < wk.nj && !(diag && 2 * k == G && wv >= G / 2);
             if (go) {
                 if (diag && k == 0)
-                    sym_round64<R, true, T>(tl[s], lane, ti0, tni, inner, rc, xi, yi, zi, mi, tmi,
+                    sym_round64<R, true, T>(tl[s], part, lane, ti0, tni, wk.nj - s * T, inner, rc, xi, yi, zi, mi, tmi,
                                             ax, ay, az, near);
                 else
-                    sym_round64<R, false, T>(tl[s], lane, ti0, tni, inner, rc, xi, yi, zi, mi, tmi,
+                    sym_round64<R, false, T>(tl[s], part, lane, ti0, tni, wk.nj - s * T, inner, rc, xi, yi, zi, mi, tmi,
                                              ax, ay, az, near);
             }
             __syncthreads();
@@ -1870,10 +1920,16 @@ __global__ __launch_bounds__(64 * G, R == 4 ? 2 : 3) void k_force64_sym(const FW
             const int li = 64 * r + lane;
             if (li < tni) {
                 double sx_ = ax[r], sy_ = ay[r], sz_ = az[r];
+                if (H > 1) {
+                    tgt[wh % H][0][li] = sx_;
+                    tgt[wh % H][1][li] = sy_;
+                    tgt[wh % H][2][li] = sz_;
+                    continue;
+                }
                 if (diag) {
-                    sx_ += tl[wv].ax[li];
-                    sy_ += tl[wv].ay[li];
-                    sz_ += tl[wv].az[li];
+                    sx_ += src_total(tl[wv], 0, li);
+                    sy_ += src_total(tl[wv], 1, li);
+                    sz_ += src_total(tl[wv], 2, li);
                 }
                 const int i = ti0 + li;
                 fpart[((size_t)0 * maxs + wk.slot) * ntot + i] = sx_;
@@ -1881,14 +1937,29 @@ __global__ __launch_bounds__(64 * G, R == 4 ? 2 : 3) void k_force64_sym(const FW
                 fpart[((size_t)2 * maxs + wk.slot) * ntot + i] = sz_;
             }
         }
+        if (H > 1) {
+            // the waves' sums in wave order
+            __syncthreads();
+            for (int e = threadIdx.x; e < tni; e += 64 * H)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    double v = tgt[0][c][e];
+#pragma unroll
+                    for (int h = 1; h < H; ++h)
+                        v += tgt[h][c][e];
+                    if (diag)
+                        v += src_total(tl[0], c, e);
+                    fpart[((size_t)c * maxs + wk.slot) * ntot + ti0 + e] = v;
+                }
+        }
         if (!diag) {
             // super-tile J's sums to slot I
-            for (int k = threadIdx.x; k < wk.nj; k += 64 * G) {
+            for (int k = threadIdx.x; k < wk.nj; k += 64 * G * H) {
                 const Tile &S = tl[k / T];
                 const int e = k % T, j = wk.j0 + k;
-                fpart[((size_t)0 * maxs + wk.pad) * ntot + j] = S.ax[e];
-                fpart[((size_t)1 * maxs + wk.pad) * ntot + j] = S.ay[e];
-                fpart[((size_t)2 * maxs + wk.pad) * ntot + j] = S.az[e];
+                fpart[((size_t)0 * maxs + wk.pad) * ntot + j] = src_total(S, 0, e);
+                fpart[((size_t)1 * maxs + wk.pad) * ntot + j] = src_total(S, 1, e);
+                fpart[((size_t)2 * maxs + wk.pad) * ntot + j] = src_total(S, 2, e);
             }
         }
         __syncthreads();
@@ -1902,8 +1973,10 @@ __global__ __launch_bounds__(64 * G, R == 4 ? 2 : 3) void k_force64_sym(const FW
 // FP32C form of the symmetric tile pairs.  Pair terms in FP32 from the hi/lo
 // records.  Tile I's sums: FP32 runs of half a sub-tile round (32 steps)
 // merged by two-sum into a (hi, lo) pair per target.  Tile J's sums: an FP32
-// run sum per source in LDS over the same 32 steps, added to the source's FP64
-// total when the run ends.  Changeover pairs in FP64 from the FP64 state: the
+// run sum per source over the same 32 steps (in registers that move between lanes, as
+// in FP64, or at R = 4 and with the encounter test fused in, in LDS), added to the
+// source's FP64 total when the run ends.  In registers: 8000 bodies in tiles of 64 37.3
+// -> 29.7 us, 131072 bodies in tiles of 128 4955 -> 4770 us.  Changeover pairs in FP64 from the FP64 state: the
 // target's part into its (hi, lo) pair, the source's part to its FP64 total.
 // Each split partial is stored rounded to FP32: a rounding of at most 2^-24 of
 // the partial, which is at most the sum of its terms' magnitudes, so all of a
@@ -1932,17 +2005,16 @@ struct ChgPart {
 
 // The rare branch of the FP32C pair loop, out of line so that it adds nothing
 // to the loop: target li of the item (position i0 + li, or a padded copy of
-// position i0 when li >= ni) against source jj (position j0 + jj, found from the
-// LDS addresses of its record, ja, and of the tile's first record, a0) at FP32
-// squared distance r2.  Positions are body indices, or with a sorted order
+// position i0 when li >= ni) against source jj (position j0 + jj) at FP32 squared
+// distance r2.  Positions are body indices, or with a sorted order
 // (ord != nullptr) the bodies ord[position].
 // Unless r2 is inside the pair's widened critical radius it returns hit = 0.
 // Otherwise the pair is evaluated in FP64 from the FP64 state: -m_i w (Q_j - Q_i)
 // goes to source jj's FP64 totals tot[jj], tot[T + jj], tot[2 T + jj], and the
 // target's part m_j w (Q_j - Q_i) is returned (zero for a padded target).
 __device__ __noinline__ ChgPart changeover_pair32(float r2, float r2j, const float4 *__restrict__ pk,
-                                                  int i0, int li, int ni, int j0, uint32_t ja,
-                                                  uint32_t a0, int T, double *tot,
+                                                  int i0, int li, int ni, int j0, int jj, int T,
+                                                  double *tot,
                                                   const double *__restrict__ qx,
                                                   const double *__restrict__ qy,
                                                   const double *__restrict__ qz,
@@ -1957,7 +2029,6 @@ __device__ __noinline__ ChgPart changeover_pair32(float r2, float r2j, const flo
     if (!(r2 < max_nonneg(pk[2 * (size_t)bi + 1].w, r2j)))
         return out;
     out.hit = 1;
-    const int jj = (int)((ja - a0) >> 4);
     const int bj = ord ? ord[j0 + jj] : j0 + jj;
     const double gx = qx[bj] - qx[bi], gy = qy[bj] - qy[bi], gz = qz[bj] - qz[bi];
     const double d2 = fma(gz, gz, fma(gy, gy, gx * gx));
@@ -2160,8 +2231,9 @@ __device__ __forceinline__ void sym_tile32c(SymTile32<T> &L, int lane, int i0, i
                         const bool on = !DIAG || (64 * r + lane < 64 * t + (lane ^ (k0 + kk)));
                         if (r2r[r] < thr && on) {
                             const ChgPart c = changeover_pair32(r2r[r], B.w, pk, i0, 64 * r + lane,
-                                                                ni, j0, ac, a0, T, L.ax, qx, qy,
-                                                                qz, m, rc, inner, ord);
+                                                                ni, j0, (int)((ac - a0) >> 4), T,
+                                                                L.ax, qx, qy, qz, m, rc, inner,
+                                                                ord);
                             if (c.hit) {
                                 add_f64_to_pair(hx[r], lx[r], c.x);
                                 add_f64_to_pair(hy[r], ly[r], c.y);
@@ -2212,6 +2284,207 @@ __device__ __forceinline__ void sym_tile32c(SymTile32<T> &L, int lane, int i0, i
     }
 }
 
+// Tile J of one wave for the FP32C loop with the source run sums in registers
+// (R <= 2), as SymTile64R: records twice over, FP64 totals in C copies.
+template <int R, int C>
+struct alignas(512) SymTile32R {
+    struct Sub {
+        float4 a[128];              // hi parts and mass
+        float4 b[128];              // lo parts and widened rc^2
+    } s[R];
+    double tot[C][3][64 * R];
+};
+
+template <int R, int C>
+__device__ __forceinline__ void put_src32(SymTile32R<R, C> &S, int e, float4 a, float4 b)
+{
+    typename SymTile32R<R, C>::Sub &U = S.s[e / 64];
+    const int j = e % 64;
+    U.a[j] = U.a[j + 64] = a;
+    U.b[j] = U.b[j + 64] = b;
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+        S.tot[c][0][e] = S.tot[c][1][e] = S.tot[c][2][e] = 0.0;
+}
+
+template <int T>
+__device__ __forceinline__ void put_src32(SymTile32<T> &S, int e, float4 a, float4 b)
+{
+    S.a[e] = a;
+    S.b[e] = b;
+    S.run[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    S.ax[e] = S.ay[e] = S.az[e] = 0.0;
+}
+
+template <int R, int C>
+__device__ __forceinline__ double src_total(const SymTile32R<R, C> &S, int c, int e)
+{
+    double v = S.tot[0][c][e];
+#pragma unroll
+    for (int k = 1; k < C; ++k)
+        v += S.tot[k][c][e];
+    return v;
+}
+
+template <int T>
+__device__ __forceinline__ double src_total(const SymTile32<T> &S, int c, int e)
+{
+    return c == 0 ? S.ax[e] : (c == 1 ? S.ay[e] : S.az[e]);
+}
+
+// A float moved one lane up the wave: lane L gets lane (L - 1) mod 64's value.
+__device__ __forceinline__ float wave_rotr1(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x13C, 0xF, 0xF, false));
+}
+
+// The tile pair of sym_tile32c with the sources' run sums in registers, as in
+// sym_tile64_rot but downwards: in step k lane L meets source (L - k) mod 64 (entry
+// 64 + L - k), and the sums move one lane up.  Over the radial order a close pair's
+// bodies are few positions apart, the source behind the target, and so meet in the
+// last steps: large terms at the end of a run lose the least (upwards the error of
+// the bodies in close pairs is a sixth larger).
+template <int R, bool DIAG, bool FAR, int H, int C>
+__device__ __forceinline__ void sym_tile32c_rot(
+    SymTile32R<R, C> &L, const SymPart<R, H> &part, int lane, int i0, int ni, int j0, int nj,
+    double inner, const float4 *__restrict__ pk, const double *__restrict__ qx,
+    const double *__restrict__ qy, const double *__restrict__ qz, const double *__restrict__ m,
+    const double *__restrict__ rc, const float (&xh)[R], const float (&yh)[R], const float (&zh)[R],
+    const float (&xl)[R], const float (&yl)[R], const float (&zl)[R], const float (&mi)[R],
+    float tmi, float (&hx)[R], float (&hy)[R], float (&hz)[R], float (&lx)[R], float (&ly)[R],
+    float (&lz)[R], int &near, const int *__restrict__ ord, unsigned far)
+{
+    constexpr int kRun = SymPart<R, H>::kSteps < 32 ? SymPart<R, H>::kSteps : 32;
+    double(&tot)[3][64 * R] = L.tot[part.c];
+#pragma unroll 1
+    for (int t = part.t0; t < part.t1 && 64 * t < nj; ++t) {
+        const bool fart = FAR && !DIAG && ((far >> t) & 1u);
+        const float thr = max_nonneg(tmi, wave_max_nonneg(L.s[t].b[lane].w));
+#pragma unroll 1
+        for (int k0 = part.k0; k0 < part.k0 + SymPart<R, H>::kSteps; k0 += kRun) {
+            float tx[R], ty[R], tz[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                tx[r] = ty[r] = tz[r] = 0.0f;
+            float jx = 0.0f, jy = 0.0f, jz = 0.0f;
+            // LDS address of a[64 + lane - k0] of sub-tile t; its b record 16 * 128 on
+            uint32_t ac = lds_addr(&L.s[t].a[64 + lane - k0]);
+            if (fart) {
+                float4 A = lds_ld4(ac);
+#pragma unroll 4
+                for (int kk = 0; kk < kRun; ++kk) {
+                    ac -= 16;
+                    const float4 An = lds_ld4(ac);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const float dx = A.x - xh[r], dy = A.y - yh[r], dz = A.z - zh[r];
+                        const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                        const float y = __builtin_amdgcn_rsqf(r2);
+                        const float q = y * (y * y);
+                        const float wi = A.w * q, wj = mi[r] * q;
+                        tx[r] = fmaf(wi, dx, tx[r]);
+                        ty[r] = fmaf(wi, dy, ty[r]);
+                        tz[r] = fmaf(wi, dz, tz[r]);
+                        jx = fmaf(-wj, dx, jx);
+                        jy = fmaf(-wj, dy, jy);
+                        jz = fmaf(-wj, dz, jz);
+                    }
+                    jx = wave_rotr1(jx);
+                    jy = wave_rotr1(jy);
+                    jz = wave_rotr1(jz);
+                    A = An;
+                }
+            } else {
+                float4 A = lds_ld4(ac), B = lds_ld4(ac + 16 * 128);
+#pragma unroll 2
+                for (int kk = 0; kk < kRun; ++kk) {
+                    ac -= 16;
+                    const float4 An = lds_ld4(ac), Bn = lds_ld4(ac + 16 * 128);
+                    // the R pairs' geometry first, then one branch for the rare
+                    // ones, so that the R chains share one basic block
+                    float dxr[R], dyr[R], dzr[R], r2r[R], qr[R];
+                    bool cand = false;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        dxr[r] = (A.x - xh[r]) + (B.x - xl[r]);
+                        dyr[r] = (A.y - yh[r]) + (B.y - yl[r]);
+                        dzr[r] = (A.z - zh[r]) + (B.z - zl[r]);
+                        r2r[r] = fmaf(dzr[r], dzr[r], fmaf(dyr[r], dyr[r], dxr[r] * dxr[r]));
+                        const float y = __builtin_amdgcn_rsqf(r2r[r]);
+                        qr[r] = y * (y * y);
+                        const bool on = !DIAG || (64 * r + lane < 64 * t + ((lane - k0 - kk) & 63));
+                        cand |= r2r[r] < thr && on;
+                        if (DIAG)
+                            qr[r] = on ? qr[r] : 0.0f;
+                    }
+                    if (cand) {
+                        const int sj = 64 * t + ((lane - k0 - kk) & 63);
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            const bool on = !DIAG || 64 * r + lane < sj;
+                            if (r2r[r] < thr && on) {
+                                const ChgPart c = changeover_pair32(
+                                    r2r[r], B.w, pk, i0, 64 * r + lane, ni, j0, sj, 64 * R,
+                                    &tot[0][0], qx, qy, qz, m, rc, inner, ord);
+                                if (c.hit) {
+                                    add_f64_to_pair(hx[r], lx[r], c.x);
+                                    add_f64_to_pair(hy[r], ly[r], c.y);
+                                    add_f64_to_pair(hz[r], lz[r], c.z);
+                                    qr[r] = 0.0f;
+                                    ++near;
+                                }
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const float dx = dxr[r], dy = dyr[r], dz = dzr[r], q = qr[r];
+                        const float wi = A.w * q, wj = mi[r] * q;
+                        tx[r] = fmaf(wi, dx, tx[r]);
+                        ty[r] = fmaf(wi, dy, ty[r]);
+                        tz[r] = fmaf(wi, dz, tz[r]);
+                        jx = fmaf(-wj, dx, jx);
+                        jy = fmaf(-wj, dy, jy);
+                        jz = fmaf(-wj, dz, jz);
+                    }
+                    jx = wave_rotr1(jx);
+                    jy = wave_rotr1(jy);
+                    jz = wave_rotr1(jz);
+                    A = An;
+                    B = Bn;
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                two_sum_f(hx[r], lx[r], tx[r]);
+                two_sum_f(hy[r], ly[r], ty[r]);
+                two_sum_f(hz[r], lz[r], tz[r]);
+            }
+            // the sums in this lane are now those of the source it would meet next
+            const int js = 64 * t + ((lane - k0 - kRun) & 63);
+            tot[0][js] += (double)jx;
+            tot[1][js] += (double)jy;
+            tot[2][js] += (double)jz;
+        }
+    }
+}
+
+template <int R, bool DIAG, int T, bool FAR, int H, int C, class... A>
+__device__ __forceinline__ void sym_round32(SymTile32R<R, C> &L, const SymPart<R, H> &part, int lane,
+                                            int i0, int ni, int j0, int nj, unsigned far, A &&...a)
+{
+    sym_tile32c_rot<R, DIAG, FAR>(L, part, lane, i0, ni, j0, nj, a..., far);
+}
+
+template <int R, bool DIAG, int T, bool FAR, int H, class... A>
+__device__ __forceinline__ void sym_round32(SymTile32<T> &L, const SymPart<R, H> &, int lane, int i0,
+                                            int ni, int j0, int, unsigned far, A &&...a)
+{
+    const EncCtx noenc{};
+    float4 noem[R];
+    sym_tile32c<R, DIAG, T, false, FAR>(L, lane, i0, ni, j0, a..., noenc, noem, noem, 0u, far);
+}
+
 // Two 64-body tiles of the radial order are far apart for the FP32C pair loop
 // when the gap between their shells, |xh_i| in [rmin, rmax] (records written
 // by k_sun_drift with the FP32C records), exceeds 2^21 times the sum of their low parts' largest norms
@@ -2230,8 +2503,8 @@ __device__ __forceinline__ bool far_tiles(float4 a, float4 b)
 // SORT: the positions of the work items are positions of the radial order
 // (ord: position -> body), whose tile bounds rtb (system s's tiles from
 // rtf[s], 64 positions each from off[s]) mark the far sub-tile pairs.
-template <int R, int G, bool SORT = false>
-__global__ __launch_bounds__(64 * G, R == 4 ? 2 : 3) void k_force32c_sym(const FWork *__restrict__ work, int nitems,
+template <int R, int G, bool SORT = false, int H = 1>
+__global__ __launch_bounds__(64 * G * H, R == 4 ? 2 : 3) void k_force32c_sym(const FWork *__restrict__ work, int nitems,
                                                          const float4 *__restrict__ pk,
                                                          const double *__restrict__ qx,
                                                          const double *__restrict__ qy,
@@ -2246,29 +2519,31 @@ __global__ __launch_bounds__(64 * G, R == 4 ? 2 : 3) void k_force32c_sym(const F
                                                          const int *__restrict__ off = nullptr)
 {
     constexpr int T = 64 * R;
-    __shared__ SymTile32<T> tl[G];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    static_assert(H == 1 || (G == 1 && R <= 2), "only single tile pairs are shared");
+    using Tile = typename std::conditional<(R <= 2), SymTile32R<R, SymPart<R, H>::kCopies>,
+                                           SymTile32<T>>::type;
+    __shared__ Tile tl[G];
+    // H > 1: the waves' sums of the targets
+    __shared__ double tgt[H > 1 ? H : 1][3][H > 1 ? T : 1];
+    const int lane = threadIdx.x & 63, wv = H > 1 ? 0 : threadIdx.x >> 6;
+    const int wh = threadIdx.x >> 6;
+    const SymPart<R, H> part(H > 1 ? wh : 0);
     const size_t plane = (size_t)maxs * ntot;
     int near = 0;
     for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
         const FWork wk = work[it];
         const bool diag = wk.i0 == wk.j0;
         // the G source tiles of super-tile J (nj real records from j0)
-        for (int k = threadIdx.x; k < G * T; k += 64 * G) {
-            SymTile32<T> &S = tl[k / T];
-            const int e = k % T;
+        for (int k = threadIdx.x; k < G * T; k += 64 * G * H) {
             // sources past the end: massless and far away (r^2 ~ 1e36, so the
             // weight underflows to 0 instead of meeting a target at r = 0)
+            float4 A = make_float4(1e18f, 1e18f, 1e18f, 0.0f), B = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             if (k < wk.nj) {
                 const int b = SORT ? ord[wk.j0 + k] : wk.j0 + k;
-                S.a[e] = pk[2 * (size_t)b];
-                S.b[e] = pk[2 * (size_t)b + 1];
-            } else {
-                S.a[e] = make_float4(1e18f, 1e18f, 1e18f, 0.0f);
-                S.b[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                A = pk[2 * (size_t)b];
+                B = pk[2 * (size_t)b + 1];
             }
-            S.run[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            S.ax[e] = S.ay[e] = S.az[e] = 0.0;
+            put_src32(tl[k / T], k % T, A, B);
         }
         __syncthreads();
         // this wave's target tile: tni bodies from ti0 (none when tni <= 0)
@@ -2291,8 +2566,6 @@ __global__ __launch_bounds__(64 * G, R == 4 ? 2 : 3) void k_force32c_sym(const F
             hx[r] = hy[r] = hz[r] = lx[r] = ly[r] = lz[r] = 0.0f;
         }
         tmi = wave_max_nonneg(tmi);
-        const EncCtx noenc{};
-        float4 noem[R];
         // Round k: wave w pairs its target tile with source tile (w + k) mod G, so
         // that the waves of a round update distinct source tiles.  Off the
         // diagonal G rounds cover the G x G tile pairs.  On the diagonal (I = J)
@@ -2305,10 +2578,10 @@ __global__ __launch_bounds__(64 * G, R == 4 ? 2 : 3) void k_force32c_sym(const F
             const bool go = tni > 0 && s * T < wk.nj && !(diag && 2 * k == G && wv >= G / 2);
             if (go) {
                 if (diag && k == 0) {
-                    sym_tile32c<R, true, T>(tl[s], lane, ti0, tni, wk.j0 + s * T, inner, pk, qx,
-                                            qy, qz, m, rc, xh, yh, zh, xl, yl, zl, mi, tmi, hx, hy,
-                                            hz, lx, ly, lz, near, SORT ? ord : nullptr, noenc, noem,
-                                            noem, 0u);
+                    sym_round32<R, true, T, false>(tl[s], part, lane, ti0, tni, wk.j0 + s * T,
+                                                   wk.nj - s * T, 0u, inner, pk, qx, qy, qz, m, rc,
+                                                   xh, yh, zh, xl, yl, zl, mi, tmi, hx, hy, hz, lx,
+                                                   ly, lz, near, SORT ? ord : nullptr);
                 } else {
                     // far source sub-tiles (radial order, no padded targets)
                     unsigned far = 0u;
@@ -2326,11 +2599,10 @@ __global__ __launch_bounds__(64 * G, R == 4 ? 2 : 3) void k_force32c_sym(const F
                             far |= f ? 1u << t : 0u;
                         }
                     }
-                    sym_tile32c<R, false, T, false, SORT>(tl[s], lane, ti0, tni, wk.j0 + s * T,
-                                                          inner, pk, qx, qy, qz, m, rc, xh, yh, zh,
-                                                          xl, yl, zl, mi, tmi, hx, hy, hz, lx, ly,
-                                                          lz, near, SORT ? ord : nullptr, noenc,
-                                                          noem, noem, 0u, far);
+                    sym_round32<R, false, T, SORT>(tl[s], part, lane, ti0, tni, wk.j0 + s * T,
+                                                   wk.nj - s * T, far, inner, pk, qx, qy, qz, m,
+                                                   rc, xh, yh, zh, xl, yl, zl, mi, tmi, hx, hy, hz,
+                                                   lx, ly, lz, near, SORT ? ord : nullptr);
                 }
             }
             __syncthreads();
@@ -2345,24 +2617,45 @@ __global__ __launch_bounds__(64 * G, R == 4 ? 2 : 3) void k_force32c_sym(const F
                 double sx_ = (double)hx[r] + (double)lx[r];
                 double sy_ = (double)hy[r] + (double)ly[r];
                 double sz_ = (double)hz[r] + (double)lz[r];
+                if (H > 1) {
+                    tgt[wh % H][0][li] = sx_;
+                    tgt[wh % H][1][li] = sy_;
+                    tgt[wh % H][2][li] = sz_;
+                    continue;
+                }
                 if (diag) {
-                    sx_ += tl[wv].ax[li];
-                    sy_ += tl[wv].ay[li];
-                    sz_ += tl[wv].az[li];
+                    sx_ += src_total(tl[wv], 0, li);
+                    sy_ += src_total(tl[wv], 1, li);
+                    sz_ += src_total(tl[wv], 2, li);
                 }
                 fpart[(size_t)wk.slot * ntot + i] = (float)sx_;
                 fpart[plane + (size_t)wk.slot * ntot + i] = (float)sy_;
                 fpart[2 * plane + (size_t)wk.slot * ntot + i] = (float)sz_;
             }
         }
+        if (H > 1) {
+            // the waves' sums in wave order
+            __syncthreads();
+            for (int e = threadIdx.x; e < tni; e += 64 * H)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    double v = tgt[0][c][e];
+#pragma unroll
+                    for (int h = 1; h < H; ++h)
+                        v += tgt[h][c][e];
+                    if (diag)
+                        v += src_total(tl[0], c, e);
+                    fpart[c * plane + (size_t)wk.slot * ntot + ti0 + e] = (float)v;
+                }
+        }
         if (!diag) {
             // super-tile J's sums to slot I
-            for (int k = threadIdx.x; k < wk.nj; k += 64 * G) {
-                const SymTile32<T> &S = tl[k / T];
+            for (int k = threadIdx.x; k < wk.nj; k += 64 * G * H) {
+                const Tile &S = tl[k / T];
                 const int e = k % T, j = wk.j0 + k;
-                fpart[((size_t)0 * maxs + wk.pad) * ntot + j] = (float)S.ax[e];
-                fpart[((size_t)1 * maxs + wk.pad) * ntot + j] = (float)S.ay[e];
-                fpart[((size_t)2 * maxs + wk.pad) * ntot + j] = (float)S.az[e];
+                fpart[((size_t)0 * maxs + wk.pad) * ntot + j] = (float)src_total(S, 0, e);
+                fpart[((size_t)1 * maxs + wk.pad) * ntot + j] = (float)src_total(S, 1, e);
+                fpart[((size_t)2 * maxs + wk.pad) * ntot + j] = (float)src_total(S, 2, e);
             }
         }
         __syncthreads();
@@ -4717,6 +5010,26 @@ hipError_t launch_drift(const Dev &d, const Params &p, double dt, double sun_h,
     return hipGetLastError();
 }
 
+// Waves that share one tile pair of the symmetric force (one tile pair per
+// workgroup).  One wave takes a pair of tiles of 64 in 10 us and of 128 in 24 us, so
+// that few pairs leave the chip idle, and as many as a few per wave slot (3072)
+// leave its last round half empty; each further wave stages and sums up for itself.
+// The force kernel alone, 1 / 2 / 4 waves: tiles of 64, 1001 bodies (136 pairs) 10.0
+// / 7.2 / 5.5 us, 3001 bodies (1128) 13.7 / 11.3 / 11.2 us in FP64 and 11.4 / 8.8 /
+// 9.6 us in FP32C, 6000 bodies (4465) 26.3 / 26.9 / 28.3 us; tiles of 128, 5003
+// bodies (820) 25.2 / 20.6 / 19.7 us, 10000 (3160) 63.3 / 54.0 / 52.7 us, 131072
+// (524800) 7540 / 7681 / 8212 us.  Eight steps with their encounter checks, whose small
+// kernels run in the gaps: FP64 13000 bodies (5253) 971 / 924 / 963 us, 20000 (12403)
+// 1901 / 1836 / 1905 us, 30000 (27730) 3655 / 3623 / 3792 us; FP32C, whose shorter pair
+// terms leave more of the time to each wave's own part, 13000 bodies 821 / 766 / 809
+// us, 16384 (8256) 950 / 990 us, 30000 2647 / 2713 / 2930 us.
+int sym_waves(int nitems, const Params &p)
+{
+    if (p.force_r == 1)
+        return nitems < 1024 ? 4 : (nitems < 4096 ? 2 : 1);
+    return nitems < 4096 ? 4 : (nitems < (p.mode == 1 ? 8192 : 1 << 18) ? 2 : 1);
+}
+
 hipError_t launch_force(const Dev &d, const Params &p, hipStream_t s)
 {
     if (d.nfw == 0)
@@ -4729,38 +5042,38 @@ hipError_t launch_force(const Dev &d, const Params &p, hipStream_t s)
 #define NB_SYM32_ARGS d.fwork, d.nfw, d.pk, d.qx, d.qy, d.qz, d.m, d.rc, d.fpart32, d.ntot, \
                       d.maxs, p.inner, d.stats
 #define NB_RSYM32_ARGS NB_SYM32_ARGS, d.rord, d.rtb, d.rtf, d.off
-#define NB_SYM_G(R_)                                                                          \
+// G waves on G tile pairs each, or (H_ > 1) H_ waves on one tile pair
+#define NB_SYM_GH(R_, G_, H_)                                                                 \
     do {                                                                                      \
-        if (p.mode == 1 && d.force_rsort) {                                                   \
-            if (d.sym_g == 4)                                                                 \
-                k_force32c_sym<R_, 4, true><<<grid, 256, 0, s>>>(NB_RSYM32_ARGS);             \
-            else if (d.sym_g == 2)                                                            \
-                k_force32c_sym<R_, 2, true><<<grid, 128, 0, s>>>(NB_RSYM32_ARGS);             \
-            else                                                                              \
-                k_force32c_sym<R_, 1, true><<<grid, 64, 0, s>>>(NB_RSYM32_ARGS);              \
-        } else if (p.mode == 1) {                                                             \
-            if (d.sym_g == 4)                                                                 \
-                k_force32c_sym<R_, 4><<<grid, 256, 0, s>>>(NB_SYM32_ARGS);                    \
-            else if (d.sym_g == 2)                                                            \
-                k_force32c_sym<R_, 2><<<grid, 128, 0, s>>>(NB_SYM32_ARGS);                    \
-            else                                                                              \
-                k_force32c_sym<R_, 1><<<grid, 64, 0, s>>>(NB_SYM32_ARGS);                     \
-        } else {                                                                              \
-            if (d.sym_g == 4)                                                                 \
-                k_force64_sym<R_, 4><<<grid, 256, 0, s>>>(NB_SYM_ARGS);                       \
-            else if (d.sym_g == 2)                                                            \
-                k_force64_sym<R_, 2><<<grid, 128, 0, s>>>(NB_SYM_ARGS);                       \
-            else                                                                              \
-                k_force64_sym<R_, 1><<<grid, 64, 0, s>>>(NB_SYM_ARGS);                        \
-        }                                                                                     \
+        if (p.mode == 1 && d.force_rsort)                                                     \
+            k_force32c_sym<R_, G_, true, H_><<<grid, 64 * G_ * H_, 0, s>>>(NB_RSYM32_ARGS);   \
+        else if (p.mode == 1)                                                                 \
+            k_force32c_sym<R_, G_, false, H_><<<grid, 64 * G_ * H_, 0, s>>>(NB_SYM32_ARGS);   \
+        else                                                                                  \
+            k_force64_sym<R_, G_, H_><<<grid, 64 * G_ * H_, 0, s>>>(NB_SYM_ARGS);             \
+    } while (0)
+#define NB_SYM_G(R_, HMAX_)                                                                   \
+    do {                                                                                      \
+        const int h = std::min(HMAX_, sym_waves(d.nfw, p));                                   \
+        if (d.sym_g == 4)                                                                     \
+            NB_SYM_GH(R_, 4, 1);                                                              \
+        else if (d.sym_g == 2)                                                                \
+            NB_SYM_GH(R_, 2, 1);                                                              \
+        else if (HMAX_ >= 4 && h == 4)                                                        \
+            NB_SYM_GH(R_, 1, (HMAX_ >= 4 ? 4 : 1));                                           \
+        else if (HMAX_ >= 2 && h >= 2)                                                        \
+            NB_SYM_GH(R_, 1, (HMAX_ >= 2 ? 2 : 1));                                           \
+        else                                                                                  \
+            NB_SYM_GH(R_, 1, 1);                                                              \
     } while (0)
         if (p.force_r == 1)
-            NB_SYM_G(1);
+            NB_SYM_G(1, 4);
         else if (p.force_r == 4)
-            NB_SYM_G(4);
+            NB_SYM_G(4, 1);
         else
-            NB_SYM_G(2);
+            NB_SYM_G(2, 4);
 #undef NB_SYM_G
+#undef NB_SYM_GH
 #undef NB_SYM_ARGS
 #undef NB_RSYM32_ARGS
 #undef NB_SYM32_ARGS

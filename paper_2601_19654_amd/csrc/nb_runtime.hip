@@ -482,8 +482,9 @@ long long sym_items(int nsys, const int32_t *off, int TI)
 // widest whose work items (super-tile pairs, one workgroup each) reach
 // kSymMinItems(g).  Measured on whole steps: wider super-tiles write fewer
 // partials but cost the force kernel its rounds' barriers, which pays from
-// about 32 workgroups per compute unit (256 systems of 200-4000 bodies: 2;
-// 131072 bodies: 4), not at 16384 bodies (1).
+// about 32 workgroups per compute unit (a step at widths 1 / 2 / 4: 256 systems of
+// 200-4000 bodies 728 / 668 / 701 us, 34000 bodies 420 / 395 / 412 us, 65536 bodies
+// 1425 / 1335 / 1318 us, FP32C), not at 16384 bodies (1).
 int sym_width(const Params &p, int nsys, const int32_t *off)
 {
     if (p.force_g == 1 || p.force_g == 2 || p.force_g == 4)
