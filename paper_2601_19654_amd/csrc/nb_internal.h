@@ -30,9 +30,15 @@ constexpr long long kSymMinItems(int g) { return g >= 2 ? 8192 : 0; }
 // / 12.4 us, 8 systems of up to 3000 bodies 23.7 / 22.8 us.
 constexpr long long kSymR1Items = 600;
 
-// Most split slots for which the drift launch of a run also sums the force's
-// partials (Dev::fin_drift).
+// Most split slots for which the launch after the force (the next drift, with drag the
+// kick) also sums its partials (Dev::fin_slots), and, where several threads sum a
+// body's, most workgroups: those threads only help to sum, and a launch that fills the
+// chip pays for their place.  Four steps, partials summed apart / in the drift: 16
+// systems of 500 bodies 175 / 162 us, 200 systems of up to 900 (520 workgroups) 406 / 393
+// us, 200 systems of up to 2000 (960) 736 / 754 us, 256 systems of up to 4000 (2200)
+// 2570 / 2657 us.
 constexpr int kFinDriftSlots = 64;
+constexpr int kFinDriftBlocks = 768;
 // Threads per body that sum split partials, by the largest slot count: about eight
 // slots each, at most `most` (4 or 16) threads.
 constexpr int fin_slices(int maxs, int most)
@@ -143,7 +149,8 @@ struct Dev {
     // tables
     RBlk *rblk;  int nrb;
     FWork *fwork; int nfw; int maxs;
-    int fin_drift;        // inside a run the drift launch sums the force's partials and kicks
+    int fin_slots;        // the launch after the force sums its partials: with drag the kick,
+    int fin_drift;        // else inside a run the next drift (which also kicks)
     int ns_all;           // the split count of every system with bodies, if they all share it; else 0
     PWork *ework; int new_;
     PWork *dwork; int ndw;
@@ -288,7 +295,8 @@ hipError_t launch_to_dh(const Dev &d, const double *x, const double *v, int fram
 hipError_t launch_from_dh(const Dev &d, double *x, double *v, int frame, hipStream_t s);
 // per-block sums of m V into part (rpart or rpart_drift())
 hipError_t launch_momentum(const Dev &d, double *part, hipStream_t s);
-hipError_t launch_kick(const Dev &d, const Params &p, double h, hipStream_t s);
+hipError_t launch_kick(const Dev &d, const Params &p, double h, hipStream_t s,
+                       double *part_in = nullptr, double *part_out = nullptr, bool fin = false);
 // S(h) from the per-block sums of m V in `part`; rcrit: also the critical radii
 // (and the FP32C records and per-block largest rc^2)
 hipError_t launch_sun_drift(const Dev &d, double h, int rcrit, const Params &p, const double *part,

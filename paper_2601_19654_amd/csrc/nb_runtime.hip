@@ -718,7 +718,10 @@ size_t carve(const Params &p, int nsys, int ntot, int enc_cap, const Tables &t, 
     d.nfw = (int)t.fwork.size();
     d.fwork = (FWork *)take(t.fwork.size() * sizeof(FWork));
     d.maxs = t.maxs;
-    d.fin_drift = !p.drag && !p.resolve && !t.force_rsort && !t.enc_fused && t.maxs <= kFinDriftSlots;
+    // (the threads that only help to sum cost a launch of many workgroups its occupancy)
+    d.fin_slots = !t.force_rsort && !t.enc_fused && t.maxs <= kFinDriftSlots &&
+                  (t.maxs <= 8 || d.nrb <= kFinDriftBlocks);
+    d.fin_drift = d.fin_slots && !p.drag && !p.resolve;
     d.ns_all = t.maxs;
     for (int s = 0; s < nsys; ++s)
         if (t.rb_count[s] > 0 && t.nsplit[s] != t.maxs)
@@ -902,8 +905,12 @@ int enqueue_step_tail(nb_ctx *c, double dt, bool last, bool to_drift = false)
     else
         HIP_OK(c, launch_force(d, c->p, c->stream));
     if (c->p.drag) {
-        HIP_OK(c, launch_force_finalize(d, c->p, 0.0, 1, c->stream, ord, fz));
-        HIP_OK(c, launch_kick(d, c->p, h, c->stream));
+        // V is the drift's: its sums of m V are this kick's, and the kick sums the
+        // force's partials itself where the drift would without drag
+        const bool fin = d.fin_slots && !fz;
+        if (!fin)
+            HIP_OK(c, launch_force_finalize(d, c->p, 0.0, 1, c->stream, ord, fz));
+        HIP_OK(c, launch_kick(d, c->p, h, c->stream, d.rpart_drift(), d.rpart, fin));
     } else if (!to_drift) {
         HIP_OK(c, launch_force_finalize(d, c->p, h, last ? 1 : 2, c->stream, ord, fz));
     }
@@ -941,9 +948,12 @@ int enqueue_run(nb_ctx *c, double dt, int steps)
             d.nce = &d.stats->set_nce[par];
         if (k >= c->d.nsnap)
             HIP_OK(c, hipStreamWaitEvent(c->stream, c->ev_join[par], 0));
+        // with drag, the sums of m V that the step before left serve the opening kick
+        const bool again = !merge && k > 0;
         if (first)
-            HIP_OK(c, launch_kick(d, c->p, h, c->stream));
-        HIP_OK(c, launch_drift(d, c->p, dt, h, merge ? d.rpart_prev() : d.rpart, c->stream,
+            HIP_OK(c, launch_kick(d, c->p, h, c->stream, again ? d.rpart : nullptr,
+                                  again ? d.rpart_prev() : d.rpart));
+        HIP_OK(c, launch_drift(d, c->p, dt, h, merge || again ? d.rpart_prev() : d.rpart, c->stream,
                                d.fin_drift && !first));
         HIP_OK(c, hipEventRecord(c->ev_fork[par], c->stream));
         if ((r = enqueue_step_tail(c, dt, last, d.fin_drift && !last)))

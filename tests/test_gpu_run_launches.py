@@ -1,8 +1,10 @@
 """Steps inside a captured run leave launches out (the force's partials are summed
-by the next step's drift launch, the direct checks of a run are counted at its
-end): the same bits and the same lists and statistics as single steps, which are
+by the next step's drift launch, with gas drag by the kick, whose sums of m V the steps
+hand on; the direct checks of a run are counted at its end): the same bits and the same lists and statistics as single steps, which are
 runs of one step, at the slot counts where the summing changes (8, 16, 32, 64
 slots), for batches, small bodies and both modes."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -36,6 +38,33 @@ def _check(w, **kw):
 def test_slot_counts(n, mode):
     # tiles of 64 bodies: 5 .. 65 slots
     assert _check(workloads.ring(n, m=3e-7), mode=mode, step_algo=1, force_r=1, force_g=1) > 0
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("n", [300, 512, 513, 1025, 4096, 4097])
+def test_drag(n, mode):
+    w = dataclasses.replace(workloads.ring(n, m=3e-7), drag=True)
+    kw = dict(mode=mode, step_algo=1, force_r=1, force_g=1, force_algo=2)
+    _check(w, **kw)
+    # against the phases, which sum the partials and m V in launches of their own
+    a, b = ctx_for(w, **kw), ctx_for(w, **kw)
+    a.step(w.dt, 3)
+    h = 0.5 * w.dt
+    for _ in range(3):
+        b.kick(h)
+        b.sun_drift(h)
+        b.drift(w.dt)
+        b.encounters()
+        b.sun_drift(h)
+        b.force()
+        b.kick(h)
+    for p, q in zip(a.download(nb.NB_DH), b.download(nb.NB_DH)):
+        assert np.max(np.abs(p - q)) <= 1e-14 * np.max(np.abs(p))
+
+
+def test_many_systems():
+    # more workgroups than the launches sum partials in with several threads a body
+    _check(workloads.batch([560] * 300), mode=1, step_algo=1, force_algo=2)
 
 
 @pytest.mark.parametrize("w", [workloads.batch([900, 1, 0, 300, 2100]), workloads.bigsmall(40, 3000, m_big=1e-5, a_lo=0.95, a_hi=1.05)],
