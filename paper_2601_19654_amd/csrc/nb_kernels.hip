@@ -1297,18 +1297,38 @@ __global__ __launch_bounds__(kBlock) void k_force32c(const FWork *__restrict__ w
         atomicAdd((unsigned long long *)&stats->near_pairs, (unsigned long long)near);
 }
 
-// Few sources (every system has at most kFewMax big bodies, one split): each
-// wave owns the 64 R targets of a work item and sums over all of the system's
-// sources, held in the wave's own LDS slice; waves stride over the items and
-// restage the sources only when the system changes.  Same pair arithmetic and
-// per-target source order as the kernels above, no cross-wave reduction.
-constexpr int kFewMax = 256;
-
+// Few sources (every system's big bodies in one split): each wave owns the 64 R
+// targets of a work item and sums over all of the system's sources.  These are the
+// same for every lane and are read through the scalar cache, a few ahead: no staging,
+// no LDS, so that registers alone bound the waves per SIMD.  Same pair arithmetic and
+// per-target source order as the kernels above, no cross-wave reduction.  Bound by the
+// pair arithmetic (about 100 cycles per wave and source in FP64).  100 big bodies and
+// 1048576 small ones, one target a lane: with the sources in each wave's LDS 101 us
+// (FP64) and 104 us (FP32C), now 83 and 71 us.
 __device__ __forceinline__ void wave_lds_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The workgroup's changeover pairs to the counter: one atomic per workgroup, as those
+// of the whole grid on one counter take turns (11 ns each).
+__device__ __forceinline__ void add_near(int near, DevStats *stats)
+{
+    __shared__ int cnt[kWaves];
+    for (int o = 32; o > 0; o >>= 1)
+        near += __shfl_xor(near, o);
+    if ((threadIdx.x & 63) == 0)
+        cnt[threadIdx.x >> 6] = near;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int t = 0;
+        for (int w = 0; w < kWaves; ++w)
+            t += cnt[w];
+        if (t)
+            atomicAdd((unsigned long long *)&stats->near_pairs, (unsigned long long)t);
+    }
 }
 
 template <int R>
@@ -1322,22 +1342,10 @@ __global__ __launch_bounds__(kBlock) void k_force64_few(const FWork *__restrict_
                                                         double *__restrict__ fpart, int ntot, int maxs,
                                                         double inner, DevStats *stats)
 {
-    __shared__ double4 sj[kWaves][kFewMax];
-    __shared__ double2 sx[kWaves][kFewMax];     // {1.5 m, rc}
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int cached = -1, near = 0;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int near = 0;
     for (int it = blockIdx.x * kWaves + wv; it < nfw; it += gridDim.x * kWaves) {
         const FWork wk = work[it];
-        if (wk.j0 != cached) {
-            for (int k = lane; k < wk.nj; k += 64) {
-                const int j = wk.j0 + k;
-                const double mj = m[j];
-                sj[wv][k] = make_double4(qx[j], qy[j], qz[j], mj);
-                sx[wv][k] = make_double2(1.5 * mj, rc[j]);
-            }
-            cached = wk.j0;
-            wave_lds_sync();
-        }
         double xi[R], yi[R], zi[R], rci[R], r2i[R], thr[R], ax[R], ay[R], az[R];
         const double tmax = tile_rc2[wk.rb0];
 #pragma unroll
@@ -1352,19 +1360,20 @@ __global__ __launch_bounds__(kBlock) void k_force64_few(const FWork *__restrict_
             thr[k] = fmax(r2i[k], tmax);
             ax[k] = ay[k] = az[k] = 0.0;
         }
-#pragma unroll 2
+#pragma unroll 4
         for (int jj = 0; jj < wk.nj; ++jj) {
-            const double4 J = sj[wv][jj];
-            const double m15 = sx[wv][jj].x;
+            const int j = wk.j0 + jj;
+            const double Jx = qx[j], Jy = qy[j], Jz = qz[j], mj = m[j];
+            const double m15 = 1.5 * mj;
 #pragma unroll
             for (int k = 0; k < R; ++k) {
-                double dx = J.x - xi[k], dy = J.y - yi[k], dz = J.z - zi[k];
+                double dx = Jx - xi[k], dy = Jy - yi[k], dz = Jz - zi[k];
                 double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-                double s = m_rinv3(J.w, m15, r2);
+                double s = m_rinv3(mj, m15, r2);
                 if (r2 < thr[k]) {
-                    double rcj = sx[wv][jj].y;
+                    double rcj = rc[j];
                     if (r2 < fmax(r2i[k], fmax(rcj * rcj, DBL_MIN))) {
-                        s = J.w * changeover_w(r2, fmax(rci[k], rcj), inner);
+                        s = mj * changeover_w(r2, fmax(rci[k], rcj), inner);
                         ++near;
                     }
                 }
@@ -1384,10 +1393,7 @@ __global__ __launch_bounds__(kBlock) void k_force64_few(const FWork *__restrict_
             }
         }
     }
-    for (int o = 32; o > 0; o >>= 1)
-        near += __shfl_xor(near, o);
-    if (lane == 0 && near)
-        atomicAdd((unsigned long long *)&stats->near_pairs, (unsigned long long)near);
+    add_near(near, stats);
 }
 
 template <int R>
@@ -1402,20 +1408,10 @@ __global__ __launch_bounds__(kBlock) void k_force32c_few(const FWork *__restrict
                                                          float *__restrict__ fpart, int ntot,
                                                          int maxs, double inner, DevStats *stats)
 {
-    __shared__ float4 sa[kWaves][kFewMax];
-    __shared__ float4 sb[kWaves][kFewMax];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int cached = -1, near = 0;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int near = 0;
     for (int it = blockIdx.x * kWaves + wv; it < nfw; it += gridDim.x * kWaves) {
         const FWork wk = work[it];
-        if (wk.j0 != cached) {
-            for (int k = lane; k < wk.nj; k += 64) {
-                sa[wv][k] = pk[2 * (size_t)(wk.j0 + k)];
-                sb[wv][k] = pk[2 * (size_t)(wk.j0 + k) + 1];
-            }
-            cached = wk.j0;
-            wave_lds_sync();
-        }
         float xh[R], yh[R], zh[R], xl[R], yl[R], zl[R], r2i[R], thr[R];
         float hx[R], hy[R], hz[R], lx[R], ly[R], lz[R], tx[R], ty[R], tz[R];
         double nx[R], ny[R], nz[R];
@@ -1436,10 +1432,10 @@ __global__ __launch_bounds__(kBlock) void k_force32c_few(const FWork *__restrict
         }
         for (int jb = 0; jb < wk.nj; jb += kMerge) {
             const int jm = min(wk.nj, jb + kMerge);
-#pragma unroll 2
+#pragma unroll 4
             for (int jj = jb; jj < jm; ++jj) {
-                const float4 A = sa[wv][jj];
-                const float4 B = sb[wv][jj];
+                const float4 A = pk[2 * (size_t)(wk.j0 + jj)];
+                const float4 B = pk[2 * (size_t)(wk.j0 + jj) + 1];
 #pragma unroll
                 for (int k = 0; k < R; ++k) {
                     float dx = (A.x - xh[k]) + (B.x - xl[k]);
@@ -1485,10 +1481,7 @@ __global__ __launch_bounds__(kBlock) void k_force32c_few(const FWork *__restrict
             }
         }
     }
-    for (int o = 32; o > 0; o >>= 1)
-        near += __shfl_xor(near, o);
-    if (lane == 0 && near)
-        atomicAdd((unsigned long long *)&stats->near_pairs, (unsigned long long)near);
+    add_near(near, stats);
 }
 
 // Symmetric pairs (every body big): each unordered pair is evaluated once and
@@ -5135,8 +5128,8 @@ hipError_t launch_force(const Dev &d, const Params &p, hipStream_t s)
         return hipGetLastError();
     }
     if (d.force_few) {
-        // waves stride over the items; about 8 workgroups per CU
-        const int grid = std::min(cdiv(d.nfw, kWaves), 2048);
+        // one item a wave
+        const int grid = std::min(cdiv(d.nfw, kWaves), 1 << 22);
 #define NB_FEW_ARGS d.fwork, d.nfw, d.qx, d.qy, d.qz, d.m, d.rc, d.tile_rc2, d.fpart, d.ntot, d.maxs, \
                     p.inner, d.stats
 #define NB_FEW32_ARGS d.fwork, d.nfw, d.pk, d.qx, d.qy, d.qz, d.m, d.rc, d.tile_rc2, d.fpart32, d.ntot, \

@@ -280,10 +280,11 @@ constexpr long long kFewTiles = 1024;
 
 // Automatic targets per lane: the symmetric force by its tile pairs (kSymR1Items);
 // the ordered one (some bodies small, or asked for) two from 512 tiles of 128
-// targets on, in FP32C only up to 1024, where the few-source kernels begin: 128 big
-// bodies and 30000 small ones 37 / 44 us a step with one / two targets (FP32C),
-// 100000 small ones 71 / 56 us (FP32C) and 56 / 52 us (FP64), 300000 small ones 119
-// / 127 us (FP32C), their force alone 48 / 41 us (FP64).
+// targets up to 1024, where the few-source kernels begin, which hold the sources in
+// scalar registers and take one: 128 big bodies and 30000 small ones 37 / 44 us a step
+// with one / two targets (FP32C), 100000 small ones 71 / 56 us (FP32C) and 56 / 52 us
+// (FP64); the force alone, 100 big bodies and 1048576 small ones 83 / 87 us (FP64) and
+// 71 / 78 us (FP32C), 20 and 300000 10.0 / 10.0 and 10.3 / 10.6 us.
 void auto_force_r(Params &p, int nsys, const int32_t *off, const int32_t *nbig)
 {
     if (!p.r_auto)
@@ -295,7 +296,7 @@ void auto_force_r(Params &p, int nsys, const int32_t *off, const int32_t *nbig)
     long long tiles = 0;
     for (int s = 0; s < nsys; ++s)
         tiles += (off[s + 1] - off[s] + 127) / 128;
-    p.force_r = tiles < 512 || (p.mode == NB_FP32C && tiles >= kFewTiles) ? 1 : 2;
+    p.force_r = tiles < 512 || tiles >= kFewTiles ? 1 : 2;
 }
 
 // The force pass with the encounter test in it holds four targets per lane only
