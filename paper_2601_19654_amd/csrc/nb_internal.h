@@ -277,6 +277,9 @@ struct Params {
                           // systems of at most kBlock big bodies
     int r_auto;           // 1: the caller left force_r to the library (resolved at creation)
     int enc_auto;         // 1: the caller left enc_algo to the library
+    int enc_keep, alone_keep;   // the automatic choice (and whether the direct check's
+                          // records are there beside the sorted check) kept over a
+                          // compaction; 0: none kept
     int step_algo;        // 1: per-phase launches, 2: persistent per-system launch, 3: the
                           // persistent launch of small systems (an automatic choice)
     int force_algo;       // 0 automatic, 1 ordered pairs, 2 symmetric tile pairs, 4 symmetric

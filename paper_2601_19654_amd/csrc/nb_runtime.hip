@@ -315,6 +315,8 @@ int choose_enc_algo(const Params &p, int nsys, const int32_t *off, const int32_t
         return p.mode == NB_FP32C && !p.resolve && !has_small(nsys, off, nbig) ? 4 : 2;
     if (p.enc_algo >= 1 && p.enc_algo <= 3)
         return p.enc_algo;
+    if (p.enc_keep)
+        return p.enc_keep;
     // small bodies and at most kBlock big bodies per system: every body against
     // the big bodies of its system
     if (has_small(nsys, off, nbig) && max_big(nsys, off, nbig) <= kBlock)
@@ -513,7 +515,7 @@ void build_tables(const Params &p, int nsys, const int32_t *off, const int32_t *
     // the fused pass is the symmetric force's: without it, the sorted check alone
     t.enc_fused = t.enc_fused && t.force_sym;
     t.enc_alone = t.enc_sorted && !t.enc_fused && p.enc_auto &&
-                  max_pairs(nsys, off, nbig) <= kEncAlonePairs;
+                  (p.enc_keep ? p.alone_keep : max_pairs(nsys, off, nbig) <= kEncAlonePairs);
     const bool direct = !t.enc_sorted || t.enc_alone;
     // 4: the symmetric FP32C force over the radial order (not with the fused
     // pass, which runs over the encounter check's order)
@@ -665,7 +667,7 @@ constexpr long long kSnapSetBytes = 1ll << 30;
 // and the further sets fit in kSnapSetBytes; else two.
 int snap_sets(const Params &p, const Tables &t, int ntot)
 {
-    const long long per = (long long)ntot * (13 * sizeof(double) + (t.enc_sorted ? 0 : kEncRecBytes));
+    const long long per = (long long)ntot * (13 * sizeof(double) + 2 * sizeof(double4));
     if (p.resolve || p.step_algo == 2 || t.enc_fused || per * (kSnapSets - 1) > kSnapSetBytes)
         return 2;
     return kSnapSets;
@@ -1266,7 +1268,23 @@ int setup_layout(nb_ctx *c, int nsys, const int32_t *off, const int32_t *nbig)
     Tables t;
     build_tables(c->p, nsys, off, nbig, t);
     Dev d{};
-    const size_t need = carve(c->p, nsys, off[nsys], c->enc_cap, t, nullptr, d);
+    size_t need = carve(c->p, nsys, off[nsys], c->enc_cap, t, nullptr, d);
+    if (c->ws_bytes < need && c->ntot > 0 && c->p.enc_auto) {
+        // fewer bodies than before, past a line between the encounter checks, whose other
+        // side takes more of the workspace (eight sets of the direct check's records):
+        // the check the context has had
+        Params q = c->p;
+        q.enc_keep = c->d.enc_sorted ? 2 : 1;
+        q.alone_keep = c->d.eq_alone != nullptr;
+        Tables u;
+        build_tables(q, nsys, off, nbig, u);
+        const size_t kept = carve(q, nsys, off[nsys], c->enc_cap, u, nullptr, d);
+        if (kept <= c->ws_bytes) {
+            c->p = q;
+            t = std::move(u);
+            need = kept;
+        }
+    }
     if (c->ws_bytes < need)
         return set_err(c, NB_E_WORKSPACE, "workspace of %zu bytes, %zu needed", c->ws_bytes, need);
     drop_graph(c);

@@ -69,3 +69,29 @@ def test_alone_and_beside_the_step():
     (ea, _), (eb, _) = _list(w, 0, True), _list(w, 1, True)
     assert ea.nce == eb.nce > 0
     assert np.array_equal(ea.ice, eb.ice) and np.array_equal(ea.jce, eb.jce) and np.array_equal(ea.ce, eb.ce)
+
+
+@pytest.mark.parametrize("n,lost", [(10030, 60), (10200, 700), (41000, 300)])
+def test_compaction_past_the_line(n, lost):
+    """A compaction takes a context past the line between the checks: it still fits the
+    workspace it was created with, and its next list is a fresh context's."""
+    from paper_2601_19654_amd import nb
+    w = workloads.ring(n, m=1e-9)
+    w.x[:lost] *= 100.0
+    w.v[:lost] *= 3.0          # unbound, beyond the ejection radius
+    c = ctx_for(w, step_algo=1)
+    c.step(w.dt, 1)
+    cnt, _ = c.events(1e12, 0.0, 50.0)
+    assert cnt["ejected"] == lost
+    idx = c.compact()
+    assert len(idx) <= n - lost and c.ntot == len(idx)
+    x, v = c.download(nb.NB_DH)
+    c.step(w.dt, 1)
+    e = c.last_encounters()
+    f = nb.Context(c.off, nb.default_params(G=w.G, step_algo=1), enc_cap=1 << 16, device="cuda:0")
+    f.upload(w.m0, w.m[idx], x, v, frame=nb.NB_DH)
+    f.step(w.dt, 1)
+    g = f.last_encounters()
+    assert e.nce == g.nce and np.array_equal(e.ice, g.ice) and np.array_equal(e.jce, g.jce)
+    c.close()
+    f.close()
