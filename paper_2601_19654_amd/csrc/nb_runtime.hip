@@ -236,17 +236,19 @@ int choose_step_algo(const Params &p, int nsys, const int32_t *off, const int32_
 
 // Encounter algorithm: explicit choice, else the direct check up to
 // kEncDirectPairs pairs with a big member in the largest system, and the sorted
-// check above.  Beside the step on the second queue (whole steps, direct against
-// sorted): 1500 bodies 46 / 50 us, 8000 bodies 67 / 72 us, 12000 bodies 112 / 106
-// us, 16384 bodies 165 / 156 us: once the force pass fills the chip, the sorted
-// check's small kernels run in its gaps, while the direct check's matrix products
-// (all pairs) take their time from it.  The line lies at the pairs of 10000
-// bodies.  Where nothing runs beside it (the full method, and nb_drift with
+// check above.  Beside the step on the second queue (a step of a long run, direct
+// against sorted): 6000 bodies 51 / 59 us (FP64) and 45 / 60 us (FP32C), 9000 bodies
+// 74 / 71 and 64 / 64 us, 12000 bodies 105 / 100 and 87 / 81 us, 20000 bodies 232 / 235
+// and 172 / 176 us, 40000 bodies 784 / 760 and 557 / 546 us: once the force pass fills
+// the chip, the sorted check's small kernels run in its gaps, while the direct check's
+// matrix products (all pairs) take their time from it.  The line lies at the pairs of
+// 10000 bodies; between 18000 and 26000 bodies the direct check is 1-3 % better again,
+// which is left.  Where nothing runs beside it (the full method, and nb_drift with
 // nb_encounters, which take the direct check then also in a context whose steps
-// run the sorted one) it pays further: one check alone, direct against sorted,
-// 16384 bodies 17 / 50 us (0.5-5 AU disk) and 43 / 77 us (dense 0.9-1.1 AU ring),
-// 32768 bodies 41 / 72 and 142 / 147 us, 65536 bodies 142 / 125 and 488 / 311 us:
-// up to the pairs of 40960 bodies.
+// run the sorted one) it pays further: one check alone, direct against sorted, 16384
+// bodies 18 / 53 us (0.5-5 AU disk) and 19 / 51 us (dense 0.9-1.1 AU ring), 32768
+// bodies 40 / 73 and 47 / 83 us, 65536 bodies 128 / 125 and 153 / 131 us: up to the
+// pairs of 40960 bodies.
 constexpr long long kEncDirectPairs = 10000ll * 9999 / 2;
 constexpr long long kEncAlonePairs = 40960ll * 40959 / 2;
 
