@@ -863,7 +863,7 @@ __device__ __forceinline__ void enc_record(double mx, double my, double mz, doub
 // A step with the finalize apart / folded in: 300 bodies 29.8 / 27.5 us, 16 systems
 // of 500 bodies 35.7 / 30.7, 3001 bodies (47 slots) 37.1 / 37.5, 5000 bodies (79
 // slots) 47 / 50: hence kFinDriftSlots.
-template <typename FP, int NSL>
+template <typename FP, int NSL, bool ISO>
 __global__ __launch_bounds__(kBlock * (NSL ? NSL : 1)) void k_drift(const RBlk *__restrict__ rblk, const double *__restrict__ m0, double G,
                         double dt, const double *__restrict__ m, double *qx, double *qy,
                         double *qz, double *vx, double *vy, double *vz, double *__restrict__ q0x,
@@ -940,13 +940,15 @@ __global__ __launch_bounds__(kBlock * (NSL ? NSL : 1)) void k_drift(const RBlk *
         v0x[i] = u;
         v0y[i] = v;
         v0z[i] = w;
-        // the solver apart from the code around it: the forms of this launch give the
-        // same bits, whatever else they compute
-        for (double *a : {&x, &y, &z, &u, &v, &w, &mu})
-            opaque(*a);
+        // ISO (all but the full method, whose steps use one form of this launch): the solver
+        // apart from the code around it, so that the forms give the same bits
+        if constexpr (ISO)
+            for (double *a : {&x, &y, &z, &u, &v, &w, &mu})
+                opaque(*a);
         fail = kepler_drift(mu, dt, x, y, z, u, v, w) != 0;
-        for (double *a : {&x, &y, &z, &u, &v, &w})
-            opaque(*a);
+        if constexpr (ISO)
+            for (double *a : {&x, &y, &z, &u, &v, &w})
+                opaque(*a);
         // Encounter data of this body over the step: chord c = Q1 - Q0 and midpoint M
         {
             const double c[3] = {x - sx, y - sy, z - sz};
@@ -5031,8 +5033,8 @@ hipError_t launch_drift(const Dev &d, const Params &p, double dt, double sun_h,
     if (pre)
         k_sys_total<<<d.nsys, kBlock, 0, s>>>(d.rb_first, d.rb_count, part_in, d.ptot);
     const int nsl = fin ? fin_slices(d.maxs, 4) : 0;
-#define NB_DRIFT(FP_, NSL_, PART_)                                                                \
-    k_drift<FP_, NSL_><<<d.nrb, kBlock * (NSL_ ? NSL_ : 1), 0, s>>>(                              \
+#define NB_DRIFT(FP_, NSL_, ISO_, PART_)                                                          \
+    k_drift<FP_, NSL_, ISO_><<<d.nrb, kBlock * (NSL_ ? NSL_ : 1), 0, s>>>(                              \
         d.rblk, d.m0, p.G, dt, d.m, d.qx, d.qy, d.qz, d.vx, d.vy, d.vz, d.q0x, d.q0y, d.q0z,      \
         d.v0x, d.v0y, d.v0z, d.kflag, d.stats, d.rpart_drift(), d.rc,                             \
         d.enc_sorted ? d.lnr_part : nullptr, d.q1x, d.q1y, d.q1z, d.v1x, d.v1y, d.v1z, d.rc1,     \
@@ -5041,12 +5043,14 @@ hipError_t launch_drift(const Dev &d, const Params &p, double dt, double sun_h,
 #define NB_DRIFT_FIN(NSL_)                                                                        \
     do {                                                                                          \
         if (d.fpart32)                                                                            \
-            NB_DRIFT(float, NSL_, d.fpart32);                                                     \
+            NB_DRIFT(float, NSL_, true, d.fpart32);                                                     \
         else                                                                                      \
-            NB_DRIFT(double, NSL_, d.fpart);                                                      \
+            NB_DRIFT(double, NSL_, true, d.fpart);                                                      \
     } while (0)
-    if (nsl == 0)
-        NB_DRIFT(double, 0, nullptr);
+    if (nsl == 0 && p.resolve)
+        NB_DRIFT(double, 0, false, nullptr);
+    else if (nsl == 0)
+        NB_DRIFT(double, 0, true, nullptr);
     else if (nsl == 1)
         NB_DRIFT_FIN(1);
     else if (nsl == 2)
