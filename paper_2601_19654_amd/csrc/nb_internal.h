@@ -140,7 +140,7 @@ struct Dev {
     double4 *mr;          // persistent steps, per body: chord midpoint (x,y,z) and encounter reach R
     void *eq;             // direct check, per body after a drift: three records of 8 halves (else null)
     void *eq_alone;       // sorted check in steps, direct check elsewhere: set 0's records (else null)
-    double *scale2;       // nsys: largest |Q|^2 at the upload (the records' unit)
+    unsigned long long *scale;   // nsys: exponents of |Q|^2 at the upload (the records' unit)
     int *kflag, *ce, *sys_of;
     double *m0;           // nsys
     int *off;             // nsys+1

@@ -174,12 +174,12 @@ __global__ void k_validate(int ntot, int nsys, const double *__restrict__ m0,
                            const double *__restrict__ m, const double *__restrict__ x,
                            const double *__restrict__ v, const int *__restrict__ sys_of,
                            const int *__restrict__ off, const int *__restrict__ nbig, int *flag,
-                           double *__restrict__ scale2)
+                           unsigned long long *__restrict__ scale)
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     int bad = 0;
     if (i < nsys)
-        scale2[i] = 0.0;
+        scale[i] = 0ull;
     if (i < ntot) {
         double mi = m[i];
         bad = (!isfinite(mi) || mi < 0.0) ? 1 : 0;
@@ -217,20 +217,26 @@ __global__ void k_partial_mv(const RBlk *__restrict__ rblk, const double *__rest
             part[(size_t)blockIdx.x * 4 + w] = v[w];
 }
 
+// Blocks of a system whose bodies set its unit of length (enc_inv_scale): a wave of each
+// adds the sum of its bodies' exponents, shifted by kScaleShift, and their number.
+constexpr int kScaleBlocks = 16, kScaleShift = 20;
+static_assert(kScaleBlocks * kBlock < 1 << kScaleShift, "the number stays below the sum");
+
 // Heliocentric -> DH: Q = x, V = v - sum m v / (m0 + sum m); or a plain copy.
 __global__ void k_to_dh(const RBlk *__restrict__ rblk, const int *__restrict__ rb_first,
                         const int *__restrict__ rb_count, const double *__restrict__ m0,
                         const double *__restrict__ part, int ntot, const double *__restrict__ x,
                         const double *__restrict__ v, int helio, double *qx, double *qy,
                         double *qz, double *vx, double *vy, double *vz,
-                        double *__restrict__ scale2)
+                        unsigned long long *__restrict__ scale)
 {
-    // scale2: also the largest |Q|^2 of every system (cleared before; non-negative
-    // doubles order like their bits)
+    // scale: also the binary exponents of |Q|^2 of every system's bodies, summed over
+    // up to kScaleBlocks of its blocks (cleared before; whole numbers, so that the sum
+    // does not depend on the order): enc_inv_scale
     __shared__ double sh[4 * kBlock];
     RBlk b = rblk[blockIdx.x];
     double c[3] = {0.0, 0.0, 0.0};
-    double r2 = 0.0;
+    int e = 0, cnt = 0;
     if (helio) {
         double P[4];
         system_sum<4>(part, 4, rb_first[b.sys], rb_count[b.sys], P, sh);
@@ -248,19 +254,21 @@ __global__ void k_to_dh(const RBlk *__restrict__ rblk, const int *__restrict__ r
         vx[i] = v[i] - c[0];
         vy[i] = v[(size_t)ntot + i] - c[1];
         vz[i] = v[(size_t)2 * ntot + i] - c[2];
-        r2 = x0 * x0 + x1 * x1 + x2 * x2;
+        const double r2 = x0 * x0 + x1 * x1 + x2 * x2;
+        if (r2 > 0.0 && isfinite(r2)) {
+            e = ilogb(r2);
+            cnt = 1;
+        }
     }
-    r2 = wave_max(r2);
-    if ((threadIdx.x & 63) == 0)
-        sh[threadIdx.x >> 6] = r2;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kBlock / 64; ++w)
-            r2 = fmax(r2, sh[w]);
-        // (a block below the largest so far leaves it alone)
-        if (r2 > __hip_atomic_load(&scale2[b.sys], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            atomicMax((unsigned long long *)&scale2[b.sys], (unsigned long long)__double_as_longlong(r2));
+    const int nb = rb_count[b.sys], stride = (nb + kScaleBlocks - 1) / kScaleBlocks;
+    if (((int)blockIdx.x - rb_first[b.sys]) % stride)
+        return;
+    for (int o = 32; o > 0; o >>= 1) {
+        e += __shfl_xor(e, o);
+        cnt += __shfl_xor(cnt, o);
     }
+    if ((threadIdx.x & 63) == 0 && cnt)
+        atomicAdd(&scale[b.sys], ((unsigned long long)(long long)e << kScaleShift) + (unsigned long long)cnt);
 }
 
 // DH -> heliocentric (v = V + P/m0) or DH copy, into plane-major x, v.
@@ -787,22 +795,33 @@ __device__ __forceinline__ double enc_deviation(double dt, const double (&v0)[3]
 // add up to at most 2 (nn_i + nn_j)): splitting 2^-21 (nn_i + nn_j), the products left
 // out 2^-22 (nn_i + nn_j), summing 32 terms (measured: 2^-21 of their magnitudes) 2^-20
 // (nn_i + nn_j), FP16 values below 2^-14 in steps of 2^-24: 2^-22 (sqrt nn_i + sqrt
-// nn_j) and 2^-31.  The shares below are at least four times that.  A body outside 8 L
-// (or not finite) gets a record that makes a candidate of each of its pairs.
+// nn_j) and 2^-31.  The shares below are at least four times that.
+// The shares grow with L, so L is a typical distance, not the largest (enc_inv_scale),
+// and a midpoint outside the ball of kEncBall L is moved to the ball's nearest point:
+// the projection onto a convex set brings no two points further apart, so D only
+// shrinks, and a body far out stays a candidate only of those near its direction at the
+// ball's edge (and of those its own s reaches).  One body at 65000 AU beside 9990 at 1-3 AU: 602 us a check
+// with the largest distance as L, 16 us now (13 us without it).  A body whose chord,
+// deviation or s is outside 8 L (or not finite) gets a record that makes a candidate of
+// each of its pairs.
 constexpr double kEncK1 = 0x1p-17, kEncK2 = 0x1p-20, kEncK3 = 0x1p-28;
 constexpr double kEncMax = 8.0;                 // largest component of u / L
+constexpr double kEncBall = 7.5;                // largest |M| / L
 constexpr double kEncAlUnit = 64.0;             // al is stored times this ...
-constexpr double kEncAlOut = -60000.0;          // ... and this for a body outside 8 L
+constexpr double kEncAlOut = -60000.0;          // ... and this for a candidate of every pair
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-// 1/L of a system from the largest |Q|^2 of its bodies at the upload: L the power
-// of two at or above |Q| (1 when there is none).
-__device__ __forceinline__ double enc_inv_scale(double r2)
+// 1/L of a system from the exponents of |Q|^2 of its bodies at the upload (k_to_dh): L
+// about the power of two above the geometric mean of |Q| (1 when there is none).
+__device__ __forceinline__ double enc_inv_scale(unsigned long long v)
 {
-    if (!(r2 > 0.0) || !isfinite(r2))
+    const int cnt = (int)(v & ((1ull << kScaleShift) - 1ull));
+    if (cnt == 0)
         return 1.0;
-    return ldexp(1.0, -(ilogb(r2) / 2 + 1));
+    const int sum = (int)((long long)v >> kScaleShift);
+    const int e = (sum - (sum < 0 ? cnt - 1 : 0)) / cnt;      // the mean, rounded down
+    return ldexp(1.0, -((e >> 1) + 1));
 }
 
 // The record of a body: (M_hi, c_hi, s', al_hi), (M_lo, c_lo, al_lo, 0), (d', 1/unit,
@@ -812,9 +831,16 @@ __device__ __forceinline__ void enc_record(double mx, double my, double mz, doub
                                            double cz, const double (&d)[3], double s, double inv_l,
                                            v8h *out)
 {
-    const double u[6] = {mx * inv_l, my * inv_l, mz * inv_l, cx * inv_l, cy * inv_l, cz * inv_l};
+    double u[6] = {mx * inv_l, my * inv_l, mz * inv_l, cx * inv_l, cy * inv_l, cz * inv_l};
     v8h A, B, D;
-    bool in = true;
+    const double R2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+    bool in = R2 <= DBL_MAX;
+    if (R2 > kEncBall * kEncBall) {
+        const double f = kEncBall / sqrt(R2);
+        u[0] *= f;
+        u[1] *= f;
+        u[2] *= f;
+    }
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
         in = in && fabs(u[k]) <= kEncMax;
@@ -878,7 +904,7 @@ __global__ __launch_bounds__(kBlock * (NSL ? NSL : 1)) void k_drift(const RBlk *
                         double *__restrict__ rc1, const double *__restrict__ part_in,
                         double sun_h, const int *__restrict__ rb_first,
                         const int *__restrict__ rb_count, const double *__restrict__ ptot,
-                        v8h *__restrict__ eq, const double *__restrict__ scale2,
+                        v8h *__restrict__ eq, const unsigned long long *__restrict__ scale,
                         int *__restrict__ nce, const FP *__restrict__ fpart, int ntot, int maxs,
                         const int *__restrict__ nsplit, double kick_h)
 {
@@ -959,7 +985,7 @@ __global__ __launch_bounds__(kBlock * (NSL ? NSL : 1)) void k_drift(const RBlk *
                 const double p = enc_deviation(dt, e0, e1, c, d);
                 // 2^-45 (|M| + |c|): the rounding of midpoint, chord and deviations
                 const double s = 0.75 * p + rci + 0x1p-45 * (norm1(mx, my, mz) + norm1(c[0], c[1], c[2]));
-                enc_record(mx, my, mz, c[0], c[1], c[2], d, s, enc_inv_scale(scale2[b.sys]),
+                enc_record(mx, my, mz, c[0], c[1], c[2], d, s, enc_inv_scale(scale[b.sys]),
                            eq + kEncRec * (size_t)i);
             } else {
                 const double lnr = log(fmax(sqrt(mx * mx + my * my), 1e-300));
@@ -4183,7 +4209,7 @@ struct SmallArgs {
     double *qx, *qy, *qz, *vx, *vy, *vz, *ax, *ay, *az, *rc;
     double *q0x, *q0y, *q0z, *v0x, *v0y, *v0z, *q1x, *q1y, *q1z, *v1x, *v1y, *v1z, *rc1;
     v8h *eq;
-    const double *scale2;
+    const unsigned long long *scale;
     int *kflag, *ce;
     unsigned long long *keys;
     int cap;
@@ -4215,7 +4241,7 @@ __global__ __launch_bounds__(NT) void k_steps_small(SmallArgs A)
     double x = A.qx[i], y = A.qy[i], z = A.qz[i], u = A.vx[i], v = A.vy[i], w = A.vz[i];
     double ax = A.ax[i], ay = A.ay[i], az = A.az[i], rc = A.rc[i];
     const double mi = on ? A.m[i] : 0.0;
-    const double hill = cbrt(mi / (3.0 * mm)), inv_l = enc_inv_scale(A.scale2[S.sys]);
+    const double hill = cbrt(mi / (3.0 * mm)), inv_l = enc_inv_scale(A.scale[S.sys]);
     const bool big = t < nb;
     double P[3] = {0.0, 0.0, 0.0};
     for (int b = 0; b < A.rb_count[S.sys]; ++b)
@@ -4919,7 +4945,7 @@ hipError_t launch_validate(const Dev &d, const double *m0, const double *m, cons
 {
     int n = d.ntot > d.nsys ? d.ntot : d.nsys;
     k_validate<<<cdiv(n, kBlock), kBlock, 0, s>>>(d.ntot, d.nsys, m0, m, x, v, d.sys_of, d.off,
-                                                   d.nbig, d.flag, d.scale2);
+                                                   d.nbig, d.flag, d.scale);
     return hipGetLastError();
 }
 
@@ -4932,7 +4958,7 @@ hipError_t launch_to_dh(const Dev &d, const double *x, const double *v, int fram
         k_partial_mv<<<d.nrb, kBlock, 0, s>>>(d.rblk, d.m, v, v + d.ntot, v + 2 * (size_t)d.ntot,
                                                d.rpart);
     k_to_dh<<<d.nrb, kBlock, 0, s>>>(d.rblk, d.rb_first, d.rb_count, d.m0, d.rpart, d.ntot, x, v,
-                                      helio, d.qx, d.qy, d.qz, d.vx, d.vy, d.vz, d.scale2);
+                                      helio, d.qx, d.qy, d.qz, d.vx, d.vy, d.vz, d.scale);
     return hipGetLastError();
 }
 
@@ -5038,7 +5064,7 @@ hipError_t launch_drift(const Dev &d, const Params &p, double dt, double sun_h,
         d.rblk, d.m0, p.G, dt, d.m, d.qx, d.qy, d.qz, d.vx, d.vy, d.vz, d.q0x, d.q0y, d.q0z,      \
         d.v0x, d.v0y, d.v0z, d.kflag, d.stats, d.rpart_drift(), d.rc,                             \
         d.enc_sorted ? d.lnr_part : nullptr, d.q1x, d.q1y, d.q1z, d.v1x, d.v1y, d.v1z, d.rc1,     \
-        part_in, sun_h, d.rb_first, d.rb_count, pre ? d.ptot : nullptr, (v8h *)d.eq, d.scale2,    \
+        part_in, sun_h, d.rb_first, d.rb_count, pre ? d.ptot : nullptr, (v8h *)d.eq, d.scale,    \
         d.nce, PART_, d.ntot, d.maxs, d.nsplit, 0.5 * dt)
 #define NB_DRIFT_FIN(NSL_)                                                                        \
     do {                                                                                          \
@@ -5378,7 +5404,7 @@ hipError_t launch_small_steps(const Dev &d, const Params &p, double dt, int nste
     const SmallArgs A{d.psys, nsteps, p.drag, p.mode == 1, d.force_sym, dt, p.G, p.n_hill, p.inner,
                       drag_params(p), d.m0, d.m, d.qx, d.qy, d.qz, d.vx, d.vy, d.vz, d.ax, d.ay,
                       d.az, d.rc, d.q0x, d.q0y, d.q0z, d.v0x, d.v0y, d.v0z, d.q1x, d.q1y, d.q1z,
-                      d.v1x, d.v1y, d.v1z, d.rc1, (v8h *)d.eq, d.scale2, d.kflag, d.ce, d.keys,
+                      d.v1x, d.v1y, d.v1z, d.rc1, (v8h *)d.eq, d.scale, d.kflag, d.ce, d.keys,
                       d.enc_cap, d.stats, d.step_nce, d.rpart_prev(), d.rb_first, d.rb_count};
     // 512 threads keep the whole state in registers; above 128 bodies the pair phase
     // is longer than what the 1024 threads' spills cost (100 bodies 8.8 / 11.4 us a

@@ -696,7 +696,7 @@ size_t carve(const Params &p, int nsys, int ntot, int enc_cap, const Tables &t, 
     const size_t eq_all = (size_t)ntot * kEncRecBytes, eq_bytes = t.enc_sorted ? 0 : eq_all;
     d.eq = eq_bytes ? take(eq_bytes) : nullptr;
     d.eq_alone = t.enc_alone ? take(eq_all) : nullptr;
-    d.scale2 = (double *)take((size_t)nsys * sizeof(double));
+    d.scale = (unsigned long long *)take((size_t)nsys * sizeof(unsigned long long));
     // further sets of drift outputs: one per step of a captured run when the
     // check runs on a second queue and the sets stay within kSnapSetBytes, else two
     d.nsnap = snap_sets(p, t, ntot);
