@@ -10,6 +10,7 @@ namespace nb {
 constexpr int kBlock = 256;      // threads of every O(N) kernel and of the pair kernels
 constexpr int kSmallMax = 256;   // most bodies of a system stepped by k_steps_small
 constexpr int kEncTargets = 128; // targets per pair item of the direct encounter check
+constexpr int kEncSources = 1024;   // most sources of one (64 groups of 16)
 constexpr int kEncRecBytes = 48; // direct check: record of a body
 constexpr int kDiagJ = 256;      // sources per pair item of the diagnostics
 constexpr int kScanChunkCells = 1024;   // cells per block of the counting sort's scan

@@ -2911,6 +2911,54 @@ __device__ __forceinline__ HRec enc_load(const EncIn &E, int i)
     return r;
 }
 
+// The exact test's bound in FP32 (k_enc_direct, where its filter keeps most pairs): the
+// record in units of the system's scale, the velocities times 2 dt.  A pair the exact
+// test's bound passes is never dropped: with u = 2^-24 the differences carry 2u (|x_i| +
+// |x_j|), so f0, f1 an error of 14u (|Q_i|^2 + |Q_j|^2), g0, g1 of 14u (|Q|^2 + dt^2 |V|^2
+// summed over both bodies), and the bound with its own rounding less than 32u of both
+// bodies' |Q0|^2 + |Q1|^2 + dt^2 (|V0|^2 + |V1|^2): slack takes twice that.  rc is widened by 2^-18
+// for its rounding and the exact test's own margin.
+struct alignas(16) EncF {
+    float q0[3], q1[3], v0[3], v1[3], rc, slack, pad[2];
+};
+
+__device__ __forceinline__ EncF enc_load32(const EncIn &E, int i, double dt, double inv_l)
+{
+    const HRec R = enc_load(E, i);
+    EncF r;
+    double w = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double a = inv_l * R.q0[k], b = inv_l * R.q1[k], c = inv_l * dt * R.v0[k],
+                     d = inv_l * dt * R.v1[k];
+        r.q0[k] = (float)a;
+        r.q1[k] = (float)b;
+        r.v0[k] = (float)(2.0 * c);
+        r.v1[k] = (float)(2.0 * d);
+        w += a * a + b * b + c * c + d * d;
+    }
+    r.rc = (float)(inv_l * R.rc * (1.0 + 0x1p-18));
+    r.slack = (float)(w * (0x1p-18 * (1.0 + 0x1p-20)));
+    return r;
+}
+
+__device__ __forceinline__ bool enc_bound32(const EncF &I, const EncF &J)
+{
+    float f0 = 0.0f, f1 = 0.0f, g0 = 0.0f, g1 = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const float a = J.q0[k] - I.q0[k], b = J.q1[k] - I.q1[k];
+        f0 = fmaf(a, a, f0);
+        f1 = fmaf(b, b, f1);
+        g0 = fmaf(a, J.v0[k] - I.v0[k], g0);
+        g1 = fmaf(b, J.v1[k] - I.v1[k], g1);
+    }
+    const float lower = fmaf(-4.0f / 27.0f, fmaxf(0.0f, -g0) + fmaxf(0.0f, g1), fminf(f0, f1));
+    const float rc = fmaxf(I.rc, J.rc);
+    // (a value that is not finite goes to the exact test)
+    return !(lower > fmaf(rc, rc, I.slack + J.slack));
+}
+
 // Direct check of every pair i < j with a big member (i big): the filter of enc_record as
 // a product of matrices, then the exact test of the pairs it keeps.
 //
@@ -2936,14 +2984,26 @@ __device__ __forceinline__ HRec enc_load(const EncIn &E, int i)
 // items, by the latency of the row loads.  The kernel: 100 bodies 22 -> 5.0 us, 16384
 // bodies in 0.5-5 AU 14.4 us; the whole check at 1001 bodies 40 -> 10 us (nine launches
 // before).
+// With steps of most of a radian the relative chords are as long as the distances and
+// the filter keeps most pairs.  A group of 16 rows where half of the lanes keep kEncDense
+// or more of their 32 pairs waits for the end of the loop, where the targets are
+// taken into registers and the group's sources into LDS and every pair meets the Hermite bound
+// in FP32 (enc_bound32), which keeps few.  Every pair so costs about as much as one in
+// twenty through the queue: a 0.9-1.1 AU ring of 9990 bodies and steps of 0.16 yr 73 us,
+// by the queue alone 605 us, in the sorted check 220 us.
+constexpr int kEncDense = 2;
 __global__ __launch_bounds__(64, 3) void k_enc_direct(const PWork *__restrict__ work,
                                                    const v8h *__restrict__ eq, EncIn in, double dt,
                                                    unsigned long long *__restrict__ keys, int cap,
                                                    int *__restrict__ ce, int *__restrict__ nce,
-                                                   int tag)
+                                                   int tag,
+                                                   const unsigned long long *__restrict__ scale,
+                                                   const int *__restrict__ sys_of)
 {
     constexpr int NG = kEncTargets / 16;
     __shared__ int qe[128];
+    // 16 sources of a group of many candidates
+    __shared__ EncF sj[16];
     const PWork wk = work[blockIdx.x];
     const int lane = threadIdx.x, q = lane >> 4, r = lane & 15;
     // K slots 8q .. 8q + 7, rows against columns (g as in enc_record): q = 0 the high
@@ -2955,6 +3015,33 @@ __global__ __launch_bounds__(64, 3) void k_enc_direct(const PWork *__restrict__ 
     const v8h g = {g0, g0, g0, (_Float16)4.0f, (_Float16)4.0f, (_Float16)4.0f, (_Float16)-4.0f, zero};
     const int cpart = q == 0 || q == 2 ? 0 : (q == 1 ? 1 : 2);
     const int rpart = q < 2 ? 0 : q - 1;
+    int qn = 0;
+    auto drain = [&](int n) {
+        wave_lds_sync();
+        if (lane < n) {
+            const int e = qe[lane];
+            const HRec I = enc_load(in, wk.i0 + (e & 255));
+            enc_exact(I, enc_load(in, wk.j0 + (e >> 8)), dt, keys, cap, ce, nce, tag);
+        }
+    };
+    // lanes' candidates (target i0 + ti, source j0 + sj) to the queue
+    auto push = [&](bool cand, int ti, int sj) {
+        const unsigned long long mk = __builtin_amdgcn_ballot_w64(cand);
+        if (!mk)
+            return;
+        if (cand)
+            qe[qn + __popcll(mk & ((1ull << lane) - 1ull))] = ti | (sj << 8);
+        qn += __popcll(mk);
+        if (qn >= 64) {
+            drain(64);
+            const int rest = qn - 64;
+            const int e = lane < rest ? qe[64 + lane] : 0;
+            wave_lds_sync();
+            if (lane < rest)
+                qe[lane] = e;
+            qn = rest;
+        }
+    };
     v8h col[NG];
 #pragma unroll
     for (int k = 0; k < NG; ++k) {
@@ -2974,18 +3061,11 @@ __global__ __launch_bounds__(64, 3) void k_enc_direct(const PWork *__restrict__ 
             col[k][3] = q == 3 ? (_Float16)60000.0f : zero;
         }
     }
-    int qn = 0;
-    auto drain = [&](int n) {
-        wave_lds_sync();
-        if (lane < n) {
-            const int e = qe[lane];
-            const HRec I = enc_load(in, wk.i0 + (e & 255));
-            enc_exact(I, enc_load(in, wk.j0 + (e >> 8)), dt, keys, cap, ce, nce, tag);
-        }
-    };
     auto rows = [&](int s) {
         return eq[kEncRec * (size_t)(wk.j0 + min(s + r, wk.nj - 1)) + rpart];
     };
+    // the groups of many candidates, for after the loop (a work item has at most 64)
+    unsigned long long dense = 0ull;
     // rows loaded two groups ahead
     v8h row = rows(0), next = rows(16);
     for (int s = 0; s < wk.nj; s += 16) {
@@ -3010,26 +3090,41 @@ __global__ __launch_bounds__(64, 3) void k_enc_direct(const PWork *__restrict__ 
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 m = __builtin_amdgcn_alignbit(m, (unsigned)__float_as_int(f[k][v]), 31);
+        if (__builtin_expect(__popcll(__builtin_amdgcn_ballot_w64(__popc(m) >= kEncDense)) >= 32, 0)) {
+            dense |= 1ull << (s >> 4);
+            continue;
+        }
         while (__builtin_amdgcn_ballot_w64(m != 0u)) {
             const int b = m ? __clz(m) : 0;
-            // source j0 + sj, target i0 + ti
             const int sj = s + 4 * q + (b & 3), ti = 16 * (b >> 2) + r;
             const bool cand = m != 0u && sj < wk.nj && wk.j0 + sj > wk.i0 + ti;
             m &= ~(0x80000000u >> b);
-            const unsigned long long mk = __builtin_amdgcn_ballot_w64(cand);
-            if (!mk)
-                continue;
-            if (cand)
-                qe[qn + __popcll(mk & ((1ull << lane) - 1ull))] = ti | (sj << 8);
-            qn += __popcll(mk);
-            if (qn >= 64) {
-                drain(64);
-                const int rest = qn - 64;
-                const int e = lane < rest ? qe[64 + lane] : 0;
-                wave_lds_sync();
-                if (lane < rest)
-                    qe[lane] = e;
-                qn = rest;
+            push(cand, ti, sj);
+        }
+    }
+    if (__builtin_expect(dense != 0ull, 0)) {
+        const double inv_l = enc_inv_scale(scale[sys_of[wk.i0]]);
+        const bool two = wk.ni > 64, h0 = lane < wk.ni, h1 = 64 + lane < wk.ni;
+        const EncF I0 = enc_load32(in, wk.i0 + (h0 ? lane : 0), dt, inv_l);
+        const EncF I1 = enc_load32(in, wk.i0 + (h1 ? 64 + lane : 0), dt, inv_l);
+        while (dense) {
+            const int s = 16 * (__ffsll((long long)dense) - 1), jn = min(16, wk.nj - s);
+            dense &= dense - 1ull;
+            wave_lds_sync();
+            if (lane < jn)
+                sj[lane] = enc_load32(in, wk.j0 + s + lane, dt, inv_l);
+            wave_lds_sync();
+            for (int k = 0; k < jn; ++k) {
+                const EncF J = sj[k];
+                // source minus lane's first target
+                const int d = wk.j0 + s + k - (wk.i0 + lane);
+                const bool c0 = enc_bound32(I0, J) && h0 && d > 0;
+                const bool c1 = two && enc_bound32(I1, J) && h1 && d > 64;
+                if (!__builtin_amdgcn_ballot_w64(c0 || c1))
+                    continue;
+#pragma unroll 1
+                for (int e = 0; e < 128; e += 64)
+                    push(e ? c1 : c0, e + lane, s + k);
             }
         }
     }
@@ -5292,7 +5387,7 @@ hipError_t launch_enc_test(const Dev &d, double dt, hipStream_t s)
         const EncIn in{d.q0x, d.q0y, d.q0z, d.v0x, d.v0y, d.v0z, d.q1x, d.q1y, d.q1z, d.v1x, d.v1y, d.v1z,
                        d.rc1};
         k_enc_direct<<<d.new_, 64, 0, s>>>(d.ework, (const v8h *)d.eq, in, dt, d.keys, d.enc_cap, d.ce,
-                                           &d.stats->cur_nce, kEncFlag);
+                                           &d.stats->cur_nce, kEncFlag, d.scale, d.sys_of);
     }
     k_enc_count<<<1, 64, 0, s>>>(d.enc_cap, d.stats);
     return hipGetLastError();
@@ -5359,7 +5454,7 @@ hipError_t launch_enc_in_run(const Dev &d, double dt, int set, hipStream_t s)
         return hipSuccess;
     const EncIn in{d.q0x, d.q0y, d.q0z, d.v0x, d.v0y, d.v0z, d.q1x, d.q1y, d.q1z, d.v1x, d.v1y, d.v1z, d.rc1};
     k_enc_direct<<<d.new_, 64, 0, s>>>(d.ework, (const v8h *)d.eq, in, dt, d.keys, d.enc_cap, d.ce,
-                                       &d.stats->set_nce[set], kEncTag + set);
+                                       &d.stats->set_nce[set], kEncTag + set, d.scale, d.sys_of);
     return hipGetLastError();
 }
 

@@ -422,11 +422,16 @@ void pair_items(int a, int n, int nb, int J, std::vector<PWork> &out)
 
 // Work items of the direct encounter check: targets in strips of kEncTargets big
 // bodies, sources from the strip's first body on in chunks of J (whole groups of
-// 16).  J starts at the parameter and is halved, down to 128, while there are
-// fewer than kEncMinItems items (one wave each; 1024 SIMDs).  The kernel with
-// chunks of 1024 against this rule's: 1001 bodies 21.5 / 5.5 us, 5003 bodies 24.5
-// / 6.8 us, 16384 bodies 17.9 / 14.4 us.
+// 16).  J starts at the parameter (at most kEncSources) and is halved, down to 128, while
+// there are fewer than kEncMinItems items (one wave each; 1024 SIMDs), and further, down
+// to 32, while there are fewer than kEncFewItems.  The kernel with chunks of 1024 against
+// the first rule's: 1001 bodies 21.5 / 5.5 us, 5003 bodies 24.5 / 6.8 us, 16384 bodies
+// 17.9 / 14.4 us; the whole check by the first rule / by both: 1001 bodies of a ring 8.4 /
+// 7.5 us, with steps of 0.12 yr (every pair a candidate) 42 / 15 us.  More waves than
+// these take their time from the force beside them (the second rule as far as 2048 items
+// too: a step of 5003 bodies in FP32C 38.6 -> 39.8 us).
 constexpr long long kEncMinItems = 2048;
+constexpr long long kEncFewItems = 256;
 
 int enc_chunk(const Params &p, int nsys, const int32_t *off, const int32_t *nbig)
 {
@@ -439,8 +444,8 @@ int enc_chunk(const Params &p, int nsys, const int32_t *off, const int32_t *nbig
         }
         return c;
     };
-    int J = std::max(16, (std::min(p.enc_j, 1 << 20) + 15) / 16 * 16);
-    while (J > 128 && items(J) < kEncMinItems)
+    int J = std::max(16, (std::min(p.enc_j, kEncSources) + 15) / 16 * 16);
+    while (J > 32 && items(J) < (J > 128 ? kEncMinItems : kEncFewItems))
         J = (J / 2 + 15) / 16 * 16;
     return J;
 }

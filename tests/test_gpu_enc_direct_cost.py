@@ -37,3 +37,16 @@ def test_one_body_far_out(far):
     _, ref = _check(w, 2, w.dt)
     assert e.nce > 0 and _same(e, ref)
     assert ms < 2.0 * base, (ms, base)
+
+
+@pytest.mark.parametrize("n,dt", [(500, 0.16), (1001, 0.3), (9990, 0.1), (9990, 0.16)])
+def test_long_steps(n, dt):
+    """Steps of most of a radian, where the filter keeps most pairs of a ring: the direct
+    check costs no more than the sorted one (up to three times as much when every kept
+    pair takes the exact test from memory)."""
+    w = workloads.ring(n, m=1e-9)
+    ms, e = _check(w, 1, dt)
+    ref_ms, ref = _check(w, 2, dt)
+    print(n, dt, ms, ref_ms)
+    assert _same(e, ref)
+    assert ms < 1.1 * ref_ms, (ms, ref_ms)
