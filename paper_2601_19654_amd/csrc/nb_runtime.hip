@@ -101,7 +101,7 @@ int set_err(nb_ctx *c, int code, const char *fmt, ...)
 
 Params to_internal(const nb_params &q)
 {
-    Params p;
+    Params p{};
     p.G = q.G;
     p.n_hill = q.n_hill;
     p.inner = q.chg_inner;
