@@ -281,6 +281,7 @@ struct Params {
     int enc_keep, alone_keep;   // the automatic choice (and whether the direct check's
                           // records are there beside the sorted check) kept over a
                           // compaction; 0: none kept
+    int snap_keep;        // the number of sets of drift outputs kept likewise; 0: none
     int step_algo;        // 1: per-phase launches, 2: persistent per-system launch, 3: the
                           // persistent launch of small systems (an automatic choice)
     int force_algo;       // 0 automatic, 1 ordered pairs, 2 symmetric tile pairs, 4 symmetric

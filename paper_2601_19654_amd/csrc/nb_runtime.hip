@@ -19,7 +19,9 @@
 using namespace nb;
 
 struct nb_ctx {
-    Params p;
+    // as asked for (or from the tuning table), and with the automatic choices of the
+    // present layout
+    Params base, p;
     bool tuned = false;   // tile and algorithm fields taken from the tuning table
     int nsys = 0, ntot = 0, enc_cap = 0;
     int device = 0;
@@ -675,7 +677,8 @@ constexpr long long kSnapSetBytes = 1ll << 30;
 int snap_sets(const Params &p, const Tables &t, int ntot)
 {
     const long long per = (long long)ntot * (13 * sizeof(double) + 2 * sizeof(double4));
-    if (p.resolve || p.step_algo == 2 || t.enc_fused || per * (kSnapSets - 1) > kSnapSetBytes)
+    if (p.resolve || p.step_algo == 2 || t.enc_fused || p.snap_keep == 2 ||
+        per * (kSnapSets - 1) > kSnapSetBytes)
         return 2;
     return kSnapSets;
 }
@@ -1272,29 +1275,43 @@ void release(nb_ctx *c)
 // lost bodies are removed.
 int setup_layout(nb_ctx *c, int nsys, const int32_t *off, const int32_t *nbig)
 {
+    // The automatic choices of a fresh context.  Where bodies were removed, a choice's other
+    // side may take more of the workspace the context was created with (narrower super-tiles
+    // more partials, the direct check more sets of its records, smaller arrays more sets of
+    // drift outputs, the symmetric force more than the ordered one): then those the context
+    // has had, the force's first.
+    Params q;
     Tables t;
-    build_tables(c->p, nsys, off, nbig, t);
-    Dev d{};
-    size_t need = carve(c->p, nsys, off[nsys], c->enc_cap, t, nullptr, d);
-    if (c->ws_bytes < need && c->ntot > 0 && c->p.enc_auto) {
-        // fewer bodies than before, past a line between the encounter checks, whose other
-        // side takes more of the workspace (eight sets of the direct check's records):
-        // the check the context has had
-        Params q = c->p;
-        q.enc_keep = c->d.enc_sorted ? 2 : 1;
-        q.alone_keep = c->d.eq_alone != nullptr;
-        Tables u;
-        build_tables(q, nsys, off, nbig, u);
-        const size_t kept = carve(q, nsys, off[nsys], c->enc_cap, u, nullptr, d);
-        if (kept <= c->ws_bytes) {
-            c->p = q;
-            t = std::move(u);
-            need = kept;
+    size_t need = 0;
+    for (int keep = 0; keep < (c->ntot > 0 ? 3 : 1); ++keep) {
+        q = c->base;
+        auto_force_r(q, nsys, off, nbig);
+        fused_tiles(q, nsys, off, nbig);
+        if (keep >= 1) {
+            q.force_r = c->p.force_r;
+            if (c->d.force_sym)
+                q.force_g = c->d.sym_g;
+            else if (q.force_algo == 0)
+                q.force_algo = 1;
         }
+        if (keep >= 2) {
+            if (q.enc_auto) {
+                q.enc_keep = c->d.enc_sorted ? 2 : 1;
+                q.alone_keep = c->d.eq_alone != nullptr;
+            }
+            q.snap_keep = c->d.nsnap;
+        }
+        t = Tables{};
+        build_tables(q, nsys, off, nbig, t);
+        Dev d{};
+        need = carve(q, nsys, off[nsys], c->enc_cap, t, nullptr, d);
+        if (need <= c->ws_bytes)
+            break;
     }
     if (c->ws_bytes < need)
         return set_err(c, NB_E_WORKSPACE, "workspace of %zu bytes, %zu needed", c->ws_bytes, need);
     drop_graph(c);
+    c->p = q;
     c->nsys = nsys;
     c->ntot = off[nsys];
     c->off.assign(off, off + nsys + 1);
@@ -1490,17 +1507,15 @@ int nb_create(const nb_params *p, int nsys, const int32_t *off, const int32_t *n
     if (!workspace || ((uintptr_t)workspace % kAlign) != 0)
         return NB_E_WORKSPACE;
     nb_ctx *c = new nb_ctx();
-    c->p = to_internal(*p);
+    c->base = to_internal(*p);
     {
         std::string why;
-        if (apply_tuning(*p, nsys, off, nbig, c->p, &c->tuned, &why)) {
+        if (apply_tuning(*p, nsys, off, nbig, c->base, &c->tuned, &why)) {
             delete c;
             return NB_E_INVALID;
         }
-        if (c->p.enc_algo == 3 && max_big(nsys, off, nbig) > kBlock)
-            c->p.enc_algo = 0;
-        auto_force_r(c->p, nsys, off, nbig);
-        fused_tiles(c->p, nsys, off, nbig);
+        if (c->base.enc_algo == 3 && max_big(nsys, off, nbig) > kBlock)
+            c->base.enc_algo = 0;
     }
     c->enc_cap = enc_cap;
     c->stream = (hipStream_t)stream;
