@@ -1,9 +1,13 @@
-"""Tile-size search for the pair kernels, cached per (GPU arch, mode, size class).
+"""Search of the pair kernels' tiles and algorithms, cached per (GPU arch, mode, size class).
 
 For a given batch of systems it times, with HIP events on the context's stream
-(nb_time_kernel), the whole force evaluation (force kernel plus the sum of its
-split partials) over targets-per-lane x sources-per-work-item candidates and the encounter kernel over sources-per-work-item candidates, and
-stores the fastest choice in ``tuning.json`` (with every candidate's time) under
+(nb_time_kernel), the whole force evaluation (force kernel plus the sum of its split
+partials) over its candidates, and then whole steps: of the force candidates near the
+fastest, of the encounter checks and of the step launches.  A check alone says little
+about a step: the sorted check's small kernels run in the gaps of the force beside them,
+the direct check's matrix products take their time from it.  The library's automatic
+choice (0) is a candidate of both, and is taken unless another is faster by more than
+TIE.  The choices are stored in ``tuning.json`` (with every candidate's time) under
 ``<arch>/<mode>/n<max system size, next power of two>/s<systems, next power of two>``,
 and the chosen fields in ``tuning.tsv``, the table the library itself reads
 (``nb_params.autotune_path``) whenever the caller leaves the tile fields at 0.
@@ -26,7 +30,10 @@ CACHE = os.path.join(PKG, "tuning.json")
 FORCE_R = (1, 2, 4)
 FORCE_J = (256, 512, 1024, 2048, 4096)
 FORCE_G = (1, 2, 4)          # super-tile widths of the symmetric force
-ENC_J = (256, 512, 1024, 2048, 4096)
+ENC_J = 1024                 # most sources per item of the direct check (the library halves it)
+TIE = 0.04                   # an automatic choice is kept unless another is faster by more
+STEP_REPEATS, STEP_REPS = 5, 32   # best of five timings of 32 steps
+NEAR, NEAR_MOST = 1.25, 8    # force candidates whose steps are timed: within NEAR of the fastest, at most 8
 
 
 def _pow2(n: int) -> int:
@@ -103,86 +110,63 @@ def tune(w, mode: str, reps: int = 10, verbose: bool = True) -> dict:
                     print(f"[autotune] {mode} force evaluation algo={fa} r={r} j={j} g={g}: {ms:.4f} ms",
                           file=sys.stderr, flush=True)
                 c.close()
-    # encounter candidates: (1, j) direct with source chunks of j, (2, 0) sorted
-    # tiles, (3, 0) every body against its system's big bodies (some small
-    # bodies, at most 256 big bodies per system)
     sizes = np.diff(w.off)
     nbig = sizes if w.nbig is None else np.asarray(w.nbig)
-    enc_cands = [(1, j) for j in ENC_J if j <= max(256, _pow2(int(sizes.max()))) * 2] + [(2, 0)]
-    if np.any(nbig < sizes) and int(nbig.max()) <= 256:
-        enc_cands.append((3, 0))
-    for ea, j in enc_cands:
-        p = nb.default_params(G=w.G, mode=_mode_id(mode), drag=int(w.drag), enc_jchunk=j or 1024,
-                              enc_algo=ea)
+
+    def step_ms(fa_, r_, j_, g_, ea_, sa_):
+        p = nb.default_params(G=w.G, mode=_mode_id(mode), drag=int(w.drag), force_r=r_, force_jchunk=j_,
+                              force_algo=fa_, force_g=g_, enc_jchunk=ENC_J, enc_algo=ea_, step_algo=sa_)
+        c = nb.Context(w.off, p, enc_cap=1 << 18, device="cuda:0", tuned=False, nbig=w.nbig)
+        c.upload(w.m0, w.m, w.x, w.v)
+        # (the first runs capture their graphs, and raise the clocks of an idle GPU)
+        c.step(w.dt, STEP_REPS, allow=(nb.NB_E_CAPACITY, nb.NB_E_KEPLER))
+        times = [c.time_kernel(nb.NB_K_STEP, reps=STEP_REPS, dt=w.dt) for _ in range(STEP_REPEATS)]
+        c.close()
+        if verbose:
+            print(f"[autotune] {mode} step, force algo={fa_} r={r_} j={j_} g={g_}, check {ea_}, launch {sa_}: "
+                  f"{min(times):.4f} ms", file=sys.stderr, flush=True)
+        return min(times)
+
+    def best(times):
+        """The fastest candidate, the automatic one (0) on a tie."""
+        k = min(times, key=times.get)
+        return 0 if 0 in times and times[0] <= (1.0 + TIE) * times[k] else k
+
+    # the force candidates near the fastest, by whole steps of one launch per phase with
+    # the automatic check (the super-tile width trades force-kernel time for partial
+    # traffic, which the check beside the force shares)
+    fms = min(res_force.values())
+    near = sorted((k for k in res_force if res_force[k] <= NEAR * fms), key=res_force.get)[:NEAR_MOST]
+    res_near = {k: step_ms(*k, 0, 1) for k in near}
+    force = min(res_near, key=res_near.get)
+    # the encounter checks: automatic, direct, sorted, and (FP32C, every body big, the
+    # symmetric force) inside the force pass; and the check alone, for the record
+    direct = 3 if np.any(nbig < sizes) and int(nbig.max()) <= 256 else 1
+    checks = (0, direct, 2) + ((4,) if mode == "fp32c" and all_big and force[0] == 2 else ())
+    res_enc = {ea: step_ms(*force, ea, 1) for ea in checks}
+    ea = best(res_enc)
+    res_alone = {}
+    for a in (direct, 2):
+        p = nb.default_params(G=w.G, mode=_mode_id(mode), drag=int(w.drag), enc_jchunk=ENC_J, enc_algo=a)
         c = nb.Context(w.off, p, enc_cap=1 << 18, device="cuda:0", tuned=False, nbig=w.nbig)
         c.upload(w.m0, w.m, w.x, w.v)
         c.drift(w.dt, allow_fail=True)
-        ms = c.time_kernel(nb.NB_K_ENCOUNTER, reps=reps)
-        res_enc[(ea, j)] = ms
-        if verbose:
-            print(f"[autotune] {mode} encounter algo={ea} j={j}: {ms:.4f} ms", file=sys.stderr, flush=True)
+        res_alone[a] = c.time_kernel(nb.NB_K_ENCOUNTER, reps=reps)
         c.close()
-    (fa, r, j, g), fms = min(res_force.items(), key=lambda kv: kv[1])
-    (ea, ej), ems = min(res_enc.items(), key=lambda kv: kv[1])
-
-    def step_ms(fa_, r_, j_, g_, sa):
-        p = nb.default_params(G=w.G, mode=_mode_id(mode), drag=int(w.drag), force_r=r_, force_jchunk=j_,
-                              force_algo=fa_, force_g=g_, enc_jchunk=ej or 1024, enc_algo=ea, step_algo=sa)
-        c = nb.Context(w.off, p, enc_cap=1 << 18, device="cuda:0", tuned=False, nbig=w.nbig)
-        c.upload(w.m0, w.m, w.x, w.v)
-        c.step(w.dt, 3, allow=(nb.NB_E_CAPACITY, nb.NB_E_KEPLER))
-        ms = c.time_kernel(nb.NB_K_STEP, reps=max(2, reps // 2), dt=w.dt)
-        c.close()
-        return ms
-
-    # force evaluations within 10 % of the fastest are told apart by the whole
-    # step, where the force pass shares the GPU with the encounter check (the
-    # super-tile width trades force-kernel time for partial traffic there)
-    near = [k for k, v in res_force.items() if v <= 1.10 * fms]
-    res_near = {}
-    if len(near) > 1:
-        for k in near:
-            res_near[k] = step_ms(*k, 1)
-            if verbose:
-                print(f"[autotune] {mode} step with force algo={k[0]} r={k[1]} j={k[2]} g={k[3]}: "
-                      f"{res_near[k]:.4f} ms", file=sys.stderr, flush=True)
-        fa, r, j, g = min(res_near.items(), key=lambda kv: kv[1])[0]
-        fms = res_force[(fa, r, j, g)]
-    # the encounter test inside the force pass (FP32C, every body big, symmetric
-    # force): only a whole step compares it with the separate check
-    if mode == "fp32c" and all_big and fa == 2 and ea == 2:
-        base = res_near.get((fa, r, j, g)) or step_ms(fa, r, j, g, 1)
-        p4 = nb.default_params(G=w.G, mode=_mode_id(mode), drag=int(w.drag), force_r=r, force_jchunk=j,
-                               force_algo=fa, force_g=g, enc_jchunk=ej or 1024, enc_algo=4, step_algo=1)
-        c = nb.Context(w.off, p4, enc_cap=1 << 18, device="cuda:0", tuned=False, nbig=w.nbig)
-        c.upload(w.m0, w.m, w.x, w.v)
-        c.step(w.dt, 3, allow=(nb.NB_E_CAPACITY, nb.NB_E_KEPLER))
-        fused = c.time_kernel(nb.NB_K_STEP, reps=max(2, reps // 2), dt=w.dt)
-        c.close()
-        res_enc[(4, 0)] = fused
-        if verbose:
-            print(f"[autotune] {mode} step with the check in the force pass: {fused:.4f} ms "
-                  f"(separate: {base:.4f} ms)", file=sys.stderr, flush=True)
-        # the step time of the chosen check (the per-phase launch's entry below)
-        res_near[(fa, r, j, g)] = min(base, fused)
-        if fused < base:
-            ea = 4
-    # whole-step launch: per-phase launches (tuned tiles) vs the persistent launch
-    res_step = {}
-    for sa in ((1, 2) if mode == "fp64" and int(np.diff(w.off).max()) <= 8192 else (1,)):
-        res_step[sa] = (res_near[(fa, r, j, g)] if sa == 1 and (fa, r, j, g) in res_near
-                        else step_ms(fa, r, j, g, sa))
-        if verbose:
-            print(f"[autotune] {mode} step launch {sa}: {res_step[sa]:.4f} ms", file=sys.stderr, flush=True)
-    sa, sms = min(res_step.items(), key=lambda kv: kv[1])
-    return {"force_algo": fa, "force_r": r, "force_jchunk": j, "force_g": g, "enc_jchunk": ej or 1024,
-            "enc_algo": ea,
-            "step_algo": sa, "step_ms": round(sms, 5), "step_candidates": {str(k): round(v, 5) for k, v in res_step.items()},
-            "force_ms": round(fms, 5),
-            "encounter_ms": round(ems, 5), "workload": w.name, "tuned_at": time.strftime("%Y-%m-%d"),
-            "force_candidates": {f"a{f}_r{a}_j{b}_g{h}": round(v, 5) for (f, a, b, h), v in res_force.items()},
-            "near_tie_steps": {f"a{f}_r{a}_j{b}_g{h}": round(v, 5) for (f, a, b, h), v in res_near.items()},
-            "encounter_candidates": {f"a{a}_j{b}": round(v, 5) for (a, b), v in res_enc.items()}}
+    # the step launches: automatic, per phase, persistent
+    persistent = mode == "fp64" and int(sizes.max()) <= 8192
+    res_step = {sa: step_ms(*force, ea, sa) for sa in ((0, 1, 2) if persistent else (0, 1))}
+    sa = best(res_step)
+    name = "a{}_r{}_j{}_g{}".format
+    fa, r, j, g = force
+    return {"force_algo": fa, "force_r": r, "force_jchunk": j, "force_g": g, "enc_jchunk": ENC_J, "enc_algo": ea,
+            "step_algo": sa, "step_ms": round(res_step[sa], 5), "force_ms": round(res_force[force], 5),
+            "workload": w.name, "tuned_at": time.strftime("%Y-%m-%d"),
+            "force_candidates": {name(*k): round(v, 5) for k, v in res_force.items()},
+            "force_candidates_steps": {name(*k): round(v, 5) for k, v in res_near.items()},
+            "encounter_candidates_steps": {str(k): round(v, 5) for k, v in res_enc.items()},
+            "encounter_alone": {str(k): round(v, 5) for k, v in res_alone.items()},
+            "step_candidates": {str(k): round(v, 5) for k, v in res_step.items()}}
 
 
 def main():
@@ -204,7 +188,7 @@ def main():
             cache[k] = best
             print(f"[autotune] {k} -> force_algo={best['force_algo']} r={best['force_r']} j={best['force_jchunk']} "
                   f"enc_algo={best['enc_algo']} enc_j={best['enc_jchunk']} step_algo={best['step_algo']} "
-                  f"({best['force_ms']:.4f} / {best['encounter_ms']:.4f} ms)",
+                  f"(force {best['force_ms']:.4f}, step {best['step_ms']:.4f} ms)",
                   file=sys.stderr, flush=True)
             with open(args.out, "w") as f:
                 json.dump(cache, f, indent=1, sort_keys=True)
