@@ -819,8 +819,8 @@ __device__ __forceinline__ double enc_inv_scale(unsigned long long v)
     const int cnt = (int)(v & ((1ull << kScaleShift) - 1ull));
     if (cnt == 0)
         return 1.0;
-    const int sum = (int)((long long)v >> kScaleShift);
-    const int e = (sum - (sum < 0 ? cnt - 1 : 0)) / cnt;      // the mean, rounded down
+    const float sum = (float)(int)((long long)v >> kScaleShift);
+    const int e = (int)floorf(sum * __builtin_amdgcn_rcpf((float)cnt));      // the mean, rounded down
     return ldexp(1.0, -((e >> 1) + 1));
 }
 
