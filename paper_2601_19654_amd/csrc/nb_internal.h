@@ -117,8 +117,8 @@ struct DevStats {
 };
 
 // What a drift leaves for the encounter check (snapshots, copies, chord
-// records); a context keeps two sets so that the check of one step can run
-// beside the next step.
+// records); a context keeps several sets (kSnapSets, or two), so that the checks of a
+// run can trail its steps.
 struct Snap {
     double *q0x, *q0y, *q0z, *v0x, *v0y, *v0z;
     double *q1x, *q1y, *q1z, *v1x, *v1y, *v1z, *rc1;
@@ -138,7 +138,8 @@ struct Dev {
     // check, so that it can run beside the next S(h), force and kick
     double *q1x, *q1y, *q1z, *v1x, *v1y, *v1z, *rc1;
     float4 *pk;           // FP32C source records: 2 per body {xhi,yhi,zhi,m},{xlo,ylo,zlo,rc2}
-    double4 *mr;          // persistent steps, per body: chord midpoint (x,y,z) and encounter reach R
+    double4 *mr;          // per body, when persistent steps are asked for (step_algo 2): chord
+                          // midpoint (x,y,z) and encounter reach R (else null)
     void *eq;             // direct check, per body after a drift: three records of 8 halves (else null)
     void *eq_alone;       // sorted check in steps, direct check elsewhere: set 0's records (else null)
     unsigned long long *scale;   // nsys: exponents of |Q|^2 at the upload (the records' unit)

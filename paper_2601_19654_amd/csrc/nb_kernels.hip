@@ -4343,7 +4343,7 @@ __global__ __launch_bounds__(NT) void k_steps_small(SmallArgs A)
         for (int k = 0; k < 3; ++k)
             P[k] += A.mom[4 * (size_t)(A.rb_first[S.sys] + b) + k];
     int near = 0, nf = 0;
-    // sum of m V (two barriers; every thread returns it)
+    // sum of m V (one barrier; every thread returns it; a second one before the next)
     auto momentum = [&](double (&out)[3]) {
         double p[3] = {mi * u, mi * v, mi * w};
 #pragma unroll

@@ -676,7 +676,7 @@ constexpr long long kSnapSetBytes = 1ll << 30;
 // and the further sets fit in kSnapSetBytes; else two.
 int snap_sets(const Params &p, const Tables &t, int ntot)
 {
-    const long long per = (long long)ntot * (13 * sizeof(double) + 2 * sizeof(double4));
+    const long long per = (long long)ntot * (13 * sizeof(double) + (t.enc_sorted ? 0 : kEncRecBytes));
     if (p.resolve || p.step_algo == 2 || t.enc_fused || p.snap_keep == 2 ||
         per * (kSnapSets - 1) > kSnapSetBytes)
         return 2;
@@ -700,7 +700,7 @@ size_t carve(const Params &p, int nsys, int ntot, int enc_cap, const Tables &t, 
     for (double **pl : planes)
         *pl = (double *)take(nd);
     d.pk = (float4 *)take((size_t)ntot * 2 * sizeof(float4));
-    d.mr = (double4 *)take((size_t)ntot * sizeof(double4));
+    d.mr = p.step_algo == 2 ? (double4 *)take((size_t)ntot * sizeof(double4)) : nullptr;
     const size_t eq_all = (size_t)ntot * kEncRecBytes, eq_bytes = t.enc_sorted ? 0 : eq_all;
     d.eq = eq_bytes ? take(eq_bytes) : nullptr;
     d.eq_alone = t.enc_alone ? take(eq_all) : nullptr;
