@@ -730,12 +730,25 @@ __device__ int kepler_drift(double mu, double dt, double &x, double &y, double &
     return 0;
 }
 
-// The endpoint velocity deviations e0 = dt V0 - c, e1 = dt V1 - c of a step's chord c
-// enter the Hermite interpolant as h10(s) e0 + h11(s) e1 with h10 = s (1-s)^2 >= 0 and
-// h11 = -s^2 (1-s) <= 0, that is as s(1-s) d + s(1-s)(1-2s) p of their half difference
-// d = (e0 - e1)/2 = dt (V0 - V1)/2 and their mean p.  s(1-s) <= 1/4 and s(1-s)|1-2s| <=
-// 1/(6 sqrt 3), so the relative deviation of a pair stays below E/4 with
-//   E = |d_j - d_i| + kEncP (|p_i| + |p_j|).
+// What the encounter filters know of a pair.  The exact test's f(s) is the cubic of the
+// squared distance with slopes 2 dt dQ0.dV0 and 2 dt dQ1.dV1.  With the relative midpoint M,
+// chord c and endpoint velocity deviations e0 = dt dV0 - c, e1 = dt dV1 - c (half their
+// difference d = dt (dV0 - dV1)/2, their mean p), the cubic reproduces the straight
+// chord x(s) = M + (s - 1/2) c exactly and adds 2 h10 dQ0.e0 + 2 h11 dQ1.e1, h10 =
+// s(1-s)^2, h11 = -s^2 (1-s):
+//   f = |x|^2 + 2 sg d.x + 2 sg p.((1-2s) M - c/2),   sg = s(1-s), t = |1-2s| = sqrt(1 - 4 sg).
+// With D = |M|, a = |c|/2 and X = D - a t <= |x|, where X >= sg |d|,
+//   f >= X^2 - 2 sg |d| X - 2 sg |p| (t D + a).                                         (1)
+// E = |d| + kEncP |p|; of two bodies, |d_j - d_i| + kEncP (|p_i| + |p_j|) is no less.
+// (A) A pair with D > 2a + 3/4 E + rc stays outside rc: D = X + a t in (1), with al = 2 sg
+// <= 1/2, be = al t <= 1/(3 sqrt 3), ga = al (1 + t^2) and X = u + rc, u >= (2-t) a + 3/4 |d| +
+// 3/4 kEncP |p|, gives f - rc^2 >= X (X - al |d| - be |p|) - rc^2 - ga a |p| >=
+// a |p| ((2-t)(3/2 kEncP - be) - ga) > 0, the last bracket at least 0.1.
+// (B) Where D > a and g = (D-a)^2 - (D+a) E/2 > 0, f >= g: (1) minus g is at least
+// a(1-t)(2D - a(1+t)) - (al - kEncP/2) a |p| (as kEncP/2 > be and al <= 1/2), and g > 0 bounds
+// |p| by 2 (D-a)^2 / (kEncP (D+a)): with x = D/a >= 1 it is not negative where
+// (1-t)(2x-1-t)(x+1) >= ((1-t^2)/kEncP - 1)(x-1)^2, which holds for every t in [0, 1].  (For
+// g < 0 it can fail: p along c enters with sg a |p|, more than E/4 covers.)
 // On an orbit d is the fall toward the star, about -dt^2/2 times the acceleration,
 // which neighbours share, and p is of third order in dt: E is small where the largest
 // |e| of either body is not.
@@ -2962,12 +2975,8 @@ __device__ __forceinline__ bool enc_bound32(const EncF &I, const EncF &J)
 // Direct check of every pair i < j with a big member (i big): the filter of enc_record as
 // a product of matrices, then the exact test of the pairs it keeps.
 //
-// The Hermite data of a pair split into the straight relative chord, which the
-// cubic reproduces exactly and which stays at least D - |dc|/2 away (D = |dM| the
-// distance of the chord midpoints, dc = c_j - c_i), and the endpoint velocity
-// deviations, at most E/4 (kEncP).  So f(s) >= (D - a)^2 - (1/2)(D + a)E with a =
-// |dc|/2, which exceeds rc_ij^2 whenever D > |dc| + 3E/4 + rc_ij: such pairs cannot be
-// flagged.  Bodies moving together (neighbours on similar orbits) have short relative
+// A pair whose chord midpoints are further apart than its relative chord, 3/4 E and rc_ij
+// together cannot be flagged (kEncP, A).  Bodies moving together (neighbours on similar orbits) have short relative
 // chords and share their fall toward the star, so this keeps few pairs also when
 // steps are long: 3.7e-5 of the pairs of 20011 bodies at 0.9-1.1 AU and steps of 0.04
 // yr, as many of a 1-3 AU disk and 0.05 yr (with the sum of both bodies' largest
@@ -3167,13 +3176,12 @@ __global__ void k_enc_clear(int ntot, int *__restrict__ ce, DevStats *stats)
 // grid of about N_s/8 cells traversed in Morton order, counting-sorted, and
 // cut into tiles of 64 consecutive bodies.  A tile carries the centre and
 // radius of its chord midpoints M, chords c and endpoint velocity deviations
-// (d, with kEncP |p| added to its radius).  For i in tile A and j in tile B the
-// Hermite data split into the chord quadratic |dM + (s - 1/2) dc|^2 and the
-// relative deviation of at most E/4 (kEncP) give f(s) >= Lmin^2 - Qmax Em / 2 with
+// (d, with kEncP |p| added to its radius).  For i in tile A and j in tile B
+// f(s) >= Lmin^2 - Qmax Em / 2 where that is positive (kEncP, B), with
 //   Lmin = D - sm_A - sm_B - Cm/2,  Qmax = D + sm_A + sm_B + Cm/2,
 //   D = |cm_B - cm_A|, Cm = |cc_B - cc_A| + sc_A + sc_B, Em = |ce_B - ce_A| + se_A + se_B,
 // so a tile pair whose bound exceeds max rc^2 holds no flagged pair.  Surviving
-// tile pairs are tested pair by pair exactly as in k_encounter.  The bodies of
+// tile pairs are tested pair by pair (k_enc_pairs).  The bodies of
 // a cell are put in index order after the binning, so the sorted order does
 // not depend on the timing of its atomics; the output list is sorted.
 // ----------------------------------------------------------------------------
