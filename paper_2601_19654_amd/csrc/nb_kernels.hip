@@ -5199,16 +5199,19 @@ hipError_t launch_drift(const Dev &d, const Params &p, double dt, double sun_h,
 // / 7.2 / 5.5 us, 3001 bodies (1128) 13.7 / 11.3 / 11.2 us in FP64 and 11.4 / 8.8 /
 // 9.6 us in FP32C, 6000 bodies (4465) 26.3 / 26.9 / 28.3 us; tiles of 128, 5003
 // bodies (820) 25.2 / 20.6 / 19.7 us, 10000 (3160) 63.3 / 54.0 / 52.7 us, 131072
-// (524800) 7540 / 7681 / 8212 us.  Eight steps with their encounter checks, whose small
-// kernels run in the gaps: FP64 13000 bodies (5253) 971 / 924 / 963 us, 20000 (12403)
-// 1901 / 1836 / 1905 us, 30000 (27730) 3655 / 3623 / 3792 us; FP32C, whose shorter pair
-// terms leave more of the time to each wave's own part, 13000 bodies 821 / 766 / 809
-// us, 16384 (8256) 950 / 990 us, 30000 2647 / 2713 / 2930 us.
+// (524800) 7540 / 7681 / 8212 us.  Steps with their encounter checks, whose small
+// kernels run in the gaps: FP64 11000 bodies (3741) 91.0 / 87.6 / 89.9 us, 13000 (5253)
+// 115.4 / 109.9 / 114.4 us, 16384 (8256) 154.8 / 154.1 / 160.7 us, 20000 (12403) 232.7 /
+// 223.8 / 232.3 us, 30000 (27730) 451 / 448 / 469 us; FP32C, whose shorter pair terms leave
+// more of the time to each wave's own part, 12000 (4465) 83.0 / 76.6 / 83.3 us, 13000 91.8
+// / 89.0 / 94.8 us, 13500 (5671) 93.0 / 95.1 / 100.2 us, 14000 (6105) 94.4 / 100.2 / 104.9 us
+// (over the radial order 93.1 / 98.3 us with one and two waves), 16000 (7875) 121.6 /
+// 120.1 us (over the radial order 112.4 / 116.5 us).
 int sym_waves(int nitems, const Params &p)
 {
     if (p.force_r == 1)
         return nitems < 1024 ? 4 : (nitems < 4096 ? 2 : 1);
-    return nitems < 4096 ? 4 : (nitems < (p.mode == 1 ? 8192 : 1 << 18) ? 2 : 1);
+    return nitems < 4096 ? 4 : (nitems < (p.mode == 1 ? 5400 : 1 << 18) ? 2 : 1);
 }
 
 hipError_t launch_force(const Dev &d, const Params &p, hipStream_t s)
