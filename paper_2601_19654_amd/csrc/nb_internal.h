@@ -179,6 +179,7 @@ struct Dev {
     // sorted encounter check
     int enc_sorted;
     int *nce;             // direct check in a run: where this set's drift clears the count (else null)
+    int pair_waves;       // sorted check beside the force: waves per workgroup of its pair test
     int enc_few;          // the direct check chosen for few big bodies (reported as such)
     double *lnr_part;     // nrb x 2: min, max of ln R (cylindrical) of chord midpoints
     int *cell_of, *slot_of;   // ntot
@@ -313,6 +314,8 @@ hipError_t launch_sun_drift(const Dev &d, double h, int rcrit, const Params &p, 
 // launch_force_finalize does them
 hipError_t launch_drift(const Dev &d, const Params &p, double dt, double sun_h,
                         const double *part_in, hipStream_t s, bool fin = false);
+// waves that share one of nitems tile pairs of the symmetric force
+int sym_waves(int nitems, const Params &p);
 hipError_t launch_force(const Dev &d, const Params &p, hipStream_t s);
 // tables of a single system of d.ntot bodies (O(N) blocks, m0, super-tile pairs of
 // ST bodies, nt super-tiles) and a cleared statistics block, written on the device
@@ -323,7 +326,8 @@ hipError_t launch_single_tables(const Dev &d, int ST, int nt, double m0, hipStre
 // statistics of the encounter list the fused pass wrote
 hipError_t launch_force_finalize(const Dev &d, const Params &p, double kick_h, int kicks,
                                  hipStream_t s, const int *ord = nullptr, bool enc_count = false);
-hipError_t launch_encounters(const Dev &d, double dt, hipStream_t s);
+// beside: on the second queue of a run, with the force of the following steps beside it
+hipError_t launch_encounters(const Dev &d, double dt, hipStream_t s, bool beside = false);
 hipError_t launch_diagnostics(const Dev &d, const Params &p, hipStream_t s);
 // star impacts, collisions among the listed pairs, ejections (r_eject > 0) of
 // the last step (drift arcs of d.snap(), the sorted list), applied in place
@@ -349,7 +353,7 @@ hipError_t launch_enc_prepare(const Dev &d, double dt, hipStream_t s);
 // fused mode: the force and the encounter test in one pass, then (count != 0) the
 // list's count
 hipError_t launch_force_fused(const Dev &d, const Params &p, double dt, int count, hipStream_t s);
-hipError_t launch_enc_test(const Dev &d, double dt, hipStream_t s);
+hipError_t launch_enc_test(const Dev &d, double dt, hipStream_t s, bool beside);
 // resolver transfers: both ends of listed pairs [k0, k0 + n) -> res_buf (per end
 // m0, m, rc, Q0, V0, index); res_rows (index, Q, V; rows not finite skipped) -> state
 hipError_t launch_gather_pairs(const Dev &d, int k0, int n, hipStream_t s);

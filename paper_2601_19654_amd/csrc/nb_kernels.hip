@@ -2572,7 +2572,15 @@ __device__ __forceinline__ bool far_tiles(float4 a, float4 b)
 // SORT: the positions of the work items are positions of the radial order
 // (ord: position -> body), whose tile bounds rtb (system s's tiles from
 // rtf[s], 64 positions each from off[s]) mark the far sub-tile pairs.
-template <int R, int G, bool SORT = false, int H = 1>
+// REG: the sources' run sums in registers, else in LDS.  In registers the loop is bound
+// by the vector ALU alone, in LDS by both; but the far tile pairs of the radial order,
+// whose steps are short, bear the moves between lanes worse than the LDS.  So wider
+// workgroups over the radial order keep LDS.  The kernel / a step, registers against LDS,
+// disk of 0.5-5 AU: 33000 bodies (workgroups of two) 324.8 / 289.7 us and 372.7 / 342.0 us, 65000
+// 1147 / 1028 and 1272 / 1143, 131072 (of four) 4369 / 4109 and 4608 / 4313; a dense ring of
+// 33000 341 / 340 and 397.3 / 396.3, of 131072 4656 / 4901 and 4989 / 5255.  (One wave per tile
+// pair, 16384 bodies: 84.1 / 78.2 us, but a call of eight steps 989 / 1021 us.)
+template <int R, int G, bool SORT = false, int H = 1, bool REG = (R <= 2 && !(SORT && G > 1))>
 __global__ __launch_bounds__(64 * G * H, R == 4 ? 2 : 3) void k_force32c_sym(const FWork *__restrict__ work, int nitems,
                                                          const float4 *__restrict__ pk,
                                                          const double *__restrict__ qx,
@@ -2588,9 +2596,9 @@ __global__ __launch_bounds__(64 * G * H, R == 4 ? 2 : 3) void k_force32c_sym(con
                                                          const int *__restrict__ off = nullptr)
 {
     constexpr int T = 64 * R;
-    static_assert(H == 1 || (G == 1 && R <= 2), "only single tile pairs are shared");
-    using Tile = typename std::conditional<(R <= 2), SymTile32R<R, SymPart<R, H>::kCopies>,
-                                           SymTile32<T>>::type;
+    static_assert(H == 1 || (G == 1 && REG), "only single tile pairs are shared");
+    static_assert(!REG || R <= 2, "the register form's tiles");
+    using Tile = typename std::conditional<REG, SymTile32R<R, SymPart<R, H>::kCopies>, SymTile32<T>>::type;
     __shared__ Tile tl[G];
     // H > 1: the waves' sums of the targets
     __shared__ double tgt[H > 1 ? H : 1][3][H > 1 ? T : 1];
@@ -3675,9 +3683,10 @@ __device__ __noinline__ void enc_candidate(const SRec *__restrict__ srec, double
 // from the sorted FP64 records in memory 64 at a time, one per lane (with steps of a
 // radian most pairs of a dense ring pass the filter, and a test per pass would run on
 // a few lanes); a tile pair reads 6 KB of filter records instead of the 112-byte
-// records of both tiles.  One wave per workgroup: its 10 KB of LDS fit beside the force
-// kernel's workgroups, which hold most of a compute unit's.
-__global__ __launch_bounds__(64) void k_enc_pairs(const Tile *__restrict__ tiles,
+// records of both tiles.  W waves per workgroup (independent of each other): 10 KB of LDS
+// each, so that the workgroup's size says where it fits beside the force's (launch_enc_test).
+template <int W>
+__global__ __launch_bounds__(64 * W) void k_enc_pairs(const Tile *__restrict__ tiles,
                                                       const TileB *__restrict__ tileb,
                                                       const int2 *__restrict__ tpairs, int tp_cap,
                                                       const SRec *__restrict__ srec,
@@ -3687,18 +3696,23 @@ __global__ __launch_bounds__(64) void k_enc_pairs(const Tile *__restrict__ tiles
                                                       int cap, int *__restrict__ ce,
                                                       DevStats *stats)
 {
-    __shared__ float4 sm_[64], sc_[64], sd_[64];
+    const int wv = W > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    __shared__ float4 sm_w[W][64], sc_w[W][64], sd_w[W][64];
+    float4 (&sm_)[64] = sm_w[wv], (&sc_)[64] = sc_w[wv], (&sd_)[64] = sd_w[wv];
     // queued pairs (lane | source << 8), fewer than 64 between drains
-    __shared__ int qe[128];
+    __shared__ int qe_w[W][128];
+    int (&qe)[128] = qe_w[wv];
     // tile A's exact-test fields (q0, v0, q1, v1, rc by plane; body
     // index), staged at the tile pair's first full drain: a drain's 64 pairs
     // hold many targets and few sources
-    __shared__ double ha[13][64];
-    __shared__ int hb[64];
-    const int lane = threadIdx.x;
+    __shared__ double ha_w[W][13][64];
+    __shared__ int hb_w[W][64];
+    double (&ha)[13][64] = ha_w[wv];
+    int (&hb)[64] = hb_w[wv];
+    const int lane = threadIdx.x & 63;
     const int npair = min(stats->cur_tp, tp_cap);
     const float qnan = __int_as_float(0x7fc00000);
-    for (int p = blockIdx.x; p < npair; p += gridDim.x) {
+    for (int p = blockIdx.x * W + wv; p < npair; p += gridDim.x * W) {
         const int2 AB = tpairs[p];
         Tile TA = tiles[AB.x], TB = tiles[AB.y];
         // uniform over the wave (one tile pair a wave): kept in scalar registers
@@ -5191,29 +5205,6 @@ hipError_t launch_drift(const Dev &d, const Params &p, double dt, double sun_h,
     return hipGetLastError();
 }
 
-// Waves that share one tile pair of the symmetric force (one tile pair per
-// workgroup).  One wave takes a pair of tiles of 64 in 10 us and of 128 in 24 us, so
-// that few pairs leave the chip idle, and as many as a few per wave slot (3072)
-// leave its last round half empty; each further wave stages and sums up for itself.
-// The force kernel alone, 1 / 2 / 4 waves: tiles of 64, 1001 bodies (136 pairs) 10.0
-// / 7.2 / 5.5 us, 3001 bodies (1128) 13.7 / 11.3 / 11.2 us in FP64 and 11.4 / 8.8 /
-// 9.6 us in FP32C, 6000 bodies (4465) 26.3 / 26.9 / 28.3 us; tiles of 128, 5003
-// bodies (820) 25.2 / 20.6 / 19.7 us, 10000 (3160) 63.3 / 54.0 / 52.7 us, 131072
-// (524800) 7540 / 7681 / 8212 us.  Steps with their encounter checks, whose small
-// kernels run in the gaps: FP64 11000 bodies (3741) 91.0 / 87.6 / 89.9 us, 13000 (5253)
-// 115.4 / 109.9 / 114.4 us, 16384 (8256) 154.8 / 154.1 / 160.7 us, 20000 (12403) 232.7 /
-// 223.8 / 232.3 us, 30000 (27730) 451 / 448 / 469 us; FP32C, whose shorter pair terms leave
-// more of the time to each wave's own part, 12000 (4465) 83.0 / 76.6 / 83.3 us, 13000 91.8
-// / 89.0 / 94.8 us, 13500 (5671) 93.0 / 95.1 / 100.2 us, 14000 (6105) 94.4 / 100.2 / 104.9 us
-// (over the radial order 93.1 / 98.3 us with one and two waves), 16000 (7875) 121.6 /
-// 120.1 us (over the radial order 112.4 / 116.5 us).
-int sym_waves(int nitems, const Params &p)
-{
-    if (p.force_r == 1)
-        return nitems < 1024 ? 4 : (nitems < 4096 ? 2 : 1);
-    return nitems < 4096 ? 4 : (nitems < (p.mode == 1 ? 5400 : 1 << 18) ? 2 : 1);
-}
-
 hipError_t launch_force(const Dev &d, const Params &p, hipStream_t s)
 {
     if (d.nfw == 0)
@@ -5379,7 +5370,7 @@ hipError_t launch_enc_gather(const Dev &d, double dt, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_enc_test(const Dev &d, double dt, hipStream_t s)
+hipError_t launch_enc_test(const Dev &d, double dt, hipStream_t s, bool beside)
 {
     if (d.enc_sorted) {
         if (d.ntile > 0) {
@@ -5390,9 +5381,31 @@ hipError_t launch_enc_test(const Dev &d, double dt, hipStream_t s)
             // one wave per kept tile pair, at most eight times as many as fit at once: they
             // take turns where pairs differ (steps of a radian, 20011 bodies of a ring: 986
             // us with 4096 waves, 743 with 16384, 707 with 32768)
-            const int grid = std::min(std::max(1, d.tp_cap), 32768);
-            k_enc_pairs<<<grid, 64, 0, s>>>(d.tiles, d.tileb, d.tpairs, d.tp_cap, d.srec, d.em, d.eg, dt,
-                                                 d.keys, d.enc_cap, d.ce, d.stats);
+            // Beside one system's force of one wave per tile pair (Dev::pair_waves), whose
+            // workgroups hold most of a compute unit's LDS, single waves slip in wherever a
+            // force workgroup ends and take its place; workgroups of four (over the radial
+            // order of more than 16384 bodies two) mostly wait for the force's last, partly
+            // idle round.  A step with 1 / 2 / 4 waves, disk of 0.5-5 AU: FP64 20011 bodies
+            // 233.7 / 221.7 / 220.4 us, 26000 351.1 / 338.7 / 335.6; FP32C 20011 174.4 / 170.1
+            // / 166.2, 26000 257.4 / 252.4 / 250.9; over the radial order 15000 101.4 / 103.1 /
+            // 104.4, 16384 114.2 / 114.8 / 115.9, 18000 147.7 / 143.2 / 143.0, 26000 239.7 /
+            // 235.7 / 241.1.  Beside wider force workgroups and beside a batch single waves are
+            // as good or better (FP64 15000 bodies 135.6 / - / 137.3 us, a ring of 131072 in
+            // FP32C 4967 / - / 5010 us, four systems of up to 12000 in FP32C 196.4 / - / 203.8 us),
+            // and alone they are done sooner (steps of 0.2 yr, 40000 bodies at 1-3 AU, 524 /
+            // 569 / 668 us).
+            const int w = beside ? d.pair_waves : 1;
+            const int grid = std::min(std::max(1, cdiv(d.tp_cap, w)), 32768 / w);
+#define NB_ENC_PAIRS(W_)                                                                          \
+    k_enc_pairs<W_><<<grid, 64 * W_, 0, s>>>(d.tiles, d.tileb, d.tpairs, d.tp_cap, d.srec, d.em,  \
+                                             d.eg, dt, d.keys, d.enc_cap, d.ce, d.stats)
+            if (w == 4)
+                NB_ENC_PAIRS(4);
+            else if (w == 2)
+                NB_ENC_PAIRS(2);
+            else
+                NB_ENC_PAIRS(1);
+#undef NB_ENC_PAIRS
         }
     } else if (d.new_ > 0) {
         const EncIn in{d.q0x, d.q0y, d.q0z, d.v0x, d.v0y, d.v0z, d.q1x, d.q1y, d.q1z, d.v1x, d.v1y, d.v1z,
@@ -5444,7 +5457,7 @@ hipError_t launch_force_fused(const Dev &d, const Params &p, double dt, int coun
     return hipGetLastError();
 }
 
-hipError_t launch_encounters(const Dev &d, double dt, hipStream_t s)
+hipError_t launch_encounters(const Dev &d, double dt, hipStream_t s, bool beside)
 {
     // an empty list and no flags (the check may run beside the next drift, so
     // the drift does not clear them); the sorted check's binning clears the
@@ -5456,7 +5469,7 @@ hipError_t launch_encounters(const Dev &d, double dt, hipStream_t s)
     }
     if (e == hipSuccess)
         e = launch_enc_gather(d, dt, s);
-    return e != hipSuccess ? e : launch_enc_test(d, dt, s);
+    return e != hipSuccess ? e : launch_enc_test(d, dt, s, beside);
 }
 
 hipError_t launch_enc_in_run(const Dev &d, double dt, int set, hipStream_t s)

@@ -71,6 +71,33 @@ struct nb_ctx {
     int res_max_group = 0, res_fail = 0;
 };
 
+namespace nb {
+
+// Waves that share one tile pair of the symmetric force (one tile pair per
+// workgroup).  One wave takes a pair of tiles of 64 in 10 us and of 128 in 24 us, so
+// that few pairs leave the chip idle, and as many as a few per wave slot (3072)
+// leave its last round half empty; each further wave stages and sums up for itself.
+// The force kernel alone, 1 / 2 / 4 waves: tiles of 64, 1001 bodies (136 pairs) 10.0
+// / 7.2 / 5.5 us, 3001 bodies (1128) 13.7 / 11.3 / 11.2 us in FP64 and 11.4 / 8.8 /
+// 9.6 us in FP32C, 6000 bodies (4465) 26.3 / 26.9 / 28.3 us; tiles of 128, 5003
+// bodies (820) 25.2 / 20.6 / 19.7 us, 10000 (3160) 63.3 / 54.0 / 52.7 us, 131072
+// (524800) 7540 / 7681 / 8212 us.  Steps with their encounter checks, whose small
+// kernels run in the gaps: FP64 11000 bodies (3741) 91.3 / 88.5 / 91.1 us, 13000 (5253)
+// 116.3 / 112.3 / 115.4 us, 18000 (9951) 187.7 / 187.0 / 197.0 us, 20011 (12403) 220.4 /
+// 223.4 / 235.8 us (the kernel alone 179.0 / 176.6 us), 26000 (20706) 335.6 / 344.6 us
+// (292.8 / 292.4 us), 32000 (31375) 494 / 506 / 533 us; FP32C, whose shorter pair terms leave
+// more of the time to each wave's own part, 12000 (4465) 83.9 / 79.4 / 82.4 us, 13000 93.7
+// / 89.9 / 96.2 us, 14000 (6105) 97.1 / 97.6 / 107.4 us, 16384 (8256) 122.3 / 120.1 / 133.2
+// us, 20011 164.9 / 168.3 / 189.2 us.
+int sym_waves(int nitems, const Params &p)
+{
+    if (p.force_r == 1)
+        return nitems < 1024 ? 4 : (nitems < 4096 ? 2 : 1);
+    return nitems < 4096 ? 4 : (nitems < (p.mode == 1 ? 5400 : 15000) ? 2 : 1);
+}
+
+}  // namespace nb
+
 namespace {
 
 constexpr size_t kAlign = 256;
@@ -782,6 +809,10 @@ size_t carve(const Params &p, int nsys, int ntot, int enc_cap, const Tables &t, 
     d.force_sym = t.force_sym ? 1 : 0;
     d.sym_g = t.sym_g;
     d.force_rsort = t.force_rsort ? 1 : 0;
+    // (launch_enc_test says why the lines lie here)
+    d.pair_waves = 1;
+    if (nsys == 1 && t.force_sym && t.sym_g == 1 && sym_waves(d.nfw, p) == 1)
+        d.pair_waves = !t.force_rsort ? 4 : (d.nfw > 8256 ? 2 : 1);
     d.nrtile = t.nrtile;
     d.rord = d.force_rsort ? (int *)take((size_t)ntot * sizeof(int)) : nullptr;
     d.rtf = d.force_rsort ? (int *)take((size_t)nsys * sizeof(int)) : nullptr;
@@ -975,7 +1006,7 @@ int enqueue_run(nb_ctx *c, double dt, int steps)
         if (in_run)
             HIP_OK(c, launch_enc_in_run(d, dt, par, c->side));
         else
-            HIP_OK(c, launch_encounters(d, dt, c->side));
+            HIP_OK(c, launch_encounters(d, dt, c->side, true));
         if (in_run && k == steps - 1)
             HIP_OK(c, launch_enc_run_end(d, steps, c->side));
         HIP_OK(c, hipEventRecord(c->ev_join[par], c->side));
