@@ -93,8 +93,9 @@ typedef struct nb_params {
     int32_t force_jchunk; /* sources per force work item (0: tuned default) */
     int32_t force_r;      /* targets per lane in the force kernel: 1, 2 or 4 (0: the tuning
                              table's, else by the number of tile pairs) */
-    int32_t enc_jchunk;   /* most sources per work item of the direct encounter check (0: 1024;
-                             halved while the items are too few to fill the GPU) */
+    int32_t enc_jchunk;   /* most sources per work item of the direct encounter check (0: 1024,
+                             which is also the largest used; halved while the items are too
+                             few to fill the GPU) */
     int32_t enc_algo;     /* encounter check: 0 automatic (1 or 3 for systems of up to about
                              10000 bodies, 2 for larger ones, whose steps hide it behind the
                              force; nb_encounters after nb_drift then still runs 1 up to about
@@ -107,10 +108,13 @@ typedef struct nb_params {
                              blocks in one tile loop; FP32C, every body big, resolve 0 and
                              the symmetric force, else 2; nb_encounters and nb_force run as
                              with 2) */
-    int32_t step_algo;    /* nb_step: 0 automatic (the tuning table's choice, else one persistent
-                             launch for systems of up to 256 bodies, which then leaves the
-                             drift arcs and the list of the last step as launches per phase
-                             do, else 1), 1 one launch per phase over all systems (HIP graph),
+    int32_t step_algo;    /* nb_step: 0 automatic (the tuning table's choice; else, with the
+                             direct encounter check and without resolve, one persistent
+                             launch for up to 1536 systems of at most 128 bodies or 256 of at
+                             most 256, which leaves the drift arcs and the list of the last
+                             step as launches per phase do, and whose pairs are FP64 also in
+                             an FP32C context, whose uploads, nb_force and nb_events stay
+                             FP32C; else 1), 1 one launch per phase over all systems (HIP graph),
                              2 one persistent launch in which a workgroup owns a system for
                              many steps (FP64 pair arithmetic; systems of at most
                              NB_PERSISTENT_MAX_N bodies; not with resolve; keeps no drift arcs
@@ -159,7 +163,9 @@ typedef struct nb_stats {
     int32_t overflow_steps; /* steps whose count exceeded the list capacity */
     int64_t kepler_fail;    /* failed Kepler solves summed over the steps */
     int64_t near_pairs;     /* pair evaluations inside the changeover zone (in FP64 for FP32C);
-                               with symmetric tile pairs one evaluation serves both bodies */
+                               with symmetric tile pairs one evaluation serves both bodies, and
+                               is counted once (the persistent launches count like the
+                               context's force) */
     int64_t resolved_groups; /* resolve: groups integrated by Bulirsch-Stoer, summed */
     int64_t resolved_bodies; /* resolve: their members, summed */
     int32_t max_group;      /* resolve: largest group */
@@ -344,9 +350,11 @@ int nb_events(nb_ctx *ctx, const nb_event_params *ep, nb_event_counts *counts, i
  * bodies.  Outputs (host or device per `where`, each may be NULL): off_out[nsys+1]
  * the new offsets, nbig_out[nsys] the new big-body counts, index[new ntot] the
  * old index of every kept body.  NB_E_NOT_READY without nb_events on the current
- * state; NB_E_WORKSPACE if the new layout needs more workspace than the context
- * has (possible only when an automatic algorithm choice changes with the sizes):
- * the context is then left as it was. */
+ * state.  The automatic choices start again for the new sizes; where a fresh
+ * context of these would need more workspace than this one has, its force tiles
+ * and if need be its encounter check stay as they were (the same pairs and
+ * lists, other rounding).  NB_E_WORKSPACE if even that does not fit: the context
+ * is then left as it was. */
 int nb_compact(nb_ctx *ctx, int32_t *off_out, int32_t *nbig_out, int32_t *index, int where);
 
 /* Per system s (host arrays): E[s] total energy, EK[s] the changeover-weighted
@@ -383,7 +391,9 @@ int nb_time_kernel(nb_ctx *ctx, int which, int reps, double dt, double *ms_per_l
  * be NULL): force 1 (ordered pairs), 2 (symmetric tile pairs), 3 (few-source
  * kernels) or 4 (symmetric tile pairs over the radial order); encounter check 1 (direct), 2 (sorted tiles), 3 (big bodies only as
  * partners) or 4 (sorted tiles inside the force pass); step launch 1
- * (per phase) or 2 (persistent). */
+ * (per phase) or 2 (persistent: asked for by step_algo 2 if nb_get_params
+ * returns that, else the automatic launch of small systems, which keeps the
+ * drift arcs of the last step). */
 int nb_get_choices(const nb_ctx *ctx, int32_t *force_algo, int32_t *enc_algo, int32_t *step_algo);
 
 /* The parameters the context runs with (tile and algorithm fields after the
