@@ -3673,13 +3673,13 @@ __device__ __noinline__ void enc_candidate(const SRec *__restrict__ srec, double
 
 // One wave per kept tile pair (A, B), the waves striding over the count: lane
 // L holds the FP32 filter records of body L of tile A (midpoint with widened
-// bound, chord with big flag: 32 B), tile B's sit in the wave's LDS slice, and
+// bound, chord with rc, deviation d with the bound of the mean deviation: 48 B),
+// tile B's sit in the wave's LDS slice, and
 // every lane meets the 64 sources in turn with the relative-chord filter in
 // FP32 and the relative deviation in it (kEncP), a superset of the pairs that can be
-// flagged (the widening covers the rounding).  A lane first meets tile B's bounds with the tile-pair test, as a
-// tile of one body whose FP32 records stand for small balls around its FP64
-// values (third record: the mean endpoint deviation and its radius).  The
-// pairs the filter keeps are queued in the wave's LDS and take the exact test
+// flagged (the widening covers the rounding).  A lane first meets tile B's bounds with
+// the tile-pair test, as a tile of one body whose FP32 records stand for small balls
+// around its FP64 values.  The pairs the filter keeps are queued in the wave's LDS and take the exact test
 // from the sorted FP64 records in memory 64 at a time, one per lane (with steps of a
 // radian most pairs of a dense ring pass the filter, and a test per pass would run on
 // a few lanes); a tile pair reads 6 KB of filter records instead of the 112-byte
